@@ -180,24 +180,77 @@ StreamPlan plan_stream(int rows, int N, int k, int dots_P = 0, int dots_B = 0) {
   return s;
 }
 
-// Plan of the tile-streamed pair-wise path of a MoL-scored selection: with
-// the MFMA dots kernel where the shape allows.
-StreamPlan plan_pairwise(const DevProb& pr, int k) {
-  return dots_mfma_supported(pr) ? plan_stream(pr.B, pr.N, k, pr.P, pr.B) : plan_stream(pr.B, pr.N, k);
+// The matrix-core pair-wise path (dots into a buffer, then the f16 / two-term
+// gating chain) for rows of sRow slots; other problems are scored in float32
+// with no buffer.
+bool pairwise_mfma(const DevProb& pr, long sRow) {
+  return dots_mfma_supported(pr) && phi_mfma_supported(pr) &&
+         static_cast<long>(pr.P) * pr.B * sRow < (1l << 32);   // the gating kernel's element offsets
 }
 
-// Score one tile of the pair-wise path into keys A (mode: GenMode).
-hipError_t pairwise_tile(const DevProb& pr, const StreamPlan& s, char* w, int mode, const float* bound,
-                         int n0, int nt, uint64_t* A, long strideA, hipStream_t st) {
-  if (s.sRow == 0)
-    return launch_phi_generic(pr, mode, bound, n0, nt, nullptr, nullptr, 0, nullptr, 0, 0, nullptr, 0, A,
-                              strideA, st);
-  float* sbuf = reinterpret_cast<float*>(w + s.offS);
-  const long pstride = s.sRow * pr.B;
-  hipError_t e = launch_dots_mfma(pr, n0, nt, kDotsToBuffer, sbuf, pstride, s.sRow, nullptr, 0, st);
+// Plan of the tile-streamed pair-wise path of a MoL-scored selection.
+StreamPlan plan_pairwise(const DevProb& pr, int k) {
+  if (dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
+    const StreamPlan s = plan_stream(pr.B, pr.N, k, pr.P, pr.B);
+    if (pairwise_mfma(pr, s.sRow)) return s;
+  }
+  return plan_stream(pr.B, pr.N, k);
+}
+
+// Score items [n0, n0 + nt) of the pair-wise path into keys (row stride
+// key_stride) or phi; sbuf: the plan's dots buffer (rows of sRow slots) or NULL.
+hipError_t pairwise_score(const DevProb& pr, float* sbuf, long sRow, int mode, const float* bound, int n0, int nt,
+                          float* phi, long phi_stride, uint64_t* keys, long key_stride, hipStream_t st) {
+  if (!sbuf)
+    return launch_mol_f32(pr, mode, bound, n0, nt, nullptr, nullptr, 0, phi, phi_stride, keys, key_stride, st);
+  const long pstride = sRow * pr.B;
+  hipError_t e = launch_dots_mfma(pr, n0, nt, kDotsToBuffer, sbuf, pstride, sRow, nullptr, 0, st);
   if (e != hipSuccess) return e;
-  return (phi_mfma_supported(pr) ? launch_phi_mfma : launch_phi_generic)(
-      pr, mode, bound, n0, nt, nullptr, nullptr, 0, sbuf, pstride, s.sRow, nullptr, 0, A, strideA, st);
+  return launch_phi_mfma(pr, mode, bound, n0, nt, nullptr, nullptr, 0, sbuf, pstride, sRow, phi, phi_stride, keys,
+                         key_stride, st);
+}
+
+// Dense selection: the scores of every (query, item) pair in a buffer, then
+// one top-k kernel per row.  It replaces per-tile key sorts and per-range
+// lists wherever the buffer stays under kDenseMax bytes.
+constexpr size_t kDenseMax = size_t(512) << 20;
+// rows from this length on are reduced to bucket maxima by a launch of their
+// own (about 5 us) before the one-workgroup-per-row top-k reads them
+constexpr int kBucketMinN = 1 << 14;
+
+struct DensePlan {
+  long ld = 0;                     // floats per phi row (a multiple of 4)
+  long sRow = 0;                   // dots buffer row (0: no buffer)
+  int T = 0;                       // items per dots tile
+  size_t offPhi = 0, offBmax = 0, offS = 0, bytes = 0;
+};
+
+bool dense_fits(const DevProb& pr, int k) {
+  return k <= kTopkDenseMaxK && 4ul * pr.B * ((pr.N + 3l) & ~3l) <= kDenseMax;
+}
+
+DensePlan plan_dense(const DevProb& pr, bool gating) {
+  DensePlan f;
+  f.ld = (pr.N + 3l) & ~3l;
+  f.T = pr.N;
+  size_t off = align_up(4ul * pr.B * f.ld);
+  if (pr.N >= kBucketMinN) {
+    f.offBmax = off;
+    off = align_up(off + 4ul * pr.B * bucket_row(pr.N, 16));
+  }
+  if (gating && dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
+    // dots tiles of at most 512 MB, whole 128-item GEMM tiles
+    const long T = std::max(1024l, std::min<long>(pr.N, (512l << 20) / (4l * pr.P * pr.B) / 128 * 128));
+    const long sRow = dots_buffer_row(static_cast<int>(T));
+    if (pairwise_mfma(pr, sRow)) {
+      f.T = static_cast<int>(T);
+      f.sRow = sRow;
+      f.offS = off;
+      off = align_up(off + 4ul * pr.P * pr.B * sRow);
+    }
+  }
+  f.bytes = off;
+  return f;
 }
 
 // Reduce rows of `len` keys held in buffer A (stride strideA) to the top k,
@@ -294,7 +347,7 @@ RerankPlan plan_rerank(const DevProb& pr, int C, int k) {
   r.offFinal = off; off = align_up(off + 8ul * B * k);
   r.offUniq = off;  off = align_up(off + 4ul * B * C);
   r.offNu = off;    off = align_up(off + 4ul * B);
-  if (!rerank_supported(pr, k) && dots_mfma_supported(pr)) {
+  if (!rerank_supported(pr, k) && pairwise_mfma(pr, dots_buffer_row(C))) {
     r.sRow = dots_buffer_row(C);
     r.offS = off;   off = align_up(off + 4ul * pr.P * B * r.sRow);
   }
@@ -429,13 +482,20 @@ size_t per_embd_ws_bytes(const DevProb& pr, int kp) {
   return plan_stream(pr.B * pr.P, pr.N, kp).bytes;
 }
 
-size_t exact_ws_bytes(const DevProb& pr, int k) {
+// per-range lists or streamed key tiles: the form of every k and size
+size_t exact_list_ws_bytes(const DevProb& pr, int k) {
   return fused_supported(pr, k) ? plan_fused_exact(pr, k).bytes : plan_pairwise(pr, k).bytes;
+}
+
+size_t exact_ws_bytes(const DevProb& pr, int k) {
+  if (!fused_supported(pr, k) && dense_fits(pr, k)) return plan_dense(pr, true).bytes;
+  return exact_list_ws_bytes(pr, k);
 }
 
 size_t maxdot_ws_bytes(const DevProb& pr, int k) {
   if (fused_maxdot_supported(pr, k)) return plan_fused_exact(pr, k, true).bytes;
-  return dots_maxkeys_supported(pr) ? plan_stream(pr.B, pr.N, k).bytes : plan_pairwise(pr, k).bytes;
+  if (!dots_maxkeys_supported(pr) && dense_fits(pr, k)) return plan_dense(pr, false).bytes;
+  return plan_stream(pr.B, pr.N, k).bytes;
 }
 
 // Algorithm 1 workspace: per-component lists, the rerank output over G,
@@ -490,11 +550,42 @@ int check_two_pass_k(const mol_problem* prob, int32_t k) {
 // timed_op: mol_op code under which the main kernel is timed, -1 for none.
 // ---------------------------------------------------------------------------
 
+// Dense scores of the whole corpus, then the top-k.
+int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out_score, int32_t* out_idx, char* w,
+              int timed_op, hipStream_t st) {
+  const DensePlan f = plan_dense(pr, mode != kGenMaxDot);
+  float* phi = reinterpret_cast<float*>(w + f.offPhi);
+  float* bmax = f.offBmax ? reinterpret_cast<float*>(w + f.offBmax) : nullptr;
+  const long bstride = bucket_row(pr.N, 16);
+  float* sbuf = f.sRow ? reinterpret_cast<float*>(w + f.offS) : nullptr;
+  for (long n0 = 0; n0 < pr.N; n0 += f.T) {
+    const int nt = static_cast<int>(std::min<long>(f.T, pr.N - n0));
+    MOL_TIMED_LAUNCH(timed_op, st,
+                     pairwise_score(pr, sbuf, f.sRow, mode, bound, static_cast<int>(n0), nt, phi + n0, f.ld, nullptr,
+                                    0, st),
+                     "score tile");
+  }
+  DenseRows r;
+  r.phi = phi;
+  r.phi_stride = f.ld;
+  r.L = pr.N;
+  r.skip_neg_inf = mode == kGenBounded;
+  r.bmax = bmax;
+  r.bmax_stride = bstride;
+  if (bmax)
+    MOL_TRY_HIP(launch_bucket_max(phi, f.ld, pr.B, pr.N, 1.f, bmax, bstride, st), "bucket maxima");
+  MOL_TRY_HIP(launch_topk_dense(r, pr.B, k, out_score, out_idx, st), "dense top-k");
+  return MOL_OK;
+}
+
 // Exact MoL top-k over the corpus; with `bound` ([B] floats) only the items
-// whose max_p s_p can reach bound[b] are ranked.
+// whose max_p s_p can reach bound[b] are ranked.  lists: keep to the form
+// with per-range lists or key tiles (mol_topk_exact_noalloc's small scratch).
 int run_exact(const DevProb& pr, int k, const float* bound, float* out_score, int32_t* out_idx,
-              char* w, int timed_op, hipStream_t st) {
+              char* w, int timed_op, hipStream_t st, bool lists = false) {
   int rc;
+  if (!lists && !fused_supported(pr, k) && dense_fits(pr, k))
+    return run_dense(pr, k, bound ? kGenBounded : kGenPhi, bound, out_score, out_idx, w, timed_op, st);
   if (fused_supported(pr, k)) {
     const FusedExactPlan f = plan_fused_exact(pr, k);
     uint64_t* partial = reinterpret_cast<uint64_t*>(w + f.s.offA);
@@ -508,8 +599,9 @@ int run_exact(const DevProb& pr, int k, const float* bound, float* out_score, in
   }
   const StreamPlan s = plan_pairwise(pr, k);
   const int mode = bound ? kGenBounded : kGenPhi;
+  float* sbuf = s.sRow ? reinterpret_cast<float*>(w + s.offS) : nullptr;
   auto tile = [&](int n0, int nt, uint64_t* A, long strideA) {
-    return pairwise_tile(pr, s, w, mode, bound, n0, nt, A, strideA, st);
+    return pairwise_score(pr, sbuf, s.sRow, mode, bound, n0, nt, nullptr, 0, A, strideA, st);
   };
   return stream_topk(s, pr.N, w, tile, out_score, out_idx, st);
 }
@@ -536,9 +628,10 @@ int run_maxdot(const DevProb& pr, int k, float* out_score, int32_t* out_idx, cha
     };
     return stream_topk(s, pr.N, w, tile, out_score, out_idx, st);
   }
-  const StreamPlan s = plan_pairwise(pr, k);
+  if (dense_fits(pr, k)) return run_dense(pr, k, kGenMaxDot, nullptr, out_score, out_idx, w, timed_op, st);
+  const StreamPlan s = plan_stream(pr.B, pr.N, k);
   auto tile = [&](int n0, int nt, uint64_t* A, long strideA) {
-    return pairwise_tile(pr, s, w, kGenMaxDot, nullptr, n0, nt, A, strideA, st);
+    return launch_mol_f32(pr, kGenMaxDot, nullptr, n0, nt, nullptr, nullptr, 0, nullptr, 0, A, strideA, st);
   };
   return stream_topk(s, pr.N, w, tile, out_score, out_idx, st);
 }
@@ -584,7 +677,7 @@ int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx
   const bool gemm = dots_mfma_supported(pr);
   auto tile = [&](int n0, int nt, uint64_t* A, long strideA) {
     return gemm ? launch_dots_mfma(pr, n0, nt, kDotsToKeys, nullptr, 0, 0, A, strideA, st)
-                : launch_dots_generic(pr, n0, nt, A, strideA, st);
+                : launch_mol_f32(pr, kGenDotKeys, nullptr, n0, nt, nullptr, nullptr, 0, nullptr, 0, A, strideA, st);
   };
   return stream_topk(s, pr.N, w, tile, out_dot, out_idx, st);
 }
@@ -609,16 +702,21 @@ int run_rerank(const DevProb& pr, const int32_t* cand, int C, const int32_t* can
     if ((rc = reduce_rows(r.s, w, L0, fin, k, st))) return rc;
   } else {
     // candidates' dot products on MFMA where the shape allows, then the
-    // pair-wise gating kernel
-    float* sbuf = r.sRow ? reinterpret_cast<float*>(w + r.offS) : nullptr;
-    const long pstride = r.sRow * pr.B;
-    if (sbuf)
+    // pair-wise gating kernel; float32 otherwise
+    const int mode = negate ? kGenNegPhi : kGenPhi;
+    if (r.sRow) {
+      float* sbuf = reinterpret_cast<float*>(w + r.offS);
+      const long pstride = r.sRow * pr.B;
       MOL_TRY_HIP(launch_dots_mfma_gather(pr, uniq, nu, CT, CT, sbuf, pstride, r.sRow, st), "rerank dots");
-    MOL_TIMED_LAUNCH(timed_op, st,
-                     (sbuf && phi_mfma_supported(pr) ? launch_phi_mfma : launch_phi_generic)(
-                         pr, negate ? kGenNegPhi : kGenPhi, nullptr, 0, CT, uniq, nu, CT, sbuf, pstride,
-                         r.sRow, nullptr, 0, A, r.s.strideA, st),
-                     "rerank score");
+      MOL_TIMED_LAUNCH(timed_op, st,
+                       launch_phi_mfma(pr, mode, nullptr, 0, CT, uniq, nu, CT, sbuf, pstride, r.sRow, nullptr, 0, A,
+                                       r.s.strideA, st),
+                       "rerank score");
+    } else {
+      MOL_TIMED_LAUNCH(timed_op, st,
+                       launch_mol_f32(pr, mode, nullptr, 0, CT, uniq, nu, CT, nullptr, 0, A, r.s.strideA, st),
+                       "rerank score");
+    }
     if ((rc = reduce_rows(r.s, w, CT, fin, k, st))) return rc;
   }
   MOL_TRY_HIP(launch_decode(fin, k, pr.B, k, out_score, out_idx, st), "decode");
@@ -775,12 +873,14 @@ int mol_score(const mol_problem* prob, int32_t n_begin, int32_t n_count, float* 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const DevProb pr = dev_prob(prob);
   if (fused_supported(pr, 1)) {
-    MOL_TIMED_LAUNCH(MOL_OP_SCORE, st, launch_fused_dense(pr, n_begin, n_count, phi, st), "mol_score (fused)");
+    MOL_TIMED_LAUNCH(MOL_OP_SCORE, st,
+                     launch_fused_dense(pr, n_begin, n_count, phi, st),
+                     "mol_score (fused)");
     return MOL_OK;
   }
   MOL_TIMED_LAUNCH(MOL_OP_SCORE, st,
-                   launch_phi_generic(pr, kGenPhi, nullptr, n_begin, n_count, nullptr, nullptr, 0, nullptr, 0,
-                                      0, phi, n_count, nullptr, 0, st),
+                   launch_mol_f32(pr, kGenPhi, nullptr, n_begin, n_count, nullptr, nullptr, 0, phi, n_count, nullptr,
+                                  0, st),
                    "mol_score");
   return MOL_OK;
 }
@@ -804,13 +904,13 @@ int mol_topk_exact_noalloc(const mol_problem* prob, int32_t k, float* out_score,
   if ((rc = check_k(k, prob->N, "k"))) return rc;
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  const size_t need = exact_ws_bytes(pr, k);
+  const size_t need = exact_list_ws_bytes(pr, k);
   if (need > MOL_NOALLOC_SCRATCH_BYTES)
     return fail(MOL_EWORKSPACE, "this problem needs %zu bytes of scratch; the library holds %zu "
                 "(use mol_topk_exact with a workspace)", need, static_cast<size_t>(MOL_NOALLOC_SCRATCH_BYTES));
   char* w = static_cast<char*>(scratch_ptr());
   if (!w) return MOL_EHIP;
-  return run_exact(pr, k, nullptr, out_score, out_idx, w, MOL_OP_TOPK_EXACT, static_cast<hipStream_t>(stream));
+  return run_exact(pr, k, nullptr, out_score, out_idx, w, MOL_OP_TOPK_EXACT, static_cast<hipStream_t>(stream), true);
 }
 
 int mol_topk_exact_bounded(const mol_problem* prob, int32_t k, const float* bound, float* out_score,

@@ -1,168 +1,9 @@
-// Generic gfx950 kernels of the MoL library: one thread per (query, item)
-// pair, float32 arithmetic, any supported shape and both storage types.
-// They serve the float32 problems and every shape the MFMA kernels do not
-// cover, and provide the selection machinery (segmented bitonic top-k,
-// key decoding), the candidate deduplication of the approximate path and
-// the TopKAvg materialisation.
+// Supporting gfx950 kernels of the MoL library: the selection machinery
+// (segmented bitonic top-k, key decoding), the candidate deduplication of the
+// approximate path, the gap certificates and the TopKAvg materialisation.
 #include "mol_kernels.h"
 
 namespace mol {
-
-// ---------------------------------------------------------------------------
-// MoL score of one (query, item) pair, float32 (Eq. 1 with the two-layer
-// SiLU gating MLP of Appendix A.3).  Gating weights live in LDS as float32,
-// rows padded with zeros to PMAX so that a row is read as aligned 16-byte
-// vectors (every lane reads the same address: one broadcast per read):
-// sW1 [H][PMAX] = W1, sW2t [H][PMAX] = W2 transposed, sb1 [H],
-// sc [PMAX] = a_q[b] + b2.
-// ---------------------------------------------------------------------------
-template <typename T, int PMAX>
-__device__ __forceinline__ void pair_dots(const DevProb& pr, int b, long n, float (&s)[PMAX]) {
-  const T* Qb = static_cast<const T*>(pr.Q) + static_cast<long>(b) * pr.Pq * pr.d;
-  const T* Xn = static_cast<const T*>(pr.X) + n * pr.d;
-  const long xstride = static_cast<long>(pr.N) * pr.d;
-#pragma unroll
-  for (int p = 0; p < PMAX; ++p) {
-    s[p] = 0.f;
-    if (p < pr.P) {
-      const int pq = p / pr.Px, px = p - (p / pr.Px) * pr.Px;
-      const T* q = Qb + pq * pr.d;
-      const T* x = Xn + px * xstride;
-      float acc = 0.f;
-      for (int t = 0; t < pr.d; ++t) acc = fmaf(to_f32(q[t]), to_f32(x[t]), acc);
-      s[p] = acc;
-    }
-  }
-}
-
-template <int PMAX>
-__device__ __forceinline__ float pair_phi(const DevProb& pr, long n, const float (&s)[PMAX],
-                                          const float* sW1, const float* sW2t,
-                                          const float* sb1, const float* sc) {
-  constexpr float kLog2e = 1.4426950408889634f;
-  const int P = pr.P, H = pr.H;
-  float l[PMAX];
-#pragma unroll
-  for (int p = 0; p < PMAX; ++p) l[p] = (p < P) ? sc[p] + pr.a_x[n * P + p] : 0.f;
-  for (int j = 0; j < H; ++j) {
-    const float* w1 = sW1 + j * PMAX;
-    const float* w2 = sW2t + j * PMAX;
-    float u = sb1[j];
-#pragma unroll
-    for (int p = 0; p < PMAX; ++p) u = fmaf(w1[p], s[p], u);   // padded slots are zero
-    // SiLU: u sigma(u), sigma(u) = 1 / (1 + e^-u)
-    const float h = u * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-kLog2e * u));
-#pragma unroll
-    for (int p = 0; p < PMAX; ++p) l[p] = fmaf(w2[p], h, l[p]);
-  }
-  float m = l[0];
-#pragma unroll
-  for (int p = 1; p < PMAX; ++p)
-    if (p < P) m = fmaxf(m, l[p]);
-  float den = 0.f, num = 0.f;
-#pragma unroll
-  for (int p = 0; p < PMAX; ++p) {
-    if (p < P) {
-      const float w = __builtin_amdgcn_exp2f(kLog2e * (l[p] - m));
-      den += w;
-      num = fmaf(w, s[p], num);
-    }
-  }
-  return num * __builtin_amdgcn_rcpf(den);
-}
-
-// Grid: x over items (256 per block), y over queries.  Items are either the
-// contiguous range n_begin .. n_begin+n_count-1 or, when `items` is given,
-// items[b*item_stride + i] for i < item_count[b].  Writes a score (float32)
-// and/or sort keys; key slots past a query's item count are cleared to 0
-// (empty).  The score is, by `mode`:
-//   kGenPhi      phi;
-//   kGenBounded  phi, for items whose m = max_p s_p plus the rounding
-//                margin reaches bound[b] (phi <= m: Algorithm 1's range
-//                condition); other items get an empty key;
-//   kGenMaxDot   m itself (no gating MLP);
-//   kGenNegPhi   -phi (the smallest phi as the top-1 of the negated keys).
-template <typename T, int PMAX>
-__global__ __launch_bounds__(256) void k_phi_generic(
-    DevProb pr, int mode, const float* __restrict__ bound, int n_begin, int n_count,
-    const int32_t* __restrict__ items, const int32_t* __restrict__ item_count, long item_stride,
-    const float* __restrict__ sbuf, long s_pstride, long s_bstride,
-    float* __restrict__ phi, long phi_stride, uint64_t* __restrict__ keys, long key_stride) {
-  extern __shared__ float smem[];
-  const int P = pr.P, H = pr.H;
-  float* sW1 = smem;
-  float* sW2t = sW1 + H * PMAX;
-  float* sb1 = sW2t + H * PMAX;
-  float* sc = sb1 + H;
-  const int b = blockIdx.y;
-  if (mode != kGenMaxDot) {
-    for (int i = threadIdx.x; i < H * PMAX; i += blockDim.x) {
-      const int j = i / PMAX, p = i - (i / PMAX) * PMAX;
-      sW1[i] = p < P ? to_f32(static_cast<const T*>(pr.W1)[j * P + p]) : 0.f;
-      sW2t[i] = p < P ? to_f32(static_cast<const T*>(pr.W2)[p * H + j]) : 0.f;
-    }
-    for (int i = threadIdx.x; i < H; i += blockDim.x) sb1[i] = pr.b1[i];
-    for (int i = threadIdx.x; i < PMAX; i += blockDim.x)
-      sc[i] = i < P ? pr.a_q[static_cast<long>(b) * P + i] + pr.b2[i] : 0.f;
-  }
-  __syncthreads();
-
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_count) return;
-  const int cnt = items ? item_count[b] : n_count;
-  if (i >= cnt) {
-    if (keys) keys[b * key_stride + i] = 0;
-    return;
-  }
-  const long n = items ? static_cast<long>(items[b * item_stride + i]) : static_cast<long>(n_begin) + i;
-  float s[PMAX];
-  if (sbuf) {   // dot products formed by the MFMA kernel
-#pragma unroll
-    for (int p = 0; p < PMAX; ++p) s[p] = p < P ? sbuf[p * s_pstride + b * s_bstride + i] : 0.f;
-  } else {
-    pair_dots<T, PMAX>(pr, b, n, s);
-  }
-  float v;
-  if (mode == kGenBounded || mode == kGenMaxDot) {
-    float m = s[0], mabs = fabsf(s[0]);
-#pragma unroll
-    for (int p = 1; p < PMAX; ++p)
-      if (p < P) {
-        m = fmaxf(m, s[p]);
-        mabs = fmaxf(mabs, fabsf(s[p]));
-      }
-    if (mode == kGenMaxDot) {
-      v = m;
-    } else if (m + 0x1p-12f * (1.f + mabs) < bound[b]) {   // phi <= m: cannot reach the bound
-      if (phi) phi[b * phi_stride + i] = -__builtin_inff();
-      if (keys) keys[b * key_stride + i] = 0;
-      return;
-    } else {
-      v = pair_phi<PMAX>(pr, n, s, sW1, sW2t, sb1, sc);
-    }
-  } else {
-    v = pair_phi<PMAX>(pr, n, s, sW1, sW2t, sb1, sc);
-    if (mode == kGenNegPhi) v = -v;
-  }
-  if (phi) phi[b * phi_stride + i] = v;
-  if (keys) keys[b * key_stride + i] = make_key(v, static_cast<int32_t>(n));
-}
-
-// Per-component dot products as sort keys, rows r = b * P + p
-// (TopKDotProduct for every component).  Grid: x over items, y over queries.
-template <typename T, int PMAX>
-__global__ __launch_bounds__(256) void k_dots_generic(DevProb pr, int n_begin, int n_count,
-                                                      uint64_t* __restrict__ keys, long key_stride) {
-  const int b = blockIdx.y;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_count) return;
-  const long n = static_cast<long>(n_begin) + i;
-  float s[PMAX];
-  pair_dots<T, PMAX>(pr, b, n, s);
-#pragma unroll
-  for (int p = 0; p < PMAX; ++p)
-    if (p < pr.P) keys[(static_cast<long>(b) * pr.P + p) * key_stride + i] = make_key(s[p], static_cast<int32_t>(n));
-}
 
 // ---------------------------------------------------------------------------
 // Segmented top-k: block (seg, row) takes keys in[row][seg*S .. seg*S+S)
@@ -486,79 +327,6 @@ __global__ void k_avg_embed(const T* __restrict__ in, long sc, long sm, int ncom
 // ---------------------------------------------------------------------------
 // Host-side launchers.
 // ---------------------------------------------------------------------------
-static size_t phi_smem_bytes(const DevProb& pr, int pmax) {
-  return sizeof(float) * (2 * static_cast<size_t>(pr.H) * pmax + pr.H + pmax);
-}
-
-template <typename T, int PMAX>
-static hipError_t launch_phi_t(const DevProb& pr, int mode, const float* bound, int n_begin, int n_count,
-                               const int32_t* items, const int32_t* item_count, long item_stride,
-                               const float* sbuf, long s_pstride, long s_bstride,
-                               float* phi, long phi_stride, uint64_t* keys, long key_stride,
-                               hipStream_t st) {
-  const size_t smem = mode == kGenMaxDot ? 0 : phi_smem_bytes(pr, PMAX);
-  if (smem > 65536) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_phi_generic<T, PMAX>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(smem));
-    if (e != hipSuccess) return e;
-  }
-  dim3 grid((n_count + 255) / 256, pr.B);
-  hipLaunchKernelGGL((k_phi_generic<T, PMAX>), grid, dim3(256), smem, st, pr, mode, bound, n_begin,
-                     n_count, items, item_count, item_stride, sbuf, s_pstride, s_bstride, phi, phi_stride,
-                     keys, key_stride);
-  return hipGetLastError();
-}
-
-template <typename T>
-static hipError_t launch_phi_p(const DevProb& pr, int mode, const float* bound, int n_begin, int n_count,
-                               const int32_t* items, const int32_t* item_count, long item_stride,
-                               const float* sbuf, long s_pstride, long s_bstride,
-                               float* phi, long phi_stride, uint64_t* keys, long key_stride,
-                               hipStream_t st) {
-  if (pr.P <= 4)
-    return launch_phi_t<T, 4>(pr, mode, bound, n_begin, n_count, items, item_count, item_stride, sbuf,
-                              s_pstride, s_bstride, phi, phi_stride, keys, key_stride, st);
-  if (pr.P <= 16)
-    return launch_phi_t<T, 16>(pr, mode, bound, n_begin, n_count, items, item_count, item_stride, sbuf,
-                               s_pstride, s_bstride, phi, phi_stride, keys, key_stride, st);
-  return launch_phi_t<T, 64>(pr, mode, bound, n_begin, n_count, items, item_count, item_stride, sbuf,
-                             s_pstride, s_bstride, phi, phi_stride, keys, key_stride, st);
-}
-
-hipError_t launch_phi_generic(const DevProb& pr, int mode, const float* bound, int n_begin, int n_count,
-                              const int32_t* items, const int32_t* item_count, long item_stride,
-                              const float* sbuf, long s_pstride, long s_bstride,
-                              float* phi, long phi_stride, uint64_t* keys, long key_stride,
-                              hipStream_t st) {
-  if (n_count <= 0) return hipSuccess;
-  if (pr.dtype == MOL_BF16)
-    return launch_phi_p<bf16_t>(pr, mode, bound, n_begin, n_count, items, item_count, item_stride, sbuf,
-                                s_pstride, s_bstride, phi, phi_stride, keys, key_stride, st);
-  return launch_phi_p<float>(pr, mode, bound, n_begin, n_count, items, item_count, item_stride, sbuf,
-                             s_pstride, s_bstride, phi, phi_stride, keys, key_stride, st);
-}
-
-template <typename T>
-static hipError_t launch_dots_t(const DevProb& pr, int n_begin, int n_count, uint64_t* keys,
-                                long key_stride, hipStream_t st) {
-  dim3 grid((n_count + 255) / 256, pr.B);
-  if (pr.P <= 4)
-    hipLaunchKernelGGL((k_dots_generic<T, 4>), grid, dim3(256), 0, st, pr, n_begin, n_count, keys, key_stride);
-  else if (pr.P <= 16)
-    hipLaunchKernelGGL((k_dots_generic<T, 16>), grid, dim3(256), 0, st, pr, n_begin, n_count, keys, key_stride);
-  else
-    hipLaunchKernelGGL((k_dots_generic<T, 64>), grid, dim3(256), 0, st, pr, n_begin, n_count, keys, key_stride);
-  return hipGetLastError();
-}
-
-hipError_t launch_dots_generic(const DevProb& pr, int n_begin, int n_count, uint64_t* keys,
-                               long key_stride, hipStream_t st) {
-  if (n_count <= 0) return hipSuccess;
-  if (pr.dtype == MOL_BF16) return launch_dots_t<bf16_t>(pr, n_begin, n_count, keys, key_stride, st);
-  return launch_dots_t<float>(pr, n_begin, n_count, keys, key_stride, st);
-}
-
 int segment_size_for(int L, int k) {
   // One segment when it fits, else the largest segment (always >= 4k so
   // every pass shrinks the rows).

@@ -5,19 +5,42 @@
 
 namespace mol {
 
-// Generic (one thread per pair, float32 arithmetic) kernels.
-// Score of the pair-wise kernel: phi; phi restricted to items whose
-// max_p s_p can reach bound[b]; max_p s_p; -phi.
-enum GenMode { kGenPhi = 0, kGenBounded = 1, kGenMaxDot = 2, kGenNegPhi = 3 };
-// sbuf: NULL, or the component dot products of items n_begin + i laid out
-// as sbuf[p * s_pstride + b * s_bstride + i] (contiguous ranges only).
-hipError_t launch_phi_generic(const DevProb& pr, int mode, const float* bound, int n_begin, int n_count,
-                              const int32_t* items, const int32_t* item_count, long item_stride,
-                              const float* sbuf, long s_pstride, long s_bstride,
-                              float* phi, long phi_stride, uint64_t* keys, long key_stride,
-                              hipStream_t st);
-hipError_t launch_dots_generic(const DevProb& pr, int n_begin, int n_count, uint64_t* keys,
-                               long key_stride, hipStream_t st);
+// Float32 scoring on f32 MFMAs, any shape and storage type (mol_f32.hip).
+// Score by mode: phi; phi restricted to items whose max_p s_p can reach
+// bound[b]; max_p s_p; -phi; or no score, the component dot products
+// themselves as sort keys in rows (b, p).
+enum GenMode { kGenPhi = 0, kGenBounded = 1, kGenMaxDot = 2, kGenNegPhi = 3, kGenDotKeys = 4 };
+// Items n_begin + i, i < n_count, or (items != NULL) candidate i of query
+// b's list items[b * item_stride ..], item_count[b] of them.  Writes phi
+// (float32) and / or sort keys; an excluded item gets -inf or an empty key.
+hipError_t launch_mol_f32(const DevProb& pr, int mode, const float* bound, int n_begin, int n_count,
+                          const int32_t* items, const int32_t* item_count, long item_stride, float* phi,
+                          long phi_stride, uint64_t* keys, long key_stride, hipStream_t st);
+
+// Top-k of dense score rows, decoded (mol_topk.hip): phi [rows][phi_stride],
+// L scores a row (row_len: NULL or valid counts), bmax: NULL or per-bucket
+// maxima (of sign * phi, times sign; rows then hold L scores), ids: NULL or the item of each column.  Rows are
+// ranked by sign * phi; skip_neg_inf: a score of -inf is an excluded column.
+constexpr int kTopkDenseMaxK = 512;
+struct DenseRows {
+  const float* phi = nullptr;
+  long phi_stride = 0;
+  int L = 0;
+  const int32_t* row_len = nullptr;
+  const float* bmax = nullptr;   // bucket W i + r: columns 4 W i + r + W j, j < 4
+  long bmax_stride = 0;
+  int W = 16;
+  const int32_t* ids = nullptr;
+  long ids_stride = 0;
+  float sign = 1.f;
+  bool skip_neg_inf = false;
+};
+// floats of a row of bucket maxima
+inline long bucket_row(long L, int W) { return (L + 4 * W - 1) / (4 * W) * W; }
+// bucket maxima of sign * phi, W = 16
+hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L, float sign, float* bmax,
+                             long bmax_stride, hipStream_t st);
+hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_score, int32_t* out_idx, hipStream_t st);
 
 // Component dot products on MFMA for the generic shapes (bf16, d % 32 == 0):
 // into a buffer s[p][b][i] (row stride dots_buffer_row(nt) floats, p stride
@@ -48,7 +71,9 @@ hipError_t launch_dots_mfma_gather(const DevProb& pr, const int32_t* items, cons
                                    hipStream_t st);
 
 // Pair-wise gating on MFMA over the dots buffer (bf16, P <= 64, H <= 128):
-// the same modes, arguments and outputs as launch_phi_generic with sbuf set.
+// the modes, item arguments and outputs of launch_mol_f32 (no max-dot form;
+// P * s_pstride below 2^32).  sbuf: the component dot products of slot i laid
+// out as sbuf[p * s_pstride + b * s_bstride + i].
 bool phi_mfma_supported(const DevProb& pr);
 hipError_t launch_phi_mfma(const DevProb& pr, int mode, const float* bound, int n_begin, int n_count,
                            const int32_t* items, const int32_t* item_count, long item_stride,

@@ -17,8 +17,8 @@
 //
 // Lane (c = lane % 16, g = lane / 16) holds item c's dot products for the
 // run p = base(g) + mu, mu < 2 PXV, of the padded layout.  Modes and
-// outputs are those of the one-thread-per-pair kernel (GenMode); the
-// max-component mode, which has no gating chain, is left to that kernel.
+// outputs are those of the float32 kernel (GenMode); the max-component mode,
+// which has no gating chain, is left to that kernel.
 // PXV = 2 stands for P' = 16: the K = 16 gating chain (MolMlp16), whose lane
 // runs are p = 4 g + mu, mu < 4.
 #include <type_traits>
@@ -275,11 +275,10 @@ hipError_t launch_phi_mfma(const DevProb& pr, int mode, const float* bound, int 
                            uint64_t* keys, long key_stride, hipStream_t st) {
   if (n_count <= 0) return hipSuccess;
   if (!phi_mfma_supported(pr) || sbuf == nullptr) return hipErrorInvalidValue;
-  // the max-component mode has no gating chain (and may carry no gating
-  // input), and the kernel addresses a query's rows with 32-bit element offsets
-  if (mode == kGenMaxDot || static_cast<long>(pr.P) * s_pstride >= (1l << 32))
-    return launch_phi_generic(pr, mode, bound, n_begin, n_count, items, item_count, item_stride, sbuf, s_pstride,
-                              s_bstride, phi, phi_stride, keys, key_stride, st);
+  // no gating chain in the max-component mode; a query's rows are addressed
+  // with 32-bit element offsets
+  if (mode == kGenMaxDot || mode == kGenDotKeys || static_cast<long>(pr.P) * s_pstride >= (1l << 32))
+    return hipErrorInvalidValue;
   const long per_query = (static_cast<long>(n_count) + 15) / 16;   // 16-item steps per query
   const long groups = (pr.B + kPairQB - 1) / kPairQB;
   const long qb = std::min<long>(kPairQB, pr.B);

@@ -1,0 +1,354 @@
+// Top-k of dense float32 score rows (Definition 1's selection step), one
+// workgroup per row, straight to the decoded outputs.
+//
+// Every thread takes the maximum of its own share of the row (1024 disjoint
+// buckets).  k buckets whose maxima reach T hold k items scoring at least T,
+// so T = the k-th largest bucket maximum bounds the row's k-th score from
+// below, and about k + k^2 / 2048 items of the row reach it: those are
+// collected in LDS, ranked by counting and written out.  A row whose items
+// reaching T exceed the LDS list (massive ties, an adversarial order) is
+// finished by a radix search over its 64-bit sort keys, 8 bits a pass.
+//
+// What bounds it: one read of the row at a workgroup's rate (about 100 GB/s)
+// and a dozen barriers.  With per-bucket maxima from the kernel that scored
+// the row (bucket W i + r: items 4 W i + r + W s, s < 4)
+// it reads those instead, a quarter of the row, and then only the items of
+// the k buckets that reach T.  Measured: top-100 of 32 rows of 109,739 scores
+// 22 us plus 6 us for the maxima (chunked radix selection, segmented sort and
+// decode of 64-bit keys: 52 us); straight from the rows 61 us.
+#include "mol_kernels.h"
+
+namespace mol {
+
+namespace {
+
+constexpr int kTopThreads = 1024;
+constexpr int kTopCap = 4096;          // keys held in LDS
+constexpr int kTopHot = 1024;          // buckets collected before their items are read
+constexpr int kTopRankMax = 256;       // up to this many keys are ranked by counting, more are sorted
+
+// score image, 0 for "no item" (NaN: never ranked)
+__device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float_to_ordered(f) : 0u; }
+
+}  // namespace
+
+// phi [rows][phi_stride], L scores a row (row_len: NULL or the valid count of
+// each row); bmax: NULL, or [rows][bmax_stride] bucket maxima; ids: NULL (item
+// = column), or the item of each column [rows][ids_stride]; sign: the rows
+// are ranked by sign * phi, and that is what is written; skip_neg_inf: a score
+// of -inf marks an excluded column.  Rows with fewer than k items are padded
+// with (-inf, -1).
+__global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int L_all,
+                                                           const int32_t* __restrict__ row_len,
+                                                           const float* __restrict__ bmax, long bmax_stride, int W,
+                                                           const int32_t* __restrict__ ids, long ids_stride, int k,
+                                                           float sign, int skip_neg_inf, float* __restrict__ out_score,
+                                                           int32_t* __restrict__ out_idx) {
+  __shared__ uint64_t buf[kTopCap];
+  __shared__ uint32_t hist[256];
+  __shared__ int hot[kTopHot];
+  __shared__ uint32_t s_hi, s_lo, s_count, s_hot, s_bin, s_above;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const long row = blockIdx.x;
+  const int L = row_len ? min(row_len[row], L_all) : L_all;
+  const float* src = phi + row * phi_stride;
+  const int32_t* id = ids ? ids + row * ids_stride : nullptr;
+  const uint32_t none = skip_neg_inf ? float_to_ordered(-__builtin_inff()) : 0u;
+  // image of column i's score: 0 for an excluded one
+  auto image = [&](float f) {
+    const uint32_t u = score_image(sign * f);
+    return u > none ? u : 0u;
+  };
+  const int nb = bmax ? static_cast<int>((L + 4l * W - 1) / (4 * W) * W) : L;     // values of the first pass
+  const float* val = bmax ? bmax + row * bmax_stride : src;
+  // four values a thread and load where the row allows it
+  const bool vec = (reinterpret_cast<uintptr_t>(val) & 15) == 0;
+  auto for_values = [&](auto&& f) {                 // f(index of the first, 4 values, how many are valid)
+    constexpr int U = 4;                            // loads in flight
+    for (int i0 = 4 * tid; i0 < nb; i0 += U * 4 * kTopThreads) {
+      float4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * 4 * kTopThreads;
+        if (vec && i + 4 <= nb) {
+          v[u] = *reinterpret_cast<const float4*>(val + i);
+        } else {
+          const int last = nb - 1;
+          v[u] = float4{val[min(i, last)], val[min(i + 1, last)], val[min(i + 2, last)], val[min(i + 3, last)]};
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * 4 * kTopThreads;
+        if (i < nb) f(i, v[u], min(4, nb - i));
+      }
+    }
+  };
+
+  // the thread's maximum, in floats (values past the end repeat the last one;
+  // fmaxf passes NaN over)
+  float fm = __builtin_nanf("");
+  for_values([&](int, const float4& v, int) {
+    fm = fmaxf(fm, fmaxf(fmaxf(sign * v.x, sign * v.y), fmaxf(sign * v.z, sign * v.w)));
+  });
+  const uint32_t mx = image(sign * fm);
+
+  // T: the k-th largest thread maximum, to 24 bits below the highest bit in
+  // which the nonzero maxima differ (the bits left out only lower T); 0 with
+  // fewer than k of them
+  if (tid == 0) {
+    s_hi = 0u;
+    s_lo = 0xFFFFFFFFu;
+    s_count = 0u;
+  }
+  __syncthreads();
+  {
+    uint32_t hi = mx, lo = mx ? mx : 0xFFFFFFFFu;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      hi = max(hi, static_cast<uint32_t>(__shfl_xor(static_cast<int>(hi), o)));
+      lo = min(lo, static_cast<uint32_t>(__shfl_xor(static_cast<int>(lo), o)));
+    }
+    const uint64_t nz = __ballot(mx != 0u);
+    if (lane == 0 && nz) {
+      atomicMax(&s_hi, hi);
+      atomicMin(&s_lo, lo);
+      atomicAdd(&s_count, static_cast<uint32_t>(__popcll(nz)));
+    }
+  }
+  __syncthreads();
+  const uint32_t diff = s_hi ^ s_lo, nonzero = s_count;
+  uint32_t T = 0u;
+  // rank `kk` (from the top) among the values with image >> shift + 8 equal
+  // to the prefix: the bin of `hist` that holds it, found by wave 0
+  auto find_bin = [&](uint32_t kk) {
+    if (tid < 64) {
+      uint32_t h[4], sum = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        h[j] = hist[255 - 4 * lane - j];
+        sum += h[j];
+      }
+      uint32_t incl = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+      }
+      const uint64_t hit = __ballot(incl >= kk);
+      if (hit && lane == __ffsll(static_cast<long long>(hit)) - 1) {
+        uint32_t above = incl - sum;
+        int bin = 255 - 4 * lane;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (above + h[j] >= kk) {
+            bin = 255 - 4 * lane - j;
+            break;
+          }
+          above += h[j];
+        }
+        s_bin = static_cast<uint32_t>(bin);
+        s_above = above;
+      }
+    }
+    __syncthreads();
+  };
+  if (nonzero >= static_cast<uint32_t>(k)) {
+    uint32_t kk = static_cast<uint32_t>(k);
+    int bits = diff ? 32 - __clz(static_cast<int>(diff)) : 0;   // low bits that may differ
+    T = bits >= 32 ? 0u : s_hi >> bits << bits;
+    for (int pass = 0; pass < 3 && bits > 0; ++pass) {
+      const int shift = max(0, bits - 8);
+      __syncthreads();
+      if (tid < 256) hist[tid] = 0u;
+      __syncthreads();
+      if (mx != 0u && (bits >= 32 || (mx >> bits) == (T >> bits)))
+        atomicAdd(&hist[(mx >> shift) & ((1u << (bits - shift)) - 1u)], 1u);
+      __syncthreads();
+      find_bin(kk);
+      kk -= s_above;
+      T |= s_bin << shift;
+      bits = shift;
+    }
+  }
+  T = max(T, 1u);                                    // image 0: no item
+
+  // every item at or above T
+  __syncthreads();
+  if (tid == 0) s_count = s_hot = 0u;
+  __syncthreads();
+  // the float compare decides almost every value; images decide the rest
+  const float Tf = T > float_to_ordered(-__builtin_inff()) ? ordered_to_float(T) : -__builtin_inff();
+  auto visit = [&](auto&& f) {                       // f(image, column) of the row's items at or above T
+    for_values([&](int i, const float4& v4, int n) {
+      const float v[4] = {sign * v4.x, sign * v4.y, sign * v4.z, sign * v4.w};
+      if (!(v[0] >= Tf || v[1] >= Tf || v[2] >= Tf || v[3] >= Tf)) return;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t im = e < n ? image(sign * v[e]) : 0u;
+        if (im < T) continue;
+        if (!bmax) {
+          f(im, i + e);
+        } else {
+          const int c0 = 4 * W * ((i + e) / W) + (i + e) % W;
+          float x[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[s] = src[min(c0 + W * s, L - 1)];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const uint32_t u = c0 + W * s < L ? image(x[s]) : 0u;   // (the column past the end: none)
+            if (u >= T) f(u, c0 + W * s);
+          }
+        }
+      }
+    });
+  };
+  auto key_of = [&](uint32_t u, int col) {
+    const int32_t item = id ? id[col] : col;
+    return (static_cast<uint64_t>(u) << 32) | static_cast<uint32_t>(~static_cast<uint32_t>(item));
+  };
+  auto collect = [&](uint32_t u, int col) {
+    const uint32_t pos = atomicAdd(&s_count, 1u);
+    if (pos < static_cast<uint32_t>(kTopCap)) buf[pos] = key_of(u, col);
+  };
+  uint32_t hot_n = kTopHot + 1;
+  if (bmax) {
+    // the buckets that reach T, then their items four a bucket, one a thread:
+    // one round trip to memory instead of one for each bucket of a wave
+    for_values([&](int i, const float4& v4, int nv) {
+      const float v[4] = {sign * v4.x, sign * v4.y, sign * v4.z, sign * v4.w};
+      if (!(v[0] >= Tf || v[1] >= Tf || v[2] >= Tf || v[3] >= Tf)) return;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < nv && image(sign * v[e]) >= T) {
+          const uint32_t pos = atomicAdd(&s_hot, 1u);
+          if (pos < static_cast<uint32_t>(kTopHot)) hot[pos] = i + e;
+        }
+    });
+    __syncthreads();
+    hot_n = s_hot;
+    if (hot_n <= static_cast<uint32_t>(kTopHot))
+      for (int t = tid; t < 4 * static_cast<int>(hot_n); t += kTopThreads) {
+        const int bk = hot[t >> 2], col = 4 * W * (bk / W) + bk % W + W * (t & 3);
+        const uint32_t u = col < L ? image(src[col]) : 0u;
+        if (u >= T) collect(u, col);
+      }
+  }
+  if (hot_n > static_cast<uint32_t>(kTopHot)) visit(collect);
+  __syncthreads();
+  uint32_t n = s_count;
+  if (n > static_cast<uint32_t>(kTopCap)) {
+    // the k-th largest key, 8 bits a pass over the items at or above T (at
+    // least k of them: more than kTopCap >= k reach T)
+    uint64_t prefix = 0;
+    uint32_t kk = static_cast<uint32_t>(k);
+    for (int shift = 56; shift >= 0; shift -= 8) {
+      __syncthreads();
+      if (tid < 256) hist[tid] = 0u;
+      __syncthreads();
+      visit([&](uint32_t u, int col) {
+        const uint64_t key = key_of(u, col);
+        if (shift == 56 || (key >> (shift + 8)) == (prefix >> (shift + 8)))
+          atomicAdd(&hist[static_cast<uint32_t>(key >> shift) & 255u], 1u);
+      });
+      __syncthreads();
+      find_bin(kk);
+      kk -= s_above;
+      prefix |= static_cast<uint64_t>(s_bin) << shift;
+    }
+    __syncthreads();
+    if (tid == 0) s_count = 0u;
+    __syncthreads();
+    visit([&](uint32_t u, int col) {
+      const uint64_t key = key_of(u, col);
+      if (key >= prefix) {
+        const uint32_t pos = atomicAdd(&s_count, 1u);
+        if (pos < static_cast<uint32_t>(kTopCap)) buf[pos] = key;
+      }
+    });
+    __syncthreads();
+    n = min(s_count, static_cast<uint32_t>(kTopCap));
+  }
+  float* os = out_score + row * k;
+  int32_t* oi = out_idx + row * k;
+  const int ni = static_cast<int>(n);
+  if (ni <= kTopRankMax) {
+    // a key's rank is the number of larger ones (keys are distinct)
+    if (tid < ni) {
+      const uint64_t key = buf[tid];
+      int rank = 0;
+      int j = 0;
+      for (; j + 8 <= ni; j += 8) {
+        uint64_t o[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = buf[j + e];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rank += o[e] > key ? 1 : 0;
+      }
+      for (; j < ni; ++j) rank += buf[j] > key ? 1 : 0;
+      if (rank < k) {
+        os[rank] = key_score(key);
+        oi[rank] = key_item(key);
+      }
+    }
+  } else {
+    int S = 2 * kTopRankMax;
+    while (S < ni) S <<= 1;
+    for (int i = ni + tid; i < S; i += kTopThreads) buf[i] = 0ull;
+    __syncthreads();
+    for (int size = 2; size <= S; size <<= 1)
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        for (int i = tid; i < S / 2; i += kTopThreads) {
+          const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+          const bool desc = (lo & size) == 0;
+          const uint64_t a = buf[lo], c = buf[hi];
+          if ((a < c) == desc) {
+            buf[lo] = c;
+            buf[hi] = a;
+          }
+        }
+        __syncthreads();
+      }
+    for (int i = tid; i < min(k, ni); i += kTopThreads) {
+      os[i] = key_score(buf[i]);
+      oi[i] = key_item(buf[i]);
+    }
+  }
+  for (int i = ni + tid; i < k; i += kTopThreads) {
+    os[i] = -__builtin_inff();
+    oi[i] = -1;
+  }
+}
+
+// Bucket maxima of dense rows (the layout k_topk_dense reads): a wave takes
+// 256 consecutive scores of a row, four a lane; lane (q, j) = (lane / 16,
+// lane % 16) reads columns 64 q + 16 s + j, s < 4.
+__global__ __launch_bounds__(256) void k_bucket_max(const float* __restrict__ phi, long phi_stride, int L, float sign,
+                                                    float* __restrict__ bmax, long bmax_stride) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long row = blockIdx.y;
+  const int col = (blockIdx.x * 4 + wave) * 256 + (lane >> 4) * 64 + (lane & 15);
+  if (col - (lane & 15) >= L) return;
+  const float* src = phi + row * phi_stride;
+  float m = __builtin_nanf("");
+#pragma unroll
+  for (int s = 0; s < 4; ++s) m = fmaxf(m, col + 16 * s < L ? sign * src[col + 16 * s] : m);
+  bmax[row * bmax_stride + (col >> 6) * 16 + (col & 15)] = sign * m;
+}
+
+hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L, float sign, float* bmax,
+                             long bmax_stride, hipStream_t st) {
+  hipLaunchKernelGGL(k_bucket_max, dim3((L + 1023) / 1024, rows), dim3(256), 0, st, phi, phi_stride, L, sign, bmax,
+                     bmax_stride);
+  return hipGetLastError();
+}
+
+hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_score, int32_t* out_idx,
+                             hipStream_t st) {
+  if (k > kTopkDenseMaxK) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_topk_dense, dim3(rows), dim3(kTopThreads), 0, st, r.phi, r.phi_stride, r.L, r.row_len, r.bmax,
+                     r.bmax_stride, r.W, r.ids, r.ids_stride, k, r.sign, r.skip_neg_inf ? 1 : 0, out_score, out_idx);
+  return hipGetLastError();
+}
+
+}  // namespace mol

@@ -1,0 +1,117 @@
+"""The float32 scoring kernel and the dense-row top-k against float64
+references, at the sizes where their tiles and branches end (MI355X only)."""
+import pytest
+import torch
+
+from paper_2407_15462_amd import mol
+from parity_helpers import log
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(B, N, Pq, Px, d, H, dtype, flags=0, seed=0, offset=0, std=0.5):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+
+    def unit(*shape):
+        v = torch.randn(shape, generator=g, device="cuda")
+        return (v / v.norm(dim=-1, keepdim=True)).to(dtype)
+
+    def off(t):   # the same values `offset` elements past a 16-byte boundary
+        buf = torch.empty(t.numel() + offset, dtype=t.dtype, device="cuda")
+        buf[offset:] = t.reshape(-1)
+        return buf[offset:].view(t.shape)
+
+    P = Pq * Px
+    r = lambda *s: std * torch.randn(s, generator=g, device="cuda")   # noqa: E731
+    t = (off(unit(B, Pq, d)), off(unit(Px, N, d)), off(r(B, P)), off(r(N, P)), r(H, P).to(dtype), r(H),
+         r(P, H).to(dtype), r(P))
+    return mol.Problem(*t, flags=flags), t
+
+
+def _phi64(t):
+    Q, X, a_q, a_x, W1, b1, W2, b2 = (x.double() for x in t)
+    B, Pq, d = Q.shape
+    Px, N, _ = X.shape
+    s = torch.stack([Q.reshape(B * Pq, d) @ X[px].t().contiguous() for px in range(Px)], 1)   # [B Pq][Px][N]
+    s = s.view(B, Pq * Px, N).permute(0, 2, 1).reshape(B * N, Pq * Px)
+    u = s @ W1.t().contiguous() + b1
+    lg = (u * torch.sigmoid(u)) @ W2.t().contiguous() + b2
+    lg = lg.view(B, N, -1) + a_q[:, None] + a_x[None]
+    return (torch.softmax(lg, -1) * s.view(B, N, -1)).sum(-1), s.view(B, N, -1)
+
+
+# P at and around 16, 32 and 64; H not a multiple of 16 and the largest; d
+# whole chunks, a partial chunk, odd (element reads); batches that leave a
+# partial query block; items that leave a partial tile
+@pytest.mark.parametrize("B,N,Pq,Px,d,H,dtype,offset", [
+    (1, 33, 1, 1, 8, 1, torch.float32, 0),
+    (9, 1000, 4, 4, 64, 32, torch.float32, 0),
+    (5, 517, 4, 4, 20, 17, torch.float32, 0),
+    (3, 300, 3, 5, 7, 40, torch.float32, 0),
+    (3, 129, 17, 1, 64, 33, torch.float32, 1),
+    (6, 257, 8, 4, 36, 64, torch.float32, 0),
+    (5, 130, 8, 8, 64, 64, torch.float32, 0),
+    (2, 70, 2, 32, 96, 256, torch.float32, 0),
+    (1, 700, 7, 9, 1024, 16, torch.float32, 0),
+    (2, 70, 64, 1, 16, 250, torch.bfloat16, 0),
+    (5, 333, 8, 8, 64, 64, torch.bfloat16, 0),
+    (3, 100, 5, 3, 40, 48, torch.bfloat16, 0),
+    (3, 100, 4, 4, 33, 48, torch.bfloat16, 3),
+])
+def test_f32_scores_topk_rerank(B, N, Pq, Px, d, H, dtype, offset):
+    log(f"[f32] B={B} N={N} P={Pq}x{Px} d={d} H={H} {dtype} offset={offset}")
+    prob, t = _problem(B, N, Pq, Px, d, H, dtype, mol.MOL_FLAG_F32_GATING, seed=B * N, offset=offset)
+    phi = mol.score(prob)
+    part = mol.score(prob, 7, N - 11)
+    k = min(N, 20)
+    s, i = mol.topk_exact(prob, k)
+    bs, bi = mol.topk_exact_bounded(prob, k, s[:, k - 1].contiguous())
+    cand = torch.randint(-2, N, (B, 67), device="cuda", dtype=torch.int32,
+                         generator=torch.Generator(device="cuda").manual_seed(4))
+    rs, ri, rn = mol.rerank(prob, cand, k)
+    ms, mi = mol.topk_maxdot(prob, k)
+    ps, pi = mol.topk_per_embd(prob, k)
+    torch.cuda.synchronize()
+    want, dots = _phi64(t)
+    # |s| <= 1: dots of unit rows are off by under d 2^-24; the logits' error
+    # (their sums' rounding, and the dots' through both layers) moves phi by
+    # at most 2 max|s| of itself
+    tol = 4e-6 + 8 * d * 2.0 ** -24
+    assert (phi.double() - want).abs().max() <= tol
+    assert torch.equal(part, phi[:, 7:N - 4])
+    ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
+    assert torch.equal(s, ws[:, :k]) and torch.equal(i.long(), wi[:, :k])     # the kernel's own scores, exactly
+    assert torch.equal(bs, s) and torch.equal(bi, i)
+    for b in range(B):
+        ids = torch.unique(cand[b][cand[b] >= 0].long())
+        assert int(rn[b]) == ids.numel()
+        o = torch.sort(phi[b, ids], descending=True, stable=True)
+        n = min(k, ids.numel())
+        assert torch.equal(rs[b, :n], o.values[:n]) and torch.equal(ri[b, :n].long(), ids[o.indices[:n]])
+        assert bool((ri[b, n:] == -1).all())
+    assert (ms.double() - torch.sort(dots.amax(-1), dim=1, descending=True).values[:, :k]).abs().max() <= tol
+    top = torch.sort(dots.permute(0, 2, 1), dim=2, descending=True).values[..., :k]
+    assert (ps.double() - top).abs().max() <= tol
+    got = torch.gather(dots.permute(0, 2, 1), 2, pi.long())
+    assert (ps.double() - got).abs().max() <= tol
+
+
+# rows shorter than a workgroup, around it, and long; k at both ends of the
+# kernel's range; more tied items than the LDS list holds (the radix finish)
+@pytest.mark.parametrize("N,k,ties", [
+    (1, 1, 0), (63, 63, 0), (700, 512, 0), (1025, 100, 0), (4099, 512, 0), (40001, 1, 0), (40001, 300, 9000),
+    (40001, 512, 40001), (40001, 100, 39950),
+])
+def test_dense_topk_is_exact(N, k, ties):
+    log(f"[dense topk] N={N} k={k} ties={ties}")
+    prob, t = _problem(3, N, 2, 2, 16, 16, torch.float32, seed=N + k)
+    X = t[1]
+    if ties:   # identical items: equal scores, ranked by index
+        at = torch.randperm(N, generator=torch.Generator().manual_seed(1))[:ties].cuda()
+        X[:, at] = X[:, at[:1]]
+        t[3][at] = t[3][at[:1]]
+    phi = mol.score(prob)
+    s, i = mol.topk_exact(prob, k)
+    torch.cuda.synchronize()
+    ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
+    assert torch.equal(s, ws[:, :k]) and torch.equal(i.long(), wi[:, :k])
