@@ -214,31 +214,43 @@ hipError_t pairwise_score(const DevProb& pr, float* sbuf, long sRow, int mode, c
 // one top-k kernel per row.  It replaces per-tile key sorts and per-range
 // lists wherever the buffer stays under kDenseMax bytes.
 constexpr size_t kDenseMax = size_t(512) << 20;
-// rows from this length on are reduced to bucket maxima by a launch of their
-// own (about 5 us) before the one-workgroup-per-row top-k reads them
+// Rows from this length on are ranked through bucket maxima (if there are at
+// least 2 k of them: fewer leave a threshold that admits too much), written by
+// the fused scan or formed by a launch of their own (about 5 us); the top-k
+// kernel reads other rows directly.
 constexpr int kBucketMinN = 1 << 14;
 
 struct DensePlan {
   long ld = 0;                     // floats per phi row (a multiple of 4)
   long sRow = 0;                   // dots buffer row (0: no buffer)
   int T = 0;                       // items per dots tile
-  size_t offPhi = 0, offBmax = 0, offS = 0, bytes = 0;
+  bool fused = false;              // scored by the fused kernels
+  FusedDenseGrid g;
+  size_t offPhi = 0, offBmax = 0, offS = 0, offRedo = 0, bytes = 0;
 };
 
 bool dense_fits(const DevProb& pr, int k) {
   return k <= kTopkDenseMaxK && 4ul * pr.B * ((pr.N + 3l) & ~3l) <= kDenseMax;
 }
 
-DensePlan plan_dense(const DevProb& pr, bool gating) {
+enum DenseBy { kByFused, kByPairs, kByMaxDot };   // what scores the rows
+
+DensePlan plan_dense(const DevProb& pr, int k, DenseBy by) {
   DensePlan f;
   f.ld = (pr.N + 3l) & ~3l;
   f.T = pr.N;
   size_t off = align_up(4ul * pr.B * f.ld);
-  if (pr.N >= kBucketMinN) {
-    f.offBmax = off;
-    off = align_up(off + 4ul * pr.B * bucket_row(pr.N, 16));
+  if (by == kByFused) {
+    f.fused = true;
+    f.g = fused_dense_grid(pr, pr.N);
+    f.offRedo = off;
+    off = align_up(off + 4ul * fused_redo_flags(f.g.R, f.g.G));
   }
-  if (gating && dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
+  if (pr.N >= kBucketMinN && pr.N >= 128l * k) {
+    f.offBmax = off;
+    off = align_up(off + 4ul * pr.B * bucket_row(pr.N, f.g.SL));
+  }
+  if (by == kByPairs && dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
     // dots tiles of at most 512 MB, whole 128-item GEMM tiles
     const long T = std::max(1024l, std::min<long>(pr.N, (512l << 20) / (4l * pr.P * pr.B) / 128 * 128));
     const long sRow = dots_buffer_row(static_cast<int>(T));
@@ -487,14 +499,20 @@ size_t exact_list_ws_bytes(const DevProb& pr, int k) {
   return fused_supported(pr, k) ? plan_fused_exact(pr, k).bytes : plan_pairwise(pr, k).bytes;
 }
 
-size_t exact_ws_bytes(const DevProb& pr, int k) {
-  if (!fused_supported(pr, k) && dense_fits(pr, k)) return plan_dense(pr, true).bytes;
-  return exact_list_ws_bytes(pr, k);
+// the dense form where its buffer fits; the bounded scan of the fused shapes
+// keeps its lists, whose running threshold prunes it
+bool use_dense(const DevProb& pr, int k, bool bounded) {
+  return dense_fits(pr, k) && !(bounded && fused_supported(pr, k));
+}
+DenseBy dense_by(const DevProb& pr, int k) { return fused_supported(pr, k) ? kByFused : kByPairs; }
+
+size_t exact_ws_bytes(const DevProb& pr, int k, bool bounded) {
+  return use_dense(pr, k, bounded) ? plan_dense(pr, k, dense_by(pr, k)).bytes : exact_list_ws_bytes(pr, k);
 }
 
 size_t maxdot_ws_bytes(const DevProb& pr, int k) {
   if (fused_maxdot_supported(pr, k)) return plan_fused_exact(pr, k, true).bytes;
-  if (!dots_maxkeys_supported(pr) && dense_fits(pr, k)) return plan_dense(pr, false).bytes;
+  if (!dots_maxkeys_supported(pr) && dense_fits(pr, k)) return plan_dense(pr, k, kByMaxDot).bytes;
   return plan_stream(pr.B, pr.N, k).bytes;
 }
 
@@ -516,7 +534,7 @@ TwoPassPlan plan_two_pass(const DevProb& pr, int k) {
   t.offBound = off; off = align_up(off + 4ul * pr.B);
   t.offWork = off;
   const size_t work = std::max({per_embd_ws_bytes(pr, k), plan_rerank(pr, pr.P * k, k).bytes,
-                                exact_ws_bytes(pr, k)});
+                                exact_ws_bytes(pr, k, true)});
   t.bytes = off + align_up(work);
   return t;
 }
@@ -553,12 +571,17 @@ int check_two_pass_k(const mol_problem* prob, int32_t k) {
 // Dense scores of the whole corpus, then the top-k.
 int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out_score, int32_t* out_idx, char* w,
               int timed_op, hipStream_t st) {
-  const DensePlan f = plan_dense(pr, mode != kGenMaxDot);
+  const DensePlan f = plan_dense(pr, k, mode == kGenMaxDot ? kByMaxDot : dense_by(pr, k));
   float* phi = reinterpret_cast<float*>(w + f.offPhi);
   float* bmax = f.offBmax ? reinterpret_cast<float*>(w + f.offBmax) : nullptr;
-  const long bstride = bucket_row(pr.N, 16);
+  const long bstride = bucket_row(pr.N, f.g.SL);
   float* sbuf = f.sRow ? reinterpret_cast<float*>(w + f.offS) : nullptr;
-  for (long n0 = 0; n0 < pr.N; n0 += f.T) {
+  if (f.fused)
+    MOL_TIMED_LAUNCH(timed_op, st,
+                     launch_fused_dense(pr, f.g, 0, pr.N, phi, f.ld, bmax, bstride,
+                                        reinterpret_cast<int*>(w + f.offRedo), st),
+                     "fused MoL scores");
+  for (long n0 = 0; n0 < pr.N && !f.fused; n0 += f.T) {
     const int nt = static_cast<int>(std::min<long>(f.T, pr.N - n0));
     MOL_TIMED_LAUNCH(timed_op, st,
                      pairwise_score(pr, sbuf, f.sRow, mode, bound, static_cast<int>(n0), nt, phi + n0, f.ld, nullptr,
@@ -572,7 +595,8 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
   r.skip_neg_inf = mode == kGenBounded;
   r.bmax = bmax;
   r.bmax_stride = bstride;
-  if (bmax)
+  r.SL = f.g.SL;
+  if (bmax && !f.fused)
     MOL_TRY_HIP(launch_bucket_max(phi, f.ld, pr.B, pr.N, 1.f, bmax, bstride, st), "bucket maxima");
   MOL_TRY_HIP(launch_topk_dense(r, pr.B, k, out_score, out_idx, st), "dense top-k");
   return MOL_OK;
@@ -584,7 +608,7 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
 int run_exact(const DevProb& pr, int k, const float* bound, float* out_score, int32_t* out_idx,
               char* w, int timed_op, hipStream_t st, bool lists = false) {
   int rc;
-  if (!lists && !fused_supported(pr, k) && dense_fits(pr, k))
+  if (!lists && use_dense(pr, k, bound != nullptr))
     return run_dense(pr, k, bound ? kGenBounded : kGenPhi, bound, out_score, out_idx, w, timed_op, st);
   if (fused_supported(pr, k)) {
     const FusedExactPlan f = plan_fused_exact(pr, k);
@@ -830,7 +854,7 @@ int mol_workspace_size(const mol_problem* prob, int op, int32_t k, int32_t kprim
     case MOL_OP_TOPK_EXACT:
       if ((rc = check_problem(prob, true))) return rc;
       if ((rc = check_k(k, prob->N, "k"))) return rc;
-      *bytes = exact_ws_bytes(dev_prob(prob), k);
+      *bytes = exact_ws_bytes(dev_prob(prob), k, false);
       return MOL_OK;
     case MOL_OP_TOPK_PER_EMBD:
       if ((rc = check_problem(prob, false))) return rc;
@@ -851,7 +875,7 @@ int mol_workspace_size(const mol_problem* prob, int op, int32_t k, int32_t kprim
     case MOL_OP_TOPK_BOUNDED:
       if ((rc = check_problem(prob, true))) return rc;
       if ((rc = check_k(k, prob->N, "k"))) return rc;
-      *bytes = exact_ws_bytes(dev_prob(prob), k);
+      *bytes = exact_ws_bytes(dev_prob(prob), k, true);
       return MOL_OK;
     case MOL_OP_TOPK_TWO_PASS:
       if ((rc = check_problem(prob, true))) return rc;
@@ -874,7 +898,8 @@ int mol_score(const mol_problem* prob, int32_t n_begin, int32_t n_count, float* 
   const DevProb pr = dev_prob(prob);
   if (fused_supported(pr, 1)) {
     MOL_TIMED_LAUNCH(MOL_OP_SCORE, st,
-                     launch_fused_dense(pr, n_begin, n_count, phi, st),
+                     launch_fused_dense(pr, fused_dense_grid(pr, n_count), n_begin, n_count, phi, n_count, nullptr, 0,
+                                        nullptr, st),
                      "mol_score (fused)");
     return MOL_OK;
   }
@@ -892,7 +917,7 @@ int mol_topk_exact(const mol_problem* prob, int32_t k, float* out_score, int32_t
   if ((rc = check_k(k, prob->N, "k"))) return rc;
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  if ((rc = check_ws(ws, ws_bytes, exact_ws_bytes(pr, k)))) return rc;
+  if ((rc = check_ws(ws, ws_bytes, exact_ws_bytes(pr, k, false)))) return rc;
   return run_exact(pr, k, nullptr, out_score, out_idx, static_cast<char*>(ws), MOL_OP_TOPK_EXACT,
                    static_cast<hipStream_t>(stream));
 }
@@ -921,7 +946,7 @@ int mol_topk_exact_bounded(const mol_problem* prob, int32_t k, const float* boun
   if (!bound) return fail(MOL_EINVAL, "bound is NULL");
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  if ((rc = check_ws(ws, ws_bytes, exact_ws_bytes(pr, k)))) return rc;
+  if ((rc = check_ws(ws, ws_bytes, exact_ws_bytes(pr, k, true)))) return rc;
   return run_exact(pr, k, bound, out_score, out_idx, static_cast<char*>(ws), MOL_OP_TOPK_BOUNDED,
                    static_cast<hipStream_t>(stream));
 }

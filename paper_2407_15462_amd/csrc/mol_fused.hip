@@ -12,7 +12,12 @@
 // Epilogues (EPI):
 //  - kEpiTopk: a running per-query top-k of phi (Definition 1) kept in LDS
 //    with threshold rejection;
-//  - kEpiDense: a dense phi store;
+//  - kEpiDense: a dense phi store (mol_score), and with bucket maxima the
+//    first half of the exact top-k while the rows fit its buffer: the lists
+//    of kEpiTopk cost 12 % (16,384-item ranges) to 60 % (192-item ranges) of
+//    the scan on top of it (32 x 674,044 of 8 x 8, d = 32: 1.04 ms with lists,
+//    0.73 ms dense, selection included; 32 x 24,186 of 8 x 4, d = 128: 0.114
+//    and 0.057 ms; 256 x 262,147 with the two-term chain: 3.86 and 3.51 ms);
 //  - kEpiBounded: the same top-k over the items that can reach a per-query
 //    bound: phi is a convex combination of the s_p, so phi <= m = max_p s_p,
 //    and an item whose m (plus a rounding margin) stays below the bound, or
@@ -22,10 +27,10 @@
 //  - kEpiMaxDot: a running top-k of m itself, without the gating MLP
 //    (Section 3's max approximation of MoL, a subsection cut from the
 //    published text);
-//  - kEpiTopkPipe: kEpiTopk as a software-pipelined loop (each step's
-//    softmax tail issued with the next step's GEMM1); a step whose softmax
-//    sum leaves its safe range flags its workgroup's range, which a second
-//    launch of kEpiTopk rescores.
+//  - kEpiTopkPipe, kEpiDensePipe: kEpiTopk and kEpiDense as a
+//    software-pipelined loop (each step's softmax tail issued with the next
+//    step's GEMM1); a step whose softmax sum leaves its safe range flags its
+//    workgroup's range, which a second launch of the plain form rescores.
 //
 // Workgroup: 8 waves (2 per SIMD) = 16 queries sharing an LDS-staged
 // stream of 32-item tiles (a three-deep ring) loaded with direct
@@ -40,28 +45,29 @@ using namespace tile;
 
 namespace {
 
-enum FusedEpi { kEpiTopk = 0, kEpiDense = 1, kEpiBounded = 2, kEpiMaxDot = 3, kEpiTopkPipe = 4 };
+enum FusedEpi { kEpiTopk = 0, kEpiDense = 1, kEpiBounded = 2, kEpiMaxDot = 3, kEpiTopkPipe = 4, kEpiDensePipe = 5 };
 
 constexpr int kWaves = 8;
-constexpr int kQueriesPerWG = 2 * kWaves;   // the gating forms
 // queries per wave: two in the gating forms; four in the max-dot form, whose
 // step is GEMM1 alone: each LDS read of the X tile then feeds two GEMM1s (the
 // 64 KB of top-k lists leave one workgroup per CU; at exact_1m 9.5 ms against
 // 9.8 ms for two queries per wave and two workgroups per CU)
 template <bool AX>
 constexpr int queries_per_wave() { return AX ? 2 : 4; }
-// items per LDS stage: two 16-item steps with the gating MLP; one step in
-// the max-dot form (no a_x stream)
-template <bool AX>
-constexpr int tile_items() { return AX ? 32 : 16; }
+// items per LDS stage: two 16-item steps with the gating MLP, one step per
+// slice with four slices; one step in the max-dot form (no a_x stream)
+template <bool AX, int SL>
+constexpr int tile_items() { return !AX ? 16 : SL == 4 ? 64 : 32; }
 constexpr int kRing = 3;         // item stages in flight
 constexpr int kTopkRegion = WaveTopk::kList + WaveTopk::kStage;
 
-// PX, D, H: shape; AX: the gating inputs (a_x stream, a_q + b2) are needed
-template <int PX, int D, int H, bool AX>
+// PX, D, H: shape; AX: the gating inputs (a_x stream, a_q + b2) are needed;
+// SL: slices; TOPK: the running lists are kept
+template <int PX, int D, int H, bool AX, int SL, bool TOPK>
 struct FusedShape {
   static constexpr int P = 8 * PX;
-  static constexpr int TILE = tile_items<AX>();
+  static constexpr int TILE = tile_items<AX, SL>();
+  static constexpr int SPT = TILE / 16 / SL;   // steps of a tile per wave
   static constexpr int RUN = 2 * PX;     // s values per lane per query
   static constexpr int KD = D / 32;      // K blocks of GEMM1
   static constexpr int PT = P / 16;      // output tiles of GEMM3
@@ -71,10 +77,10 @@ struct FusedShape {
   static constexpr int ASTAGE = AX ? TILE * P * 4 : 0;   // bytes of one a_x stage
   static constexpr int LDS_X = kRing * XSTAGE;
   static constexpr int LDS_AX = kRing * ASTAGE;
-  static constexpr int LDS_CB = AX ? kQueriesPerWG * P * 4 : 0;   // [query][p] log2(e) (a_q + b2), f32
   static constexpr int QPW = queries_per_wave<AX>();   // queries per wave
-  static constexpr int QWG = QPW * kWaves;             // queries per workgroup
-  static constexpr int LDS_TOPK = QWG * kTopkRegion * 8;
+  static constexpr int QWG = QPW * kWaves / SL;        // queries per workgroup
+  static constexpr int LDS_CB = AX ? QWG * P * 4 : 0;  // [query][p] log2(e) (a_q + b2), f32
+  static constexpr int LDS_TOPK = TOPK ? QWG * kTopkRegion * 8 : 0;
   static constexpr int LDS_TOTAL = LDS_X + LDS_AX + LDS_CB + LDS_TOPK;
   // 16-byte global->LDS copies per stage, in 1 KB blocks of one wave each
   static constexpr int XBLOCKS = XSTAGE / 1024;
@@ -82,6 +88,7 @@ struct FusedShape {
   static_assert(XBLOCKS % kWaves == 0, "X stage must split evenly over the waves");
   // fewest copies any wave issues per stage (a_x blocks may not split evenly)
   static constexpr int LOADS = XBLOCKS / kWaves + ABLOCKS / kWaves;
+  static_assert(LDS_TOTAL <= 160 * 1024, "LDS budget");
 };
 
 // WG -> (item range, query group); WGs on one XCD (WG id mod 8) share item
@@ -99,16 +106,33 @@ __device__ __forceinline__ void wg_coords(int g, int R, int G, int& r, int& qg) 
 
 }  // namespace
 
-template <int PX, int D, int H, int EPI, bool X2>
+// SL: slices (dense forms).  1: the 8 waves take 2 queries each and every
+// item.  2 or 4: the waves form SL slices of 8 / SL waves, 16 / SL queries a
+// workgroup, each slice on its own 16-item steps of a tile (for batches whose
+// waves would otherwise multiply empty query slots: one query against 2^20
+// items of 8 x 8, d = 64, 0.67 ms -> 0.257 ms, 5.6 TB/s of its scan).
+// A wave without a query only stages tiles: it leaves its SIMD to the others.
+// bmax (dense forms): NULL, or [B][bmax_stride] maxima of phi over buckets of
+// 64 items: bucket SL i + s holds the 16-item runs 4 SL i + s + SL j, j < 4
+// (range_len is a multiple of 64 SL then).
+// maximum over the 16 lanes of a row, in all of them
+__device__ __forceinline__ float row16_max(float v) {
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 16));
+  return v;
+}
+
+template <int PX, int D, int H, int EPI, bool X2, int SL>
 __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
     DevProb pr, int k, int R, int range_len, int G, int n_begin, int n_end,
     const float* __restrict__ bound, uint64_t* __restrict__ partial, float* __restrict__ phi_out,
-    long phi_stride, int* __restrict__ redo) {
-  constexpr bool DENSE = EPI == kEpiDense;
+    long phi_stride, float* __restrict__ bmax, long bmax_stride, int* __restrict__ redo) {
+  constexpr bool DENSE = EPI == kEpiDense || EPI == kEpiDensePipe;
   constexpr bool MLP = EPI != kEpiMaxDot;
-  // software-pipelined top-k scan
-  constexpr bool PIPE = EPI == kEpiTopkPipe;
-  using S = FusedShape<PX, D, H, MLP>;
+  // software-pipelined scans
+  constexpr bool PIPE = EPI == kEpiTopkPipe || EPI == kEpiDensePipe;
+  static_assert(SL == 1 || DENSE, "slices: dense forms");
+  using S = FusedShape<PX, D, H, MLP, SL, !DENSE>;
   // X2: the two-term chain (plain loop only: top-k, dense and bounded forms)
   static_assert(!X2 || EPI == kEpiTopk || EPI == kEpiDense || EPI == kEpiBounded, "two-term forms");
   using Mlp = MolMlp<PX, H, X2>;
@@ -124,7 +148,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
   const int base = lane_base(g, PX);
   // second launch after the pipelined scan: only the workgroups whose
   // range it flagged run (uniform per workgroup, before any barrier)
-  if (EPI == kEpiTopk && redo) {
+  if ((EPI == kEpiTopk || EPI == kEpiDense) && redo) {
     int any = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) any |= redo[blockIdx.x * kWaves + w];
@@ -133,7 +157,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
   int r, qg;
   wg_coords(blockIdx.x, R, G, r, qg);
   const int qwg = qg * S::QWG;            // first query of the workgroup
-  const int qwv = qwg + S::QPW * wave;    // first of this wave's QPW queries
+  const int pair = wave / SL, slice = SL == 1 ? 0 : wave % SL;   // a pair's slices on neighbouring SIMDs
+  const int qwv = qwg + S::QPW * pair;    // first of this wave's QPW queries
   const int nr0 = n_begin + r * range_len;
   const int nr1 = min(n_end, nr0 + range_len);
   const int ntiles = nr1 > nr0 ? (nr1 - nr0 + S::TILE - 1) / S::TILE : 0;
@@ -174,12 +199,13 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
       copy16_to_lds(src, lds_addr(dst));
     }
   };
-  for (int t = 0; t < kRing - 1 && t < ntiles; ++t) stage(t, t);
+  constexpr int kAhead = EPI == kEpiDensePipe ? kRing : kRing - 1;   // tiles staged before the loop
+  for (int t = 0; t < kAhead && t < ntiles; ++t) stage(t, t);
 
   // ---- per-workgroup constants ----
   // log2(e) (a_q + b2) per query of the workgroup, [query][p]
   if (MLP)
-    for (int i = tid; i < kQueriesPerWG * P; i += 64 * kWaves) {
+    for (int i = tid; i < S::QWG * P; i += 64 * kWaves) {
       const int qi = i / P, p = i % P, b = qwg + qi;
       sCb[i] = b < pr.B ? kLog2e * (pr.a_q[static_cast<long>(b) * P + p] + pr.b2[p]) : 0.f;
     }
@@ -209,8 +235,31 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
                        : make_uint4(0, 0, 0, 0);
   }
 
+  // dense outputs of the lane: query qwv in rows 0-1 (written by g = 0),
+  // qwv + 1 in rows 2-3 (g = 2)
+  const int qlane = qwv + (g >> 1);
+  const bool qstore = DENSE && (g & 1) == 0 && qlane < pr.B;
+  float* const phi_row = DENSE ? phi_out + static_cast<long>(min(qlane, pr.B - 1)) * phi_stride - n_begin : nullptr;
+  float* const bmax_row = DENSE && bmax ? bmax + static_cast<long>(min(qlane, pr.B - 1)) * bmax_stride : nullptr;
+  float vmax = -__builtin_inff();         // running maximum of the open bucket
+  // one scored step of item (tile t, item n of the tile): the dense store and
+  // the bucket maximum, closed after four steps of the wave or the last one
+  auto put_dense = [&](float v, int item, bool ok, int t, int st) {
+    if (ok && qstore) phi_row[item] = v;
+    if (bmax) {
+      vmax = fmaxf(vmax, ok ? v : -__builtin_inff());
+      constexpr int TPB = 4 / S::SPT;     // tiles per bucket block
+      if (st == S::SPT - 1 && ((t % TPB) == TPB - 1 || t + 1 == ntiles)) {
+        const int blk = (nr0 + S::TILE * t) / (64 * SL);
+        vmax = row16_max(vmax);
+        if (qstore && c == 0) bmax_row[blk * SL + slice] = vmax;
+        vmax = -__builtin_inff();
+      }
+    }
+  };
+
   // stage 0 complete; later stages' copies may still be in flight
-  if (ntiles >= kRing - 1) ring_barrier<(kRing - 2) * S::LOADS>();
+  if (ntiles >= kAhead) ring_barrier<(kAhead - 1) * S::LOADS>();
   else ring_barrier<0>();
 
   if constexpr (PIPE) {
@@ -224,13 +273,18 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
     // follows.  The arithmetic of every pair is that of phi2_interleaved.
     //
     // Ring discipline: one barrier per stage, in the step that is about to
-    // read the next stage.  A stage is last read in the first step of its
-    // own tile (the second step's reads are issued one step earlier), so past
-    // the barrier of tile t's second step every wave is done with tile t - 1
-    // and its buffer is refilled right away.
+    // read the next stage.  A wave's reads run one step ahead, so past the
+    // barrier in tile t's last step every wave is done with tile t itself.
+    // The dense form refills its buffer with tile t + 3 there (with slices a
+    // tile lasts one step, and two tiles in flight cover the copies' latency);
+    // the copies are issued after the step's stores, so that the counted wait
+    // of the next barrier (tile t + 2 has landed) leaves exactly the copies of
+    // tile t + 3 in flight.  The list form refills tile t - 1's buffer right
+    // after the barrier (three tiles ahead spills a register there and gains
+    // nothing: its tiles last two steps).
     auto x_reads = [&](int t, int st, uint4(&xb)[PX][S::KD]) {
       const unsigned char* xs = sX + (t % kRing) * S::XSTAGE;
-      const int n = 16 * st + c;
+      const int n = 16 * (slice + SL * st) + c;
 #pragma unroll
       for (int px = 0; px < PX; ++px) {
         const unsigned char* row = xs + (px * S::TILE + n) * (D * 2);
@@ -243,7 +297,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
     };
     auto ax_reads = [&](int t, int st, float4(&axv)[S::PT]) {
       const unsigned char* as = sAx + (t % kRing) * S::ASTAGE;
-      const int n = 16 * st + c;
+      const int n = 16 * (slice + SL * st) + c;
 #pragma unroll
       for (int q4 = 0; q4 < S::PT; ++q4) {
         const int phys = (base / 4 + q4) ^ (n % S::AROWCH);
@@ -271,12 +325,21 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
       for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
         for (int pt = 0; pt < S::PT; ++pt) {
-          const float4 cb = *reinterpret_cast<const float4*>(sCb + (2 * wave + qb) * P + base + 4 * pt);
+          const float4 cb = *reinterpret_cast<const float4*>(sCb + (2 * pair + qb) * P + base + 4 * pt);
           c0[qb][pt] = f32x4_t{fmaf(axv[pt].x, kLog2e, cb.x), fmaf(axv[pt].y, kLog2e, cb.y),
                                fmaf(axv[pt].z, kLog2e, cb.z), fmaf(axv[pt].w, kLog2e, cb.w)};
         }
     };
     bool redo_wave = false;
+    if (DENSE && qwv >= pr.B) {            // no query: the barriers and copies only
+      for (int t = 0; t + 1 < ntiles; ++t) {
+        if (t + 2 < ntiles) ring_barrier<S::LOADS>();
+        else ring_barrier<0>();
+        if (t + kRing < ntiles) stage(t + kRing, t % kRing);
+      }
+      if (lane == 0) redo[blockIdx.x * kWaves + wave] = 0;
+      return;
+    }
     f32x4_t lg1[S::PT];     // query 1's logits of the step in flight
     float s1[S::RUN];       // query 1's dot products of the step in flight
     float den0 = 0.f, num0 = 0.f;
@@ -295,17 +358,19 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
     }
     for (int t = 0; t < ntiles; ++t) {
 #pragma unroll
-      for (int st = 0; st < 2; ++st) {
-        const int item = nr0 + S::TILE * t + 16 * st + c;
+      for (int st = 0; st < S::SPT; ++st) {
+        const int item = nr0 + S::TILE * t + 16 * (slice + SL * st) + c;
         const bool item_ok = item < nr1;
-        const bool has_next = st == 0 || t + 1 < ntiles;
-        if (st == 1 && t + 1 < ntiles) {
-          ring_barrier<0>();
-          if (t + 2 < ntiles) stage(t + 2, (t + 2) % kRing);
+        const bool last = st == S::SPT - 1;              // of the tile
+        const bool has_next = !last || t + 1 < ntiles;
+        if (last && t + 1 < ntiles) {
+          if (DENSE && t + 2 < ntiles) ring_barrier<S::LOADS>();
+          else ring_barrier<0>();
+          if (!DENSE && t + 2 < ntiles) stage(t + 2, (t + 2) % kRing);
         }
         // the next step's X reads and GEMM1 with this step's stage B (past
         // the last step the current step's stage is read again, unused)
-        const int tn = st == 0 ? t : (has_next ? t + 1 : t), stn = st == 0 ? 1 : (has_next ? 0 : 1);
+        const int tn = last && has_next ? t + 1 : t, stn = !last ? st + 1 : (has_next ? 0 : st);
         float s2n[2][S::RUN];
         float Dn, Nm;
         __builtin_amdgcn_sched_barrier(0);
@@ -344,8 +409,10 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
         // launch's lists of that range are overwritten)
         const float v = Nm * __builtin_amdgcn_rcpf(Dn);
         redo_wave |= !__all(Dn >= 0x1p-60f && Dn <= 0x1p60f);
-        // one ballot decides whether either query has a candidate
-        {
+        if constexpr (DENSE) {
+          put_dense(v, item, item_ok, t, st);
+        } else {
+          // one ballot decides whether either query has a candidate
           const bool m0 = g == 0 && item_ok && v >= top[0].theta_score;
           const bool m1 = g == 2 && item_ok && v >= top[1].theta_score;
           if (__ballot(m0 || m1)) {
@@ -353,6 +420,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
             top[1].offer(m1 ? make_key(v, item) : 0ull, lane);
           }
         }
+        if (DENSE && last && t + kRing < ntiles) stage(t + kRing, t % kRing);
         if (has_next) {
           f32x4_t c0[2][S::PT];
           gate_bias2(axv, c0);   // 2 PT LDS reads of a_q + b2
@@ -372,8 +440,9 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
     const unsigned char* as = sAx + buf * S::ASTAGE;
 
 #pragma unroll
-    for (int st = 0; st < S::TILE / 16; ++st) {
-      const int n = 16 * st + c;            // item within the stage
+    for (int st = 0; st < S::SPT; ++st) {
+      if (DENSE && qwv >= pr.B) break;            // no query: the barriers and copies only
+      const int n = 16 * (slice + SL * st) + c;   // item within the stage
       const int item = nr0 + S::TILE * t + n;
       const bool item_ok = item < nr1;
 
@@ -453,12 +522,12 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
       auto gate_bias = [&](int qb, f32x4_t(&c0)[S::PT]) {
 #pragma unroll
         for (int pt = 0; pt < S::PT; ++pt) {
-          const float4 cb = *reinterpret_cast<const float4*>(sCb + (2 * wave + qb) * P + base + 4 * pt);
+          const float4 cb = *reinterpret_cast<const float4*>(sCb + (2 * pair + qb) * P + base + 4 * pt);
           c0[pt] = f32x4_t{fmaf(axv[pt].x, kLog2e, cb.x), fmaf(axv[pt].y, kLog2e, cb.y),
                            fmaf(axv[pt].z, kLog2e, cb.z), fmaf(axv[pt].w, kLog2e, cb.w)};
         }
       };
-      if constexpr (EPI == kEpiTopk || EPI == kEpiDense) {
+      if constexpr (EPI == kEpiTopk || DENSE) {
         // both queries' MLP chains in one call: interleaved by hand where the
         // matrix chains are short against the SiLU work (H <= 64), else
         // left to the compiler with raised priority around each chain
@@ -544,14 +613,9 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
       // (the two-query chain and the max-dot sets leave each query's result
       // there; the other forms in every lane)
 #pragma unroll
-      for (int qb = 0; qb < S::QPW; ++qb) {
-        const int b = qwv + qb;
-        if constexpr (DENSE) {
-          if (g == 2 * qb && item_ok && b < pr.B) phi_out[b * phi_stride + (item - n_begin)] = phi[qb];
-        } else {
-          top[qb].offer_score(phi[qb], item, g == 2 * (qb % 2) && offer[qb], lane);
-        }
-      }
+      for (int qb = 0; qb < S::QPW && !DENSE; ++qb)
+        top[qb].offer_score(phi[qb], item, g == 2 * (qb % 2) && offer[qb], lane);
+      if constexpr (DENSE) put_dense(g < 2 ? phi[0] : phi[1], item, item_ok, t, st);
     }
     // refill the buffer read in iteration t-1, then wait for stage t+1
     if (t + kRing - 1 < ntiles) {
@@ -577,6 +641,18 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
 }
 
 // ---------------------------------------------------------------------------
+// Arguments of one launch of k_mol_fused.
+struct FusedArgs {
+  int k = 1, R = 1, range_len = 0, G = 1, SL = 1, n_begin = 0, n_end = 0;
+  const float* bound = nullptr;
+  uint64_t* partial = nullptr;
+  float* phi = nullptr;
+  long phi_stride = 0;
+  float* bmax = nullptr;
+  long bmax_stride = 0;
+  int* redo = nullptr;
+};
+
 static bool fused_shape(const DevProb& pr, bool mlp) {
   if (pr.dtype != MOL_BF16 || pr.Pq != 8) return false;
   if (pr.Px == 8 && (pr.d == 64 || pr.d == 32)) return !mlp || pr.H == 64;
@@ -592,10 +668,12 @@ bool fused_maxdot_supported(const DevProb& pr, int k) {
   return fused_shape(pr, false) && k <= WaveTopk::kList;
 }
 
+// The list and max-dot forms (mol_topk_exact beyond the dense form's buffer,
+// the bounded and max-dot scans): about one workgroup per CU, since every
+// range costs its lists' fill and a share of the final merge.
 void fused_grid(const DevProb& pr, int n_count, int& R, int& range_len, int& G, bool maxdot) {
-  const int qwg = queries_per_wave<false>() * kWaves;   // max-dot form
-  G = maxdot ? (pr.B + qwg - 1) / qwg : (pr.B + kQueriesPerWG - 1) / kQueriesPerWG;
-  // about one workgroup per CU
+  const int qwg = (maxdot ? queries_per_wave<false>() : queries_per_wave<true>()) * kWaves;
+  G = (pr.B + qwg - 1) / qwg;
   R = std::max(1, 256 / G);
   // ranges of at least 128 items (4 tiles): small corpora still fill the chip
   const int max_r = std::max(1, n_count / 128);
@@ -605,81 +683,141 @@ void fused_grid(const DevProb& pr, int n_count, int& R, int& range_len, int& G, 
   R = (n_count + range_len - 1) / range_len;
 }
 
-template <int PX, int D, int H, int EPI, bool X2>
-static hipError_t launch_fused_x(const DevProb& pr, int k, int R, int range_len, int G, int n_begin,
-                                 int n_end, const float* bound, uint64_t* partial, float* phi,
-                                 long phi_stride, int* redo, hipStream_t st) {
-  using S = FusedShape<PX, D, H, EPI != kEpiMaxDot>;
-  auto kern = &k_mol_fused<PX, D, H, EPI, X2>;
+// Grid of the dense forms.  Slices: the most that still cover the batch with
+// one query group (SL = 4 where four 64-item stages fit the LDS).  Ranges:
+// of the counts that fill 1, 2, .. 16 rounds of one workgroup per CU, the one
+// with the least rounds * (steps of a range + a workgroup's set-up, worth
+// about 8 steps): a batch of 1201 is 76 groups, and 3 ranges each left 28 of
+// 256 CUs idle (exact top-50 of 100,003 items 3.74 ms; 10 rounds of 34 ranges
+// 3.05 ms).  Multiples of 8 are preferred at equal cost: the groups sharing a
+// range then run on one XCD and meet in its L2.
+FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count) {
+  FusedDenseGrid f;
+  const bool sl4 = pr.Px * 64l * (2 * pr.d + 32) * kRing <= 150 * 1024;   // X and a_x stages of 64 items
+  f.SL = pr.B <= 4 && sl4 ? 4 : pr.B <= 8 ? 2 : 1;
+  const int qwg = 2 * kWaves / f.SL, unit = 64 * f.SL;
+  f.G = (pr.B + qwg - 1) / qwg;
+  const int blocks = (n_count + unit - 1) / unit;
+  long best = -1;
+  for (int rounds = 1; rounds <= 16; ++rounds)
+    for (int even = 0; even < 2; ++even) {
+      int R = std::min(blocks, std::max(1, 256 * rounds / f.G));
+      if (even) R = std::max(1, R / 8 * 8);
+      const int len = (blocks + R - 1) / R;                 // units of a range
+      R = (blocks + len - 1) / len;
+      const long waves = (static_cast<long>(R) * f.G + 255) / 256;
+      const long cost = waves * (4l * len + 8) * (R % 8 == 0 || R == 1 || f.G == 1 ? 100 : 101);
+      if (best < 0 || cost < best) {
+        best = cost;
+        f.R = R;
+        f.range_len = len * unit;
+      }
+    }
+  return f;
+}
+
+template <int PX, int D, int H, int EPI, bool X2, int SL>
+static hipError_t launch_fused_x(const DevProb& pr, const FusedArgs& a, hipStream_t st) {
+  using S = FusedShape<PX, D, H, EPI != kEpiMaxDot, SL, EPI != kEpiDense && EPI != kEpiDensePipe>;
+  auto kern = &k_mol_fused<PX, D, H, EPI, X2, SL>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_TOTAL);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(R * G), dim3(64 * kWaves), S::LDS_TOTAL, st, pr, k, R, range_len,
-                     G, n_begin, n_end, bound, partial, phi, phi_stride, redo);
+  hipLaunchKernelGGL(kern, dim3(a.R * a.G), dim3(64 * kWaves), S::LDS_TOTAL, st, pr, a.k, a.R, a.range_len, a.G,
+                     a.n_begin, a.n_end, a.bound, a.partial, a.phi, a.phi_stride, a.bmax, a.bmax_stride, a.redo);
   return hipGetLastError();
 }
 
-// the two-term chain where the problem asks for it (MOL_FLAG_BF16X2_GATING)
+// the two-term chain where the problem asks for it (MOL_FLAG_BF16X2_GATING),
+// and the slices of the dense forms
 template <int PX, int D, int H, int EPI>
-static hipError_t launch_fused_t(const DevProb& pr, int k, int R, int range_len, int G, int n_begin,
-                                 int n_end, const float* bound, uint64_t* partial, float* phi,
-                                 long phi_stride, int* redo, hipStream_t st) {
-  if constexpr (EPI == kEpiTopk || EPI == kEpiDense || EPI == kEpiBounded) {
-    if (pr.flags & MOL_FLAG_BF16X2_GATING)
-      return launch_fused_x<PX, D, H, EPI, true>(pr, k, R, range_len, G, n_begin, n_end, bound, partial, phi,
-                                                 phi_stride, redo, st);
+static hipError_t launch_fused_t(const DevProb& pr, const FusedArgs& a, hipStream_t st) {
+  constexpr bool kDense = EPI == kEpiDense || EPI == kEpiDensePipe;
+  constexpr bool kX2 = EPI == kEpiTopk || EPI == kEpiDense || EPI == kEpiBounded;
+  constexpr bool kSl4 = PX * 64l * (2 * D + 32) * kRing <= 150 * 1024;
+  if constexpr (kX2) {
+    if (pr.flags & MOL_FLAG_BF16X2_GATING) {
+      if constexpr (kDense) {
+        if constexpr (kSl4) {
+          if (a.SL == 4) return launch_fused_x<PX, D, H, EPI, true, 4>(pr, a, st);
+        }
+        if (a.SL == 2) return launch_fused_x<PX, D, H, EPI, true, 2>(pr, a, st);
+      }
+      return launch_fused_x<PX, D, H, EPI, true, 1>(pr, a, st);
+    }
   }
-  return launch_fused_x<PX, D, H, EPI, false>(pr, k, R, range_len, G, n_begin, n_end, bound, partial, phi,
-                                              phi_stride, redo, st);
+  if constexpr (kDense) {
+    if constexpr (kSl4) {
+      if (a.SL == 4) return launch_fused_x<PX, D, H, EPI, false, 4>(pr, a, st);
+    }
+    if (a.SL == 2) return launch_fused_x<PX, D, H, EPI, false, 2>(pr, a, st);
+  }
+  return launch_fused_x<PX, D, H, EPI, false, 1>(pr, a, st);
 }
 
 template <int EPI>
-static hipError_t launch_fused_d(const DevProb& pr, int k, int R, int range_len, int G, int n_begin,
-                                 int n_end, const float* bound, uint64_t* partial, float* phi,
-                                 long phi_stride, int* redo, hipStream_t st) {
+static hipError_t launch_fused_d(const DevProb& pr, const FusedArgs& a, hipStream_t st) {
   // the max-dot epilogue has no gating MLP: one instantiation per (Px, d)
-  if (pr.Px == 8 && pr.d == 32)
-    return launch_fused_t<8, 32, 64, EPI>(pr, k, R, range_len, G, n_begin, n_end, bound, partial, phi,
-                                          phi_stride, redo, st);
-  if (pr.Px == 8)
-    return launch_fused_t<8, 64, 64, EPI>(pr, k, R, range_len, G, n_begin, n_end, bound, partial, phi,
-                                          phi_stride, redo, st);
-  if (pr.d == 128)
-    return launch_fused_t<4, 128, 128, EPI>(pr, k, R, range_len, G, n_begin, n_end, bound, partial, phi,
-                                            phi_stride, redo, st);
-  return launch_fused_t<4, 64, 64, EPI>(pr, k, R, range_len, G, n_begin, n_end, bound, partial, phi,
-                                        phi_stride, redo, st);
+  if (pr.Px == 8 && pr.d == 32) return launch_fused_t<8, 32, 64, EPI>(pr, a, st);
+  if (pr.Px == 8) return launch_fused_t<8, 64, 64, EPI>(pr, a, st);
+  if (pr.d == 128) return launch_fused_t<4, 128, 128, EPI>(pr, a, st);
+  return launch_fused_t<4, 64, 64, EPI>(pr, a, st);
 }
 
 long fused_redo_flags(int R, int G) { return static_cast<long>(R) * G * kWaves; }
 
 hipError_t launch_fused_topk(const DevProb& pr, int k, int R, int range_len, int G,
                              const float* bound, uint64_t* partial, int* redo, hipStream_t st) {
-  if (bound)
-    return launch_fused_d<kEpiBounded>(pr, k, R, range_len, G, 0, pr.N, bound, partial, nullptr, 0, nullptr,
-                                       st);
+  FusedArgs a;
+  a.k = k;
+  a.R = R;
+  a.range_len = range_len;
+  a.G = G;
+  a.n_end = pr.N;
+  a.bound = bound;
+  a.partial = partial;
+  if (bound) return launch_fused_d<kEpiBounded>(pr, a, st);
   if (redo && !(pr.flags & MOL_FLAG_BF16X2_GATING)) {
     // pipelined scan, then the plain scan over the ranges it flagged
-    hipError_t e = launch_fused_d<kEpiTopkPipe>(pr, k, R, range_len, G, 0, pr.N, nullptr, partial, nullptr, 0,
-                                                redo, st);
+    a.redo = redo;
+    hipError_t e = launch_fused_d<kEpiTopkPipe>(pr, a, st);
     if (e != hipSuccess) return e;
-    return launch_fused_d<kEpiTopk>(pr, k, R, range_len, G, 0, pr.N, nullptr, partial, nullptr, 0, redo, st);
   }
-  return launch_fused_d<kEpiTopk>(pr, k, R, range_len, G, 0, pr.N, nullptr, partial, nullptr, 0, nullptr, st);
+  return launch_fused_d<kEpiTopk>(pr, a, st);
 }
 
 hipError_t launch_fused_maxdot(const DevProb& pr, int k, int R, int range_len, int G,
                                uint64_t* partial, hipStream_t st) {
-  return launch_fused_d<kEpiMaxDot>(pr, k, R, range_len, G, 0, pr.N, nullptr, partial, nullptr, 0, nullptr,
-                                    st);
+  FusedArgs a;
+  a.k = k;
+  a.R = R;
+  a.range_len = range_len;
+  a.G = G;
+  a.n_end = pr.N;
+  a.partial = partial;
+  return launch_fused_d<kEpiMaxDot>(pr, a, st);
 }
 
-hipError_t launch_fused_dense(const DevProb& pr, int n_begin, int n_count, float* phi,
-                              hipStream_t st) {
-  int R, range_len, G;
-  fused_grid(pr, n_count, R, range_len, G, false);
-  return launch_fused_d<kEpiDense>(pr, 1, R, range_len, G, n_begin, n_begin + n_count, nullptr, nullptr,
-                                   phi, n_count, nullptr, st);
+hipError_t launch_fused_dense(const DevProb& pr, const FusedDenseGrid& f, int n_begin, int n_count, float* phi,
+                              long phi_stride, float* bmax, long bmax_stride, int* redo, hipStream_t st) {
+  FusedArgs a;
+  a.k = 1;
+  a.R = f.R;
+  a.range_len = f.range_len;
+  a.G = f.G;
+  a.SL = f.SL;
+  a.n_begin = n_begin;
+  a.n_end = n_begin + n_count;
+  a.phi = phi;
+  a.phi_stride = phi_stride;
+  a.bmax = bmax;
+  a.bmax_stride = bmax_stride;
+  if (redo && !(pr.flags & MOL_FLAG_BF16X2_GATING)) {
+    a.redo = redo;
+    hipError_t e = launch_fused_d<kEpiDensePipe>(pr, a, st);
+    if (e != hipSuccess) return e;
+  }
+  return launch_fused_d<kEpiDense>(pr, a, st);
 }
 
 }  // namespace mol

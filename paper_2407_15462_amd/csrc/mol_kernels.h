@@ -27,17 +27,17 @@ struct DenseRows {
   long phi_stride = 0;
   int L = 0;
   const int32_t* row_len = nullptr;
-  const float* bmax = nullptr;   // bucket W i + r: columns 4 W i + r + W j, j < 4
+  const float* bmax = nullptr;   // bucket SL i + s: the runs of 16 columns 4 SL i + s + SL j, j < 4
   long bmax_stride = 0;
-  int W = 16;
+  int SL = 1;
   const int32_t* ids = nullptr;
   long ids_stride = 0;
   float sign = 1.f;
   bool skip_neg_inf = false;
 };
-// floats of a row of bucket maxima
-inline long bucket_row(long L, int W) { return (L + 4 * W - 1) / (4 * W) * W; }
-// bucket maxima of sign * phi, W = 16
+// floats of a row of bucket maxima (and a multiple of 4)
+inline long bucket_row(long L, int SL) { return ((L + 64 * SL - 1) / (64 * SL) * SL + 3) / 4 * 4; }
+// bucket maxima of sign * phi, SL = 1 (rows 16-byte aligned)
 hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L, float sign, float* bmax,
                              long bmax_stride, hipStream_t st);
 hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_score, int32_t* out_idx, hipStream_t st);
@@ -138,8 +138,17 @@ hipError_t launch_fused_topk(const DevProb& pr, int k, int R, int range_len, int
                              const float* bound, uint64_t* partial, int* redo, hipStream_t st);
 hipError_t launch_fused_maxdot(const DevProb& pr, int k, int R, int range_len, int G,
                                uint64_t* partial, hipStream_t st);
-hipError_t launch_fused_dense(const DevProb& pr, int n_begin, int n_count, float* phi,
-                              hipStream_t st);
+// Dense scores phi [B][phi_stride] of items [n_begin, n_begin + n_count).
+// bmax: NULL, or [B][bmax_stride] bucket maxima (n_begin must be 0; buckets
+// of width 16 SL, see DenseRows).  redo: NULL, or fused_redo_flags(R, G)
+// ints: the software-pipelined scan, as above.
+struct FusedDenseGrid {
+  int SL = 1;                         // slices
+  int R = 1, range_len = 0, G = 1;    // item ranges, items per range, query groups
+};
+FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count);
+hipError_t launch_fused_dense(const DevProb& pr, const FusedDenseGrid& f, int n_begin, int n_count, float* phi,
+                              long phi_stride, float* bmax, long bmax_stride, int* redo, hipStream_t st);
 
 }  // namespace mol
 

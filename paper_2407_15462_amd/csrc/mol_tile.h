@@ -285,6 +285,19 @@ __device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint3
   lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
 }
 
+// 4 or 8 consecutive bf16 weights from any 2-byte boundary as one load (the
+// compiler emits it unaligned; every lane's weights are in flight at once)
+__device__ __forceinline__ uint2 load_bf16x4(const bf16_t* p) {
+  uint2 v;
+  __builtin_memcpy(&v, p, sizeof v);
+  return v;
+}
+__device__ __forceinline__ uint4 load_bf16x8(const bf16_t* p) {
+  uint4 v;
+  __builtin_memcpy(&v, p, sizeof v);
+  return v;
+}
+
 // Per-wave constants of the gating MLP in MFMA operand layouts.
 //
 // X2 (the two-term form): W1 and -W2 enter as their own bf16 values (exact),
@@ -316,13 +329,12 @@ struct MolMlp {
     for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
       for (int m = 0; m < KP; ++m) {
-        const bf16_t* src = W1 + (16 * jt + c) * P + base + 8 * m;
-        uint32_t w[4];
+        const uint4 src = load_bf16x8(W1 + (16 * jt + c) * P + base + 8 * m);
+        uint32_t w[4] = {src.x, src.y, src.z, src.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          w[e] = X2 ? static_cast<uint32_t>(src[2 * e]) | (static_cast<uint32_t>(src[2 * e + 1]) << 16)
-                    : neg_bf16_to_f16_bits(src[2 * e], kLog2e) |
-                          (neg_bf16_to_f16_bits(src[2 * e + 1], kLog2e) << 16);
+        for (int e = 0; e < 4 && !X2; ++e)
+          w[e] = neg_bf16_to_f16_bits(static_cast<bf16_t>(w[e] & 0xffffu), kLog2e) |
+                 (neg_bf16_to_f16_bits(static_cast<bf16_t>(w[e] >> 16), kLog2e) << 16);
         w1op[jt][m] = make_uint4(w[0], w[1], w[2], w[3]);
       }
     // -W2: row 16 pt + c <-> p = base(c/4) + 4 pt + c%4; K slot 8g+e <-> j
@@ -331,17 +343,15 @@ struct MolMlp {
 #pragma unroll
       for (int m = 0; m < KH; ++m) {
         const int p = lane_base(c >> 2, PX) + 4 * pt + (c & 3);
-        uint32_t w[4];
+        // K slots e < 4: j = 32 m + 4 g + e, then 16 further on
+        const bf16_t* src = W2 + p * H + 32 * m + 4 * g;
+        const uint2 lo = load_bf16x4(src), hi = load_bf16x4(src + 16);
+        uint32_t w[4] = {lo.x, lo.y, hi.x, hi.y};
 #pragma unroll
-        for (int e2 = 0; e2 < 4; ++e2) {
-          const int e0 = 2 * e2, e1 = 2 * e2 + 1;
-          const int j0 = 32 * m + 16 * (e0 >> 2) + 4 * g + (e0 & 3);
-          const int j1 = 32 * m + 16 * (e1 >> 2) + 4 * g + (e1 & 3);
-          w[e2] = X2 ? (static_cast<uint32_t>(W2[p * H + j0]) ^ 0x8000u) |
-                           ((static_cast<uint32_t>(W2[p * H + j1]) ^ 0x8000u) << 16)
-                     : neg_bf16_to_f16_bits(W2[p * H + j0], 1.f) |
-                           (neg_bf16_to_f16_bits(W2[p * H + j1], 1.f) << 16);
-        }
+        for (int e = 0; e < 4; ++e)
+          w[e] = X2 ? w[e] ^ 0x80008000u
+                    : neg_bf16_to_f16_bits(static_cast<bf16_t>(w[e] & 0xffffu), 1.f) |
+                          (neg_bf16_to_f16_bits(static_cast<bf16_t>(w[e] >> 16), 1.f) << 16);
         w2op[pt][m] = make_uint4(w[0], w[1], w[2], w[3]);
       }
 #pragma unroll

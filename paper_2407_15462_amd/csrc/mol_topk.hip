@@ -11,11 +11,12 @@
 //
 // What bounds it: one read of the row at a workgroup's rate (about 100 GB/s)
 // and a dozen barriers.  With per-bucket maxima from the kernel that scored
-// the row (bucket W i + r: items 4 W i + r + W s, s < 4)
-// it reads those instead, a quarter of the row, and then only the items of
-// the k buckets that reach T.  Measured: top-100 of 32 rows of 109,739 scores
-// 22 us plus 6 us for the maxima (chunked radix selection, segmented sort and
-// decode of 64-bit keys: 52 us); straight from the rows 61 us.
+// the row (64 items a bucket)
+// it reads those instead, a 64th of the row, and then only the items of the k
+// buckets that reach T: one CU draws some 20 GB/s from memory other CUs wrote.  Measured: top-100 of 32
+// rows of 109,739 scores 13 us plus 6 us for the maxima (chunked radix
+// selection, segmented sort and decode of 64-bit keys: 52 us; straight from the
+// rows 61 us), of one row of 2^20 19 us.
 #include "mol_kernels.h"
 
 namespace mol {
@@ -40,7 +41,7 @@ __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float
 // with (-inf, -1).
 __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int L_all,
                                                            const int32_t* __restrict__ row_len,
-                                                           const float* __restrict__ bmax, long bmax_stride, int W,
+                                                           const float* __restrict__ bmax, long bmax_stride, int SL,
                                                            const int32_t* __restrict__ ids, long ids_stride, int k,
                                                            float sign, int skip_neg_inf, float* __restrict__ out_score,
                                                            int32_t* __restrict__ out_idx) {
@@ -59,36 +60,47 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
     const uint32_t u = score_image(sign * f);
     return u > none ? u : 0u;
   };
-  const int nb = bmax ? static_cast<int>((L + 4l * W - 1) / (4 * W) * W) : L;     // values of the first pass
-  const float* val = bmax ? bmax + row * bmax_stride : src;
-  // four values a thread and load where the row allows it
-  const bool vec = (reinterpret_cast<uintptr_t>(val) & 15) == 0;
-  auto for_values = [&](auto&& f) {                 // f(index of the first, 4 values, how many are valid)
-    constexpr int U = 4;                            // loads in flight
-    for (int i0 = 4 * tid; i0 < nb; i0 += U * 4 * kTopThreads) {
+  // f(index of the first, 4 values, how many are valid) over n floats: four
+  // consecutive ones a thread and load, or single ones where those would leave
+  // threads without a value; U loads in flight
+  auto for_values = [&](const float* v0, int n, auto&& f) {
+    constexpr int U = 4;
+    if (n <= 4 * kTopThreads) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = v0[max(min(tid + u * kTopThreads, n - 1), 0)];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (tid + u * kTopThreads < n) f(tid + u * kTopThreads, float4{v[u], v[u], v[u], v[u]}, 1);
+      return;
+    }
+    const bool vec = (reinterpret_cast<uintptr_t>(v0) & 15) == 0;
+    for (int i0 = 4 * tid; i0 < n; i0 += U * 4 * kTopThreads) {
       float4 v[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = i0 + u * 4 * kTopThreads;
-        if (vec && i + 4 <= nb) {
-          v[u] = *reinterpret_cast<const float4*>(val + i);
+        if (vec && i + 4 <= n) {
+          v[u] = *reinterpret_cast<const float4*>(v0 + i);
         } else {
-          const int last = nb - 1;
-          v[u] = float4{val[min(i, last)], val[min(i + 1, last)], val[min(i + 2, last)], val[min(i + 3, last)]};
+          const int last = n - 1;
+          v[u] = float4{v0[min(i, last)], v0[min(i + 1, last)], v0[min(i + 2, last)], v0[min(i + 3, last)]};
         }
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = i0 + u * 4 * kTopThreads;
-        if (i < nb) f(i, v[u], min(4, nb - i));
+        if (i < n) f(i, v[u], min(4, n - i));
       }
     }
   };
+  const int nb = bmax ? (L + 64 * SL - 1) / (64 * SL) * SL : L;     // values of the first pass
+  const float* val = bmax ? bmax + row * bmax_stride : src;
 
   // the thread's maximum, in floats (values past the end repeat the last one;
   // fmaxf passes NaN over)
   float fm = __builtin_nanf("");
-  for_values([&](int, const float4& v, int) {
+  for_values(val, nb, [&](int, const float4& v, int) {
     fm = fmaxf(fm, fmaxf(fmaxf(sign * v.x, sign * v.y), fmaxf(sign * v.z, sign * v.w)));
   });
   const uint32_t mx = image(sign * fm);
@@ -179,27 +191,15 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
   __syncthreads();
   // the float compare decides almost every value; images decide the rest
   const float Tf = T > float_to_ordered(-__builtin_inff()) ? ordered_to_float(T) : -__builtin_inff();
-  auto visit = [&](auto&& f) {                       // f(image, column) of the row's items at or above T
-    for_values([&](int i, const float4& v4, int n) {
+  // f(index, image) of the values at or above T of an array
+  auto for_hits = [&](const float* v0, int n, auto&& f) {
+    for_values(v0, n, [&](int i, const float4& v4, int nv) {
       const float v[4] = {sign * v4.x, sign * v4.y, sign * v4.z, sign * v4.w};
       if (!(v[0] >= Tf || v[1] >= Tf || v[2] >= Tf || v[3] >= Tf)) return;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const uint32_t im = e < n ? image(sign * v[e]) : 0u;
-        if (im < T) continue;
-        if (!bmax) {
-          f(im, i + e);
-        } else {
-          const int c0 = 4 * W * ((i + e) / W) + (i + e) % W;
-          float x[4];
-#pragma unroll
-          for (int s = 0; s < 4; ++s) x[s] = src[min(c0 + W * s, L - 1)];
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const uint32_t u = c0 + W * s < L ? image(x[s]) : 0u;   // (the column past the end: none)
-            if (u >= T) f(u, c0 + W * s);
-          }
-        }
+        const uint32_t im = e < nv ? image(sign * v[e]) : 0u;
+        if (im >= T) f(i + e, im);
       }
     });
   };
@@ -207,34 +207,44 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
     const int32_t item = id ? id[col] : col;
     return (static_cast<uint64_t>(u) << 32) | static_cast<uint32_t>(~static_cast<uint32_t>(item));
   };
-  auto collect = [&](uint32_t u, int col) {
+  auto collect = [&](int col, uint32_t u) {
     const uint32_t pos = atomicAdd(&s_count, 1u);
     if (pos < static_cast<uint32_t>(kTopCap)) buf[pos] = key_of(u, col);
   };
   uint32_t hot_n = kTopHot + 1;
   if (bmax) {
-    // the buckets that reach T, then their items four a bucket, one a thread:
-    // one round trip to memory instead of one for each bucket of a wave
-    for_values([&](int i, const float4& v4, int nv) {
-      const float v[4] = {sign * v4.x, sign * v4.y, sign * v4.z, sign * v4.w};
-      if (!(v[0] >= Tf || v[1] >= Tf || v[2] >= Tf || v[3] >= Tf)) return;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (e < nv && image(sign * v[e]) >= T) {
-          const uint32_t pos = atomicAdd(&s_hot, 1u);
-          if (pos < static_cast<uint32_t>(kTopHot)) hot[pos] = i + e;
-        }
+    // the buckets that reach T, then their items, a wave a bucket: the loads
+    // of all buckets in flight instead of one bucket's after another's
+    for_hits(val, nb, [&](int i, uint32_t) {
+      const uint32_t pos = atomicAdd(&s_hot, 1u);
+      if (pos < static_cast<uint32_t>(kTopHot)) hot[pos] = i;
     });
     __syncthreads();
     hot_n = s_hot;
-    if (hot_n <= static_cast<uint32_t>(kTopHot))
-      for (int t = tid; t < 4 * static_cast<int>(hot_n); t += kTopThreads) {
-        const int bk = hot[t >> 2], col = 4 * W * (bk / W) + bk % W + W * (t & 3);
-        const uint32_t u = col < L ? image(src[col]) : 0u;
-        if (u >= T) collect(u, col);
+    if (hot_n <= static_cast<uint32_t>(kTopHot)) {
+      const int nt = 64 * static_cast<int>(hot_n);
+      for (int t0 = tid; t0 < nt; t0 += 4 * kTopThreads) {
+        float x[4];
+        int col[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int t = t0 + u * kTopThreads;
+          col[u] = L;
+          if (t < nt) {                              // item t % 64 of bucket hot[t / 64]
+            const int bk = hot[t >> 6], blk = bk / SL;
+            col[u] = 16 * (4 * SL * blk + (bk - blk * SL) + SL * ((t >> 4) & 3)) + (t & 15);
+          }
+          x[u] = src[min(col[u], L - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t im = col[u] < L ? image(x[u]) : 0u;
+          if (im >= T) collect(col[u], im);
+        }
       }
+    }
   }
-  if (hot_n > static_cast<uint32_t>(kTopHot)) visit(collect);
+  if (hot_n > static_cast<uint32_t>(kTopHot)) for_hits(src, L, collect);
   __syncthreads();
   uint32_t n = s_count;
   if (n > static_cast<uint32_t>(kTopCap)) {
@@ -246,7 +256,7 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
       __syncthreads();
       if (tid < 256) hist[tid] = 0u;
       __syncthreads();
-      visit([&](uint32_t u, int col) {
+      for_hits(src, L, [&](int col, uint32_t u) {
         const uint64_t key = key_of(u, col);
         if (shift == 56 || (key >> (shift + 8)) == (prefix >> (shift + 8)))
           atomicAdd(&hist[static_cast<uint32_t>(key >> shift) & 255u], 1u);
@@ -259,7 +269,7 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
     __syncthreads();
     if (tid == 0) s_count = 0u;
     __syncthreads();
-    visit([&](uint32_t u, int col) {
+    for_hits(src, L, [&](int col, uint32_t u) {
       const uint64_t key = key_of(u, col);
       if (key >= prefix) {
         const uint32_t pos = atomicAdd(&s_count, 1u);
@@ -320,20 +330,24 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
   }
 }
 
-// Bucket maxima of dense rows (the layout k_topk_dense reads): a wave takes
-// 256 consecutive scores of a row, four a lane; lane (q, j) = (lane / 16,
-// lane % 16) reads columns 64 q + 16 s + j, s < 4.
+// Bucket maxima of dense rows (SL = 1: 64 consecutive columns a bucket): a
+// lane reads four columns, 16 lanes a bucket.  The rows' strides keep the
+// reads aligned and inside the buffer (a multiple of 4 floats).
 __global__ __launch_bounds__(256) void k_bucket_max(const float* __restrict__ phi, long phi_stride, int L, float sign,
                                                     float* __restrict__ bmax, long bmax_stride) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long row = blockIdx.y;
-  const int col = (blockIdx.x * 4 + wave) * 256 + (lane >> 4) * 64 + (lane & 15);
-  if (col - (lane & 15) >= L) return;
-  const float* src = phi + row * phi_stride;
+  const int col = (blockIdx.x * 256 + threadIdx.x) * 4;
   float m = __builtin_nanf("");
+  if (col < L) {
+    const float4 v = *reinterpret_cast<const float4*>(phi + row * phi_stride + col);
+    m = sign * v.x;
+    if (col + 1 < L) m = fmaxf(m, sign * v.y);
+    if (col + 2 < L) m = fmaxf(m, sign * v.z);
+    if (col + 3 < L) m = fmaxf(m, sign * v.w);
+  }
 #pragma unroll
-  for (int s = 0; s < 4; ++s) m = fmaxf(m, col + 16 * s < L ? sign * src[col + 16 * s] : m);
-  bmax[row * bmax_stride + (col >> 6) * 16 + (col & 15)] = sign * m;
+  for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 16));
+  if ((threadIdx.x & 15) == 0 && col < L) bmax[row * bmax_stride + (col >> 6)] = sign * m;
 }
 
 hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L, float sign, float* bmax,
@@ -347,7 +361,7 @@ hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_sco
                              hipStream_t st) {
   if (k > kTopkDenseMaxK) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_topk_dense, dim3(rows), dim3(kTopThreads), 0, st, r.phi, r.phi_stride, r.L, r.row_len, r.bmax,
-                     r.bmax_stride, r.W, r.ids, r.ids_stride, k, r.sign, r.skip_neg_inf ? 1 : 0, out_score, out_idx);
+                     r.bmax_stride, r.SL, r.ids, r.ids_stride, k, r.sign, r.skip_neg_inf ? 1 : 0, out_score, out_idx);
   return hipGetLastError();
 }
 
