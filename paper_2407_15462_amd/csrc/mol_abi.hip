@@ -215,9 +215,9 @@ hipError_t pairwise_score(const DevProb& pr, float* sbuf, long sRow, int mode, c
 // lists wherever the buffer stays under kDenseMax bytes.
 constexpr size_t kDenseMax = size_t(512) << 20;
 // Rows from this length on are ranked through bucket maxima (if there are at
-// least 2 k of them: fewer leave a threshold that admits too much), written by
-// the fused scan or formed by a launch of their own (about 5 us); the top-k
-// kernel reads other rows directly.
+// least 1.5 k of them: fewer leave a threshold that admits more than the
+// selection's list holds), written by the fused scan or formed by a launch of
+// their own (about 5 us); the top-k kernel reads other rows directly.
 constexpr int kBucketMinN = 1 << 14;
 
 struct DensePlan {
@@ -229,8 +229,13 @@ struct DensePlan {
   size_t offPhi = 0, offBmax = 0, offS = 0, offRedo = 0, bytes = 0;
 };
 
+bool use_buckets(long N, int k) { return N >= kBucketMinN && N >= 96l * k; }
+// k above 512 takes six passes over a row without bucket maxima: up to 64K
+// scores (about 60 us) that is still the faster way
+bool dense_k(long N, int k) { return k <= 512 || (k <= kTopkDenseMaxK && (use_buckets(N, k) || N <= 65536)); }
+
 bool dense_fits(const DevProb& pr, int k) {
-  return k <= kTopkDenseMaxK && 4ul * pr.B * ((pr.N + 3l) & ~3l) <= kDenseMax;
+  return dense_k(pr.N, k) && 4ul * pr.B * ((pr.N + 3l) & ~3l) <= kDenseMax;
 }
 
 enum DenseBy { kByFused, kByPairs, kByMaxDot };   // what scores the rows
@@ -246,7 +251,7 @@ DensePlan plan_dense(const DevProb& pr, int k, DenseBy by) {
     f.offRedo = off;
     off = align_up(off + 4ul * fused_redo_flags(f.g.R, f.g.G));
   }
-  if (pr.N >= kBucketMinN && pr.N >= 128l * k) {
+  if (use_buckets(pr.N, k)) {
     f.offBmax = off;
     off = align_up(off + 4ul * pr.B * bucket_row(pr.N, f.g.SL));
   }
@@ -423,10 +428,12 @@ PerEmbdPlan plan_per_embd(const DevProb& pr, int kp) {
   f.offBmax = off;  off = align_up(off + 4ul * s.rows * f.g.s1.R * f.g.nbk);
   f.offThr = off;   off = align_up(off + 4ul * s.rows);
   f.offThrT = off;  off = align_up(off + 4ul * s.rows);
-  if (f.g.pruned) {
-    const size_t nvec = static_cast<size_t>(pr.B) * pr.Pq;
+  if (f.g.pruned || f.g.append) {
     f.offCtl = off;   off = align_up(off + 4ul * (s.rows + 2) + 4);       // counts, flag, work-list length
     f.offKeys = off;  off = align_up(off + 8ul * s.rows * f.g.key_cap);
+  }
+  if (f.g.pruned) {
+    const size_t nvec = static_cast<size_t>(pr.B) * pr.Pq;
     f.offHotV = off;  off = align_up(off + 4ul * f.g.groups * nvec);
     f.offHotN = off;  off = align_up(off + 4ul * f.g.groups);
     f.offWork = off;  off = align_up(off + 4ul * f.g.groups * f.g.CH);
@@ -442,9 +449,11 @@ PerEmbdBufs per_embd_bufs(const PerEmbdPlan& f, char* w) {
   b.bmax = reinterpret_cast<float*>(w + f.offBmax);
   b.thr = reinterpret_cast<float*>(w + f.offThr);
   b.thr_t = reinterpret_cast<float*>(w + f.offThrT);
-  if (f.g.pruned) {
+  if (f.g.pruned || f.g.append) {
     b.ctl = reinterpret_cast<uint32_t*>(w + f.offCtl);
     b.keys = reinterpret_cast<uint64_t*>(w + f.offKeys);
+  }
+  if (f.g.pruned) {
     b.hot_v = reinterpret_cast<int*>(w + f.offHotV);
     b.hot_n = reinterpret_cast<int*>(w + f.offHotN);
     b.work = reinterpret_cast<int*>(w + f.offWork);
@@ -488,7 +497,32 @@ ThreshPlan plan_thresh(const DevProb& pr, int kp) {
   return t;
 }
 
+// Per-component lists from dense dot products: the GEMM writes every list's
+// scores and bucket maxima, one top-k launch ranks the lists.
+struct DenseListPlan {
+  long ld = 0, bstride = 0;
+  size_t offS = 0, offBmax = 0, bytes = 0;
+};
+
+DenseListPlan plan_dense_lists(const DevProb& pr) {
+  DenseListPlan f;
+  f.ld = dots_buffer_row(pr.N);
+  f.bstride = bucket_row(pr.N, 1);
+  const size_t rows = static_cast<size_t>(pr.B) * pr.P;
+  f.offBmax = align_up(4 * rows * f.ld);
+  f.bytes = f.offBmax + align_up(4 * rows * f.bstride);
+  return f;
+}
+
+// where the score buffer fits, and the shape has no per-component kernel or
+// the list is longer than its pruned form takes
+bool use_dense_lists(const DevProb& pr, int kp) {
+  return dots_mfma_supported(pr) && dense_k(pr.N, kp) && 4ul * pr.B * pr.P * dots_buffer_row(pr.N) <= kDenseMax &&
+         !(per_embd_supported(pr, kp) && kp <= 256);
+}
+
 size_t per_embd_ws_bytes(const DevProb& pr, int kp) {
+  if (use_dense_lists(pr, kp)) return plan_dense_lists(pr).bytes;
   if (per_embd_supported(pr, kp)) return plan_per_embd(pr, kp).bytes;
   if (use_thresh_per_embd(pr, kp)) return plan_thresh(pr, kp).bytes;
   return plan_stream(pr.B * pr.P, pr.N, kp).bytes;
@@ -664,15 +698,34 @@ int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx
                  hipStream_t st) {
   int rc;
   const int rows = pr.B * pr.P;
+  if (use_dense_lists(pr, kprime)) {
+    const DenseListPlan f = plan_dense_lists(pr);
+    DenseRows r;
+    float* sbuf = reinterpret_cast<float*>(w + f.offS);
+    float* bmax = use_buckets(pr.N, kprime) ? reinterpret_cast<float*>(w + f.offBmax) : nullptr;
+    MOL_TIMED_LAUNCH(timed_op, st,
+                     launch_dots_mfma(pr, 0, pr.N, kDotsToBuffer, sbuf, f.ld * pr.B, f.ld, nullptr, 0, st, 1, bmax,
+                                      f.bstride),
+                     "list dots");
+    r.phi = sbuf;
+    r.phi_stride = f.ld;
+    r.P = pr.P;
+    r.p_rows = pr.B;
+    r.L = pr.N;
+    r.bmax = bmax;
+    r.bmax_stride = f.bstride;
+    MOL_TRY_HIP(launch_topk_dense(r, rows, kprime, out_dot, out_idx, st), "list top-k'");
+    return MOL_OK;
+  }
   if (per_embd_supported(pr, kprime)) {
     const PerEmbdPlan f = plan_per_embd(pr, kprime);
     const PerEmbdBufs b = per_embd_bufs(f, w);
     uint64_t* fin = reinterpret_cast<uint64_t*>(w + f.offFinal);
     MOL_TIMED_LAUNCH(timed_op, st, launch_per_embd(pr, kprime, f.g, b, st), "per-component top-k'");
-    // pruned form: a sort per list, then the threshold scan's lists are
+    // appending forms: a sort per list, then the threshold scan's lists are
     // reduced only if some list overflowed its key buffer (flag ctl[rows])
     const uint32_t* gate = nullptr;
-    if (f.g.pruned) {
+    if (f.g.pruned || f.g.append) {
       MOL_TRY_HIP(launch_per_embd_select(pr, kprime, f.g, b, out_dot, out_idx, st), "per-component select");
       gate = b.ctl + rows;
     }

@@ -69,7 +69,8 @@ __global__ __launch_bounds__(256) void k_dots_mfma(DevProb pr, int n0, int nt, i
                                                    float* __restrict__ sbuf, long s_pstride, long s_bstride,
                                                    uint64_t* __restrict__ keys, long key_stride,
                                                    const uint64_t* __restrict__ thr, long thr_stride,
-                                                   uint32_t* __restrict__ counts) {
+                                                   uint32_t* __restrict__ counts, float* __restrict__ bmax,
+                                                   long bmax_stride) {
   constexpr int TI = 128, KS = 64, CH = KS / 8;   // tile items, K per step, chunks per row
   constexpr int NBV = TV / 64;                    // 32-vector blocks per wave
   constexpr int BL = TV * CH / 256;               // vector-row chunks per thread and step
@@ -264,6 +265,38 @@ __global__ __launch_bounds__(256) void k_dots_mfma(DevProb pr, int n0, int nt, i
     return;
   }
 
+  if (MODE == kDotsToBuffer && bmax) {
+    // bucket maxima straight from the accumulators: lane (c, h) holds half of
+    // the wave's 64 items for vector c of each block column, the other half's
+    // maximum comes by one lane swap (reading the rows back through lane
+    // shuffles cost a quarter of the kernel)
+    const int i0 = it0 + 64 * wm;
+    if (i0 + 64 > cnt) {                                 // wave-uniform: the ragged last tile
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const bool ok = i0 + 32 * ib + 8 * (e >> 2) + 4 * h + (e & 3) < cnt;
+#pragma unroll
+          for (int jb = 0; jb < NBV; ++jb) acc[ib][jb][e] = ok ? acc[ib][jb][e] : -__builtin_inff();
+        }
+    }
+#pragma unroll
+    for (int jb = 0; jb < NBV; ++jb) {
+      float m = fmaxf(acc[0][jb][0], acc[1][jb][0]);
+#pragma unroll
+      for (int e = 1; e < 16; ++e) m = fmaxf(fmaxf(m, acc[0][jb][e]), acc[1][jb][e]);
+      const uint32_t u = __float_as_uint(m);
+      auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+      m = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      const int v = v0 + wn * (TV / 2) + jb * 32 + c;
+      if (h == 0 && v < v1 && i0 < cnt) {
+        const int b = v / pr.Pq, p = (v - b * pr.Pq) * pr.Px + px;
+        bmax[(static_cast<long>(p) * pr.B + b) * bmax_stride + (i0 >> 6)] = m;
+      }
+    }
+  }
+
   // The loop ended with a barrier: the staging area is free.  Each 64-row
   // half of the tile goes through LDS (rows padded to TR floats) so that
   // every global store instruction writes a contiguous run of one row.
@@ -339,19 +372,20 @@ template <int MODE>
 static void dots_launch(int tv, dim3 grid, hipStream_t st, const DevProb& pr, int n0, int nt, int tile_stride,
                         const int32_t* items, const int32_t* item_count, long item_stride, float* sbuf,
                         long s_pstride, long s_bstride, uint64_t* keys, long key_stride, const uint64_t* thr,
-                        long thr_stride, uint32_t* counts) {
+                        long thr_stride, uint32_t* counts, float* bmax = nullptr, long bmax_stride = 0) {
   if (tv == 128)
     hipLaunchKernelGGL((k_dots_mfma<MODE, 128>), grid, dim3(256), 0, st, pr, n0, nt, tile_stride, items,
                        item_count, item_stride, sbuf, s_pstride, s_bstride, keys, key_stride, thr, thr_stride,
-                       counts);
+                       counts, bmax, bmax_stride);
   else
     hipLaunchKernelGGL((k_dots_mfma<MODE, 64>), grid, dim3(256), 0, st, pr, n0, nt, tile_stride, items,
                        item_count, item_stride, sbuf, s_pstride, s_bstride, keys, key_stride, thr, thr_stride,
-                       counts);
+                       counts, bmax, bmax_stride);
 }
 
 hipError_t launch_dots_mfma(const DevProb& pr, int n0, int nt, int mode, float* sbuf, long s_pstride,
-                            long s_bstride, uint64_t* keys, long key_stride, hipStream_t st, int tile_stride) {
+                            long s_bstride, uint64_t* keys, long key_stride, hipStream_t st, int tile_stride,
+                            float* bmax, long bmax_stride) {
   if (nt <= 0) return hipSuccess;
   if (tile_stride < 1 || (tile_stride > 1 && mode != kDotsToKeys)) return hipErrorInvalidValue;
   const int tv = dots_tv(pr);
@@ -359,7 +393,7 @@ hipError_t launch_dots_mfma(const DevProb& pr, int n0, int nt, int mode, float* 
   const dim3 grid((tiles + tile_stride - 1) / tile_stride, (pr.B * pr.Pq + tv - 1) / tv, pr.Px);
   if (mode == kDotsToBuffer)
     dots_launch<kDotsToBuffer>(tv, grid, st, pr, n0, nt, 1, nullptr, nullptr, 0l, sbuf, s_pstride, s_bstride,
-                               nullptr, 0l, nullptr, 0l, nullptr);
+                               nullptr, 0l, nullptr, 0l, nullptr, bmax, bmax_stride);
   else
     dots_launch<kDotsToKeys>(tv, grid, st, pr, n0, nt, tile_stride, nullptr, nullptr, 0l, nullptr, 0l, 0l, keys,
                              key_stride, nullptr, 0l, nullptr);

@@ -21,10 +21,12 @@ hipError_t launch_mol_f32(const DevProb& pr, int mode, const float* bound, int n
 // L scores a row (row_len: NULL or valid counts), bmax: NULL or per-bucket
 // maxima (of sign * phi, times sign; rows then hold L scores), ids: NULL or the item of each column.  Rows are
 // ranked by sign * phi; skip_neg_inf: a score of -inf is an excluded column.
-constexpr int kTopkDenseMaxK = 512;
+constexpr int kTopkDenseMaxK = 2048;
 struct DenseRows {
   const float* phi = nullptr;
   long phi_stride = 0;
+  int P = 1;                     // lists a query: list p of query b is row p * p_rows + b,
+  long p_rows = 0;               // ranked as output row b * P + p
   int L = 0;
   const int32_t* row_len = nullptr;
   const float* bmax = nullptr;   // bucket SL i + s: the runs of 16 columns 4 SL i + s + SL j, j < 4
@@ -59,9 +61,11 @@ hipError_t launch_dots_mfma_maxkeys(const DevProb& pr, int n0, int nt, uint64_t*
 bool dots_mfma_supported(const DevProb& pr);
 long dots_buffer_row(int nt);
 long dots_sample_len(int nt, int tile_stride);
+// bmax (buffer form): NULL, or bucket maxima (DenseRows, SL = 1) of the rows
+// s[p][b], bmax_stride floats apart.
 hipError_t launch_dots_mfma(const DevProb& pr, int n0, int nt, int mode, float* sbuf, long s_pstride,
                             long s_bstride, uint64_t* keys, long key_stride, hipStream_t st,
-                            int tile_stride = 1);
+                            int tile_stride = 1, float* bmax = nullptr, long bmax_stride = 0);
 hipError_t launch_dots_mfma_candidates(const DevProb& pr, int n0, int nt, const uint64_t* thr, long thr_stride,
                                        uint64_t* cand, long cand_stride, uint32_t* counts, hipStream_t st);
 // the same into the buffer for per-query candidate lists (items [B][item_stride],
@@ -164,7 +168,8 @@ struct PerEmbdGrid {
   Scan s1, s2;                         // bucket scan, threshold scan
   int bucket_tiles = 0, nbk = 0;       // 32-item tiles per bucket, buckets per range
   bool pruned = false;                 // the pruned second pass (else the threshold scan)
-  int key_cap = 0;                     // pruned pass: keys per list buffer
+  bool append = false;                 // the small-batch form's appending second scan (else the threshold scan)
+  int key_cap = 0;                     // appending forms: keys per list buffer
   int vec_wg_pruned = 0, CH = 0;       // pruned pass: vectors per workgroup, chunks per bucket group
   int groups = 0;                      // bucket groups Px * s1.R * nbk
 };
@@ -186,8 +191,8 @@ int per_embd_list_cap(int kp);
 int per_embd_stage_cap(int kp);
 void per_embd_grid(const DevProb& pr, int kp, PerEmbdGrid& g);
 // the scans (and, for the pruned form, its work list and pass); the lists
-// are then finished by launch_per_embd_select (pruned form) and, gated on
-// ctl[rows] (every list when it is set; always without the pruned form),
+// are then finished by launch_per_embd_select (appending forms) and, gated on
+// ctl[rows] (every list when it is set; always without the appending forms),
 // by the segmented reduction of `lists`
 hipError_t launch_per_embd(const DevProb& pr, int kp, const PerEmbdGrid& g, const PerEmbdBufs& b, hipStream_t st);
 hipError_t launch_per_embd_select(const DevProb& pr, int kp, const PerEmbdGrid& g, const PerEmbdBufs& b,

@@ -26,6 +26,8 @@
 //     list's key buffer; a sort per list finishes it.  Should a list
 //     receive more keys than its buffer holds (massive ties), a device flag
 //     switches the call to the threshold scan below for every list.
+//     Small batches (up to 256 query vectors: every bucket is hot for some of
+//     them) append from one more scan over all items instead of a work list.
 //     The threshold scan walks all items again from T: scores that reach
 //     it are appended to the lane's staging region in the workspace; a full
 //     staging region is merged into the list by a wave-wide bitonic sort in
@@ -58,7 +60,10 @@ constexpr int nb_pick(int d, bool scan2, bool small) { return small ? 1 : nb_for
 // waves per workgroup: 8, or 4 for lists of 512 / 1024 keys, whose merge
 // sorts need 8 / 16 KB of LDS per wave
 constexpr int waves_for(int kl) { return kl >= 512 ? 4 : 8; }
-enum ScanMode { kScanBuckets = 0, kScanThreshold = 1, kScanPruned = 2 };
+// bytes of one LDS item stage: small enough in the small-batch form that two
+// workgroups share a CU
+constexpr int stage_bytes(int kl, bool small) { return waves_for(kl) == 8 && !small ? 32768 : 16384; }
+enum ScanMode { kScanBuckets = 0, kScanThreshold = 1, kScanPruned = 2, kScanAppend = 3 };
 constexpr int kRing = 3;                     // item stages in flight
 constexpr int kSGMax = 512;                  // largest staging region per lane half
 constexpr int kMaxBuckets = 2048;            // bucket maxima per list (all ranges, both halves)
@@ -68,17 +73,19 @@ __device__ __forceinline__ f32x16_t mfma32_bf16(uint4 a, uint4 b, f32x16_t c) {
                                                  __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// per-lane key slots of the pruned pass's LDS staging, per vector block
-constexpr int kHitSlots = 2;
-
-template <int D, int KL, bool SCAN2, bool SMALL, bool PRUNED = false>
+// MODE: the scan's form (ScanMode)
+template <int D, int KL, int MODE, bool SMALL>
 struct EmbdShape {
+  static constexpr bool SCAN2 = MODE == kScanThreshold;
+  // per-lane key slots of the LDS staging, per vector block, of the forms
+  // that append to key buffers
+  static constexpr int HITS = MODE == kScanPruned ? 2 : MODE == kScanAppend ? 4 : 0;
   static constexpr int KD = D / 16;                    // K blocks (32x32x16)
   static constexpr int NB = nb_pick(D, SCAN2, SMALL);
   static constexpr int VEC_WAVE = 32 * NB;             // query vectors per wave
   static constexpr int WAVES = waves_for(KL);
   static constexpr int VEC_WG = WAVES * VEC_WAVE;
-  static constexpr int STAGE_BYTES = WAVES == 8 ? 32768 : 16384;   // bytes of one LDS item stage
+  static constexpr int STAGE_BYTES = stage_bytes(KL, SMALL);       // of one LDS item stage
   static constexpr int ROWCH = D / 8;                  // 16-byte chunks per item row
   // XOR swizzle of a row's chunks: the 16 rows one 16-lane group reads land
   // on distinct 16-byte bank slots of each 256-byte LDS line
@@ -90,8 +97,8 @@ struct EmbdShape {
   static constexpr int LOADS = STAGE_BYTES / 1024 / WAVES;   // copies per lane per stage
   static constexpr int LDS_X = kRing * STAGE_BYTES;
   static constexpr int LDS_SORT = SCAN2 ? WAVES * SORT * 8 : 0;   // the threshold scan's merge sorts
-  // the pruned pass: kHitSlots keys per (wave, block, lane), lane-contiguous
-  static constexpr int LDS_HIT = PRUNED ? WAVES * NB * kHitSlots * 64 * 8 : 0;
+  // HITS keys per (wave, block, lane), lane-contiguous
+  static constexpr int LDS_HIT = WAVES * NB * HITS * 64 * 8;
   static constexpr int LDS_TOTAL = LDS_X + LDS_SORT + LDS_HIT;
   static_assert(ST % 32 == 0, "stage holds whole 32-item tiles");
   static_assert(KL + 2 * SG <= SORT && SG <= kSGMax, "sort region holds list + both staging halves");
@@ -100,7 +107,7 @@ struct EmbdShape {
 
 }  // namespace
 
-// Inputs and outputs of the pruned pass (and the flag the threshold scan
+// Inputs and outputs of the appending forms (and the flag the threshold scan
 // and the final selection are gated on).
 struct PrunedArgs {
   const int* work = nullptr;          // [groups * CH]: g * CH + chunk of each work item
@@ -132,7 +139,8 @@ __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
     uint64_t* __restrict__ stg, const uint32_t* __restrict__ gate, PrunedArgs pa) {
   constexpr bool SCAN2 = MODE == kScanThreshold;
   constexpr bool PRUNED = MODE == kScanPruned;
-  using S = EmbdShape<D, KL, SCAN2, SMALL, PRUNED>;
+  constexpr bool APPEND = PRUNED || MODE == kScanAppend;   // keys reaching T go to the lists' key buffers
+  using S = EmbdShape<D, KL, MODE, SMALL>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* sX = smem;
   uint64_t* sSort = reinterpret_cast<uint64_t*>(smem + S::LDS_X);
@@ -238,7 +246,7 @@ __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
         for (int i = 0; i < KL; ++i) lp[i] = 0ull;
       }
     }
-    if (PRUNED && vok[nb]) {
+    if (APPEND && vok[nb]) {
       // T lowered by a few units in the last place (see the file comment)
       const float t = thr[static_cast<long>(vv[nb]) * Px + px];
       th[nb] = t - 0x1p-20f * fmaxf(1.f, fabsf(t));
@@ -316,7 +324,7 @@ __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
   // Threshold / bucket work of tile j.  RAGGED: the tile may reach past the
   // range end (items there become -inf and are never staged).
   int bcount = 0, bk = 0;                         // bucket scan: tiles in the open bucket, its index
-  uint32_t hitc = 0u;                             // pruned pass: LDS slots used, 8 bits per block
+  uint32_t hitc = 0u;                             // appending forms: LDS slots used, 8 bits per block
   // bucket scan: close bucket b of every block: the two lanes of a list
   // (items 4h .. 4h + 3 of every 8) join their maxima, half 0 stores
   auto store_buckets = [&](int b) {
@@ -364,7 +372,7 @@ __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
       }
       return;
     }
-    if constexpr (PRUNED) {
+    if constexpr (APPEND) {
       bool hit = false;
 #pragma unroll
       for (int nb = 0; nb < S::NB; ++nb) hit = hit || m[nb] >= th[nb];
@@ -390,8 +398,8 @@ __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
                 const int item = n0 + (v >> 2) * 8 + 4 * half + (v & 3);
                 const uint64_t key = make_key(acc[nb][v], item);
                 const int used = (hitc >> (8 * nb)) & 0xFF;
-                if (used < kHitSlots) {
-                  sHit[((wave * S::NB + nb) * kHitSlots + used) * 64 + lane] = key;
+                if (used < S::HITS) {
+                  sHit[((wave * S::NB + nb) * S::HITS + used) * 64 + lane] = key;
                   hitc += 1u << (8 * nb);
                 } else {
                   const long list = static_cast<long>(vv[nb]) * Px + px;
@@ -498,7 +506,7 @@ __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
     }
     return;
   }
-  if constexpr (PRUNED) {
+  if constexpr (APPEND) {
     // append the staged keys: one atomic per lane and block reserves them
 #pragma unroll
     for (int nb = 0; nb < S::NB; ++nb) {
@@ -508,7 +516,7 @@ __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
         const uint32_t base = atomicAdd(pa.cnt + list, static_cast<uint32_t>(used));
         for (int i = 0; i < used; ++i) {
           const uint32_t slot = base + i;
-          const uint64_t key = sHit[((wave * S::NB + nb) * kHitSlots + i) * 64 + lane];
+          const uint64_t key = sHit[((wave * S::NB + nb) * S::HITS + i) * 64 + lane];
           if (slot < static_cast<uint32_t>(pa.cap)) pa.keys[list * pa.cap + slot] = key;
           else *pa.flag = 1u;
         }
@@ -751,19 +759,21 @@ int per_embd_stage_cap(int kp) {
 }
 
 // items of one LDS stage (EmbdShape::ST) for width d and list capacity kl
-static int stage_items(int d, int kl) { return (waves_for(kl) == 8 ? 32768 : 16384) / (2 * d); }
+static int stage_items(int d, int kl, bool small) { return stage_bytes(kl, small) / (2 * d); }
 
 static void scan_grid(const DevProb& pr, int kp, bool scan2, PerEmbdGrid::Scan& sc) {
   const int nvec = pr.B * pr.Pq;
   const int vec_wg = waves_for(per_embd_list_cap(kp)) * 32 * nb_pick(pr.d, scan2, per_embd_small(pr, kp));
   sc.G = (nvec + vec_wg - 1) / vec_wg;
   const int units = sc.G * pr.Px;
-  // about one workgroup per CU, with ranges of at least 512 items
-  int R = std::max(1, (256 + units - 1) / units);
+  // about one workgroup per CU (two in the small-batch form's bucket and
+  // appending scans), with ranges of at least 512 items
+  const bool small = per_embd_small(pr, kp);
+  int R = std::max(1, ((small && !scan2 ? 512 : 256) + units - 1) / units);
   R = std::min(R, std::max(1, pr.N / 512));
   // whole stages per range: a range's tile walk then covers exactly
   // range_len / 32 tiles, the count the bucket layout is sized for
-  const int unit = std::max(128, stage_items(pr.d, per_embd_list_cap(kp)));
+  const int unit = std::max(128, stage_items(pr.d, per_embd_list_cap(kp), small));
   sc.range_len = (pr.N + R - 1) / R;
   sc.range_len = (sc.range_len + unit - 1) / unit * unit;
   sc.R = (pr.N + sc.range_len - 1) / sc.range_len;
@@ -775,7 +785,8 @@ void per_embd_grid(const DevProb& pr, int kp, PerEmbdGrid& g) {
   const int KL = per_embd_list_cap(kp);
   const int nvec = pr.B * pr.Pq;
   const int ntiles = g.s1.range_len / 32;
-  const int tps = stage_items(pr.d, KL) / 32;
+  const bool small = per_embd_small(pr, kp);
+  const int tps = stage_items(pr.d, KL, small) / 32;
   g.vec_wg_pruned = waves_for(KL) * 32 * nb_pick(pr.d, false, false);
   g.CH = (nvec + g.vec_wg_pruned - 1) / g.vec_wg_pruned;
   g.key_cap = 2 * KL;
@@ -787,7 +798,7 @@ void per_embd_grid(const DevProb& pr, int kp, PerEmbdGrid& g) {
   // vectors; B is chosen so that this fills 80 % of a workgroup's vector
   // slots (partly filled second chunks would cost a full pass), and at
   // least 4 k' buckets keep the pass at a quarter of a full scan or less.
-  const bool can_prune = KL <= 256 && !per_embd_small(pr, kp);
+  const bool can_prune = KL <= 256 && !small;
   int target = kp <= 128 ? kMaxBuckets / 2 : kMaxBuckets;
   if (can_prune) {
     const long want = (5l * nvec * kp + 4l * g.vec_wg_pruned - 1) / (4l * g.vec_wg_pruned);
@@ -804,6 +815,8 @@ void per_embd_grid(const DevProb& pr, int kp, PerEmbdGrid& g) {
     g.nbk = (ntiles + g.bucket_tiles - 1) / g.bucket_tiles;
   }
   g.pruned = can_prune && g.s1.R * g.nbk >= 4 * kp;
+  // 2 k' buckets: at most about 1.4 k' keys reach T, the buffers hold 2 KL
+  g.append = KL <= 256 && small && g.s1.R * g.nbk >= 2 * kp;
   g.groups = pr.Px * g.s1.R * g.nbk;
 }
 
@@ -820,7 +833,7 @@ static int resident_cus() {
 template <int D, int KL, int MODE, bool SMALL>
 static hipError_t launch_pe_t(const DevProb& pr, int kp, const PerEmbdGrid& g, const PerEmbdBufs& b,
                               const uint32_t* gate, hipStream_t st) {
-  using S = EmbdShape<D, KL, MODE == kScanThreshold, SMALL, MODE == kScanPruned>;
+  using S = EmbdShape<D, KL, MODE, SMALL>;
   const PerEmbdGrid::Scan& sc = MODE == kScanThreshold ? g.s2 : g.s1;
   auto kern = &k_topk_per_embd<D, KL, MODE, SMALL>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -828,16 +841,17 @@ static hipError_t launch_pe_t(const DevProb& pr, int kp, const PerEmbdGrid& g, c
   if (e != hipSuccess) return e;
   PrunedArgs pa;
   int grid = sc.G * pr.Px * sc.R;
-  if (MODE == kScanPruned) {
-    const int rows = pr.B * pr.Pq * pr.Px;
-    pa.work = b.work;
-    pa.work_total = b.ctl + rows + 1;
-    pa.hot_v = b.hot_v;
-    pa.hot_n = b.hot_n;
+  if (MODE == kScanPruned || MODE == kScanAppend) {
     pa.cnt = b.ctl;
     pa.keys = b.keys;
-    pa.flag = b.ctl + rows;
+    pa.flag = b.ctl + pr.B * pr.Pq * pr.Px;
     pa.cap = g.key_cap;
+  }
+  if (MODE == kScanPruned) {
+    pa.work = b.work;
+    pa.work_total = b.ctl + pr.B * pr.Pq * pr.Px + 1;
+    pa.hot_v = b.hot_v;
+    pa.hot_n = b.hot_n;
     pa.CH = g.CH;
     grid = std::min<long>(static_cast<long>(g.groups) * g.CH, resident_cus());   // persistent, one per CU
   }
@@ -851,7 +865,7 @@ static hipError_t launch_pe_s(const DevProb& pr, int kp, const PerEmbdGrid& g, c
                               hipStream_t st) {
   const int nvec = pr.B * pr.Pq, rows = nvec * pr.Px;
   hipError_t e;
-  if (g.pruned) {
+  if (g.pruned || g.append) {
     // per-list key counts, the overflow flag and the work-list length start at zero
     e = launch_fill(reinterpret_cast<uint64_t*>(b.ctl), (rows + 2 + 1) / 2, 0ull, st);
     if (e != hipSuccess) return e;
@@ -880,6 +894,13 @@ static hipError_t launch_pe_s(const DevProb& pr, int kp, const PerEmbdGrid& g, c
       if (e != hipSuccess) return e;
       // the threshold scan only where some list overflowed its key buffer
       return launch_pe_t<D, KL, kScanThreshold, false>(pr, kp, g, b, b.ctl + rows, st);
+    }
+  }
+  if constexpr (SMALL) {
+    if (g.append) {
+      e = launch_pe_t<D, KL, kScanAppend, true>(pr, kp, g, b, nullptr, st);
+      if (e != hipSuccess) return e;
+      return launch_pe_t<D, KL, kScanThreshold, true>(pr, kp, g, b, b.ctl + rows, st);
     }
   }
   return launch_pe_t<D, KL, kScanThreshold, SMALL>(pr, kp, g, b, nullptr, st);

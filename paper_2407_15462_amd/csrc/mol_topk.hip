@@ -2,7 +2,7 @@
 // workgroup per row, straight to the decoded outputs.
 //
 // Every thread takes the maximum of its own share of the row (1024 disjoint
-// buckets).  k buckets whose maxima reach T hold k items scoring at least T,
+// buckets; for k > 512 every bucket of bmax, or score, counts by itself).  k buckets whose maxima reach T hold k items scoring at least T,
 // so T = the k-th largest bucket maximum bounds the row's k-th score from
 // below, and about k + k^2 / 2048 items of the row reach it: those are
 // collected in LDS, ranked by counting and written out.  A row whose items
@@ -25,7 +25,8 @@ namespace {
 
 constexpr int kTopThreads = 1024;
 constexpr int kTopCap = 4096;          // keys held in LDS
-constexpr int kTopHot = 1024;          // buckets collected before their items are read
+constexpr int kTopCoarse = 512;        // largest k ranked by the threads' maxima
+constexpr int kTopHot = 4096;          // buckets collected before their items are read
 constexpr int kTopRankMax = 256;       // up to this many keys are ranked by counting, more are sorted
 
 // score image, 0 for "no item" (NaN: never ranked)
@@ -33,13 +34,14 @@ __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float
 
 }  // namespace
 
-// phi [rows][phi_stride], L scores a row (row_len: NULL or the valid count of
+// phi [rows][phi_stride] (P lists a query: list p of query b is row p * p_rows
+// + b, written as row b * P + p), L scores a row (row_len: NULL or the valid count of
 // each row); bmax: NULL, or [rows][bmax_stride] bucket maxima; ids: NULL (item
 // = column), or the item of each column [rows][ids_stride]; sign: the rows
 // are ranked by sign * phi, and that is what is written; skip_neg_inf: a score
 // of -inf marks an excluded column.  Rows with fewer than k items are padded
 // with (-inf, -1).
-__global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int L_all,
+__global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P, long p_rows, int L_all,
                                                            const int32_t* __restrict__ row_len,
                                                            const float* __restrict__ bmax, long bmax_stride, int SL,
                                                            const int32_t* __restrict__ ids, long ids_stride, int k,
@@ -51,8 +53,10 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
   __shared__ uint32_t s_hi, s_lo, s_count, s_hot, s_bin, s_above;
   const int tid = threadIdx.x, lane = tid & 63;
   const long row = blockIdx.x;
+  // row r is list (b, p) = (r / P, r % P) of a [p][b] layout; P = 1: row r
+  const long at = row / P + (row % P) * p_rows;
   const int L = row_len ? min(row_len[row], L_all) : L_all;
-  const float* src = phi + row * phi_stride;
+  const float* src = phi + at * phi_stride;
   const int32_t* id = ids ? ids + row * ids_stride : nullptr;
   const uint32_t none = skip_neg_inf ? float_to_ordered(-__builtin_inff()) : 0u;
   // image of column i's score: 0 for an excluded one
@@ -95,7 +99,7 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
     }
   };
   const int nb = bmax ? (L + 64 * SL - 1) / (64 * SL) * SL : L;     // values of the first pass
-  const float* val = bmax ? bmax + row * bmax_stride : src;
+  const float* val = bmax ? bmax + at * bmax_stride : src;
 
   // the thread's maximum, in floats (values past the end repeat the last one;
   // fmaxf passes NaN over)
@@ -104,10 +108,35 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
     fm = fmaxf(fm, fmaxf(fmaxf(sign * v.x, sign * v.y), fmaxf(sign * v.z, sign * v.w)));
   });
   const uint32_t mx = image(sign * fm);
+  // beyond kTopCoarse every value counts by itself: the thread maxima are too
+  // few to hold the k-th
+  const bool fine = k > kTopCoarse;
+  uint32_t lo_v = mx ? mx : 0xFFFFFFFFu, n_v = mx ? 1u : 0u;   // smallest nonzero image, count
+  auto for_images = [&](auto&& f) {                            // f(image) of each value, or of the maximum
+    if (!fine) {
+      if (mx) f(mx);
+      return;
+    }
+    for_values(val, nb, [&](int, const float4& v4, int nv) {
+      const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t im = e < nv ? image(v[e]) : 0u;
+        if (im) f(im);
+      }
+    });
+  };
+  if (fine) {
+    lo_v = 0xFFFFFFFFu;
+    n_v = 0u;
+    for_images([&](uint32_t im) {
+      lo_v = min(lo_v, im);
+      ++n_v;
+    });
+  }
 
-  // T: the k-th largest thread maximum, to 24 bits below the highest bit in
-  // which the nonzero maxima differ (the bits left out only lower T); 0 with
-  // fewer than k of them
+  // T: the k-th largest of them, to 24 bits below the highest bit in which
+  // they differ (the bits left out only lower T); 0 with fewer than k
   if (tid == 0) {
     s_hi = 0u;
     s_lo = 0xFFFFFFFFu;
@@ -115,17 +144,17 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
   }
   __syncthreads();
   {
-    uint32_t hi = mx, lo = mx ? mx : 0xFFFFFFFFu;
+    uint32_t hi = mx, lo = lo_v, n = n_v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       hi = max(hi, static_cast<uint32_t>(__shfl_xor(static_cast<int>(hi), o)));
       lo = min(lo, static_cast<uint32_t>(__shfl_xor(static_cast<int>(lo), o)));
+      n += static_cast<uint32_t>(__shfl_xor(static_cast<int>(n), o));
     }
-    const uint64_t nz = __ballot(mx != 0u);
-    if (lane == 0 && nz) {
+    if (lane == 0 && n) {
       atomicMax(&s_hi, hi);
       atomicMin(&s_lo, lo);
-      atomicAdd(&s_count, static_cast<uint32_t>(__popcll(nz)));
+      atomicAdd(&s_count, n);
     }
   }
   __syncthreads();
@@ -174,8 +203,10 @@ __global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restr
       __syncthreads();
       if (tid < 256) hist[tid] = 0u;
       __syncthreads();
-      if (mx != 0u && (bits >= 32 || (mx >> bits) == (T >> bits)))
-        atomicAdd(&hist[(mx >> shift) & ((1u << (bits - shift)) - 1u)], 1u);
+      for_images([&](uint32_t im) {
+        if (bits >= 32 || (im >> bits) == (T >> bits))
+          atomicAdd(&hist[(im >> shift) & ((1u << (bits - shift)) - 1u)], 1u);
+      });
       __syncthreads();
       find_bin(kk);
       kk -= s_above;
@@ -360,7 +391,7 @@ hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L,
 hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_score, int32_t* out_idx,
                              hipStream_t st) {
   if (k > kTopkDenseMaxK) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_topk_dense, dim3(rows), dim3(kTopThreads), 0, st, r.phi, r.phi_stride, r.L, r.row_len, r.bmax,
+  hipLaunchKernelGGL(k_topk_dense, dim3(rows), dim3(kTopThreads), 0, st, r.phi, r.phi_stride, r.P, r.p_rows, r.L, r.row_len, r.bmax,
                      r.bmax_stride, r.SL, r.ids, r.ids_stride, k, r.sign, r.skip_neg_inf ? 1 : 0, out_score, out_idx);
   return hipGetLastError();
 }

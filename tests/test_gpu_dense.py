@@ -58,3 +58,61 @@ def test_dense_topk_ties_across_ranges():
     torch.cuda.synchronize()
     ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
     assert torch.equal(s, ws[:, :100]) and torch.equal(i.long(), wi[:, :100])
+
+
+def _ordered(v, i):
+    """descending scores, ascending ids among equals"""
+    return bool(((v[:, 1:] < v[:, :-1]) | ((v[:, 1:] == v[:, :-1]) & (i[:, 1:] > i[:, :-1]))).all())
+
+
+# lists ranked from dense dot products: rows with and without bucket maxima, k
+# on both sides of 512 and at its largest, a ragged last tile, and (the last) a
+# problem whose dense scores pass the buffer's limit (the sampled-threshold form)
+@pytest.mark.parametrize("B,Pq,Px,d,N,kp", [
+    (3, 4, 4, 96, 3001, 50), (5, 2, 3, 96, 20011, 128), (2, 4, 4, 768, 16447, 5), (3, 1, 1, 64, 4000, 600),
+    (4, 1, 1, 32, 200001, 2048), (2, 1, 1, 128, 60001, 513), (1, 1, 1, 64, 50000, 512), (64, 4, 4, 96, 140001, 60),
+])
+def test_dense_lists(B, Pq, Px, d, N, kp):
+    log(f"[lists] B={B} P={Pq}x{Px} d={d} N={N} k'={kp}")
+    g = torch.Generator(device="cuda").manual_seed(N)
+    Q = torch.nn.functional.normalize(torch.randn((B, Pq, d), generator=g, device="cuda"), dim=-1).bfloat16()
+    X = torch.nn.functional.normalize(torch.randn((Px, N, d), generator=g, device="cuda"), dim=-1).bfloat16()
+    dots, ids = mol.topk_per_embd(mol.Problem(Q, X), kp)
+    torch.cuda.synchronize()
+    for b in range(0, B, max(1, B // 3)):
+        s = torch.stack([Q[b].double() @ X[px].double().t().contiguous() for px in range(Px)], 1).view(Pq * Px, N)
+        want = torch.topk(s, kp, dim=1).values
+        got = torch.gather(s, 1, ids[b].long())
+        # float32 sums of d products of unit rows
+        tol = d * 2.0 ** -24
+        assert (dots[b].double() - got).abs().max() <= tol and (got - want).abs().max() <= 2 * tol
+        assert all(torch.unique(ids[b, p]).numel() == kp for p in range(Pq * Px))
+        assert _ordered(dots[b], ids[b])
+
+
+# the small-batch per-component form: lists on both sides of its appending
+# scan's bucket rule (2 k' buckets), every width and list capacity, ragged
+# ranges; and a batch whose lists overflow their key buffers (identical items)
+@pytest.mark.parametrize("B,Px,d,N,kp,ties", [
+    (1, 1, 32, 700, 10, 0), (32, 8, 32, 33001, 200, 0), (3, 4, 64, 8192, 128, 0), (3, 4, 64, 8191, 129, 0),
+    (32, 4, 128, 24186, 100, 0), (5, 2, 128, 20000, 256, 0), (31, 8, 64, 50001, 5, 0), (4, 8, 32, 40000, 100, 3000),
+])
+def test_small_batch_lists(B, Px, d, N, kp, ties):
+    log(f"[small lists] B={B} P=8x{Px} d={d} N={N} k'={kp} ties={ties}")
+    g = torch.Generator(device="cuda").manual_seed(N + kp)
+    X = torch.nn.functional.normalize(torch.randn((Px, N, d), generator=g, device="cuda"), dim=-1).bfloat16()
+    Q = torch.nn.functional.normalize(torch.randn((B, 8, d), generator=g, device="cuda"), dim=-1).bfloat16()
+    if ties:
+        at = torch.randperm(N, generator=torch.Generator().manual_seed(2))[:ties].cuda()
+        X[:, at] = X[:, at[:1]]
+        Q[0] = X[torch.arange(8) % Px, at[0]]
+        Q[1] = 0
+    dots, ids = mol.topk_per_embd(mol.Problem(Q, X), kp)
+    torch.cuda.synchronize()
+    tol = d * 2.0 ** -24
+    for b in range(B):
+        s = torch.stack([Q[b].double() @ X[px].double().t().contiguous() for px in range(Px)], 1).view(8 * Px, N)
+        want = torch.topk(s, kp, dim=1).values
+        got = torch.gather(s, 1, ids[b].long())
+        assert (dots[b].double() - got).abs().max() <= tol and (got - want).abs().max() <= 2 * tol
+        assert _ordered(dots[b], ids[b])
