@@ -334,37 +334,41 @@ int stream_topk(const StreamPlan& s, int N, char* ws, F score_tile, float* out_s
   return MOL_OK;
 }
 
-// Rerank workspace: uniq [B][C], n_unique [B], key rows A/B, final keys,
-// and on the generic path with MFMA dots the candidates' dot products.
+// Rerank workspace: uniq [B][C], n_unique [B], then dense scores [B][ld] or
+// (k beyond the dense selection) key rows A/B and final keys, and on the
+// generic path with MFMA dots the candidates' dot products.
 struct RerankPlan {
   StreamPlan s;
+  long ld = 0;                     // floats per score row (0: key rows)
   long sRow = 0;
-  size_t offUniq = 0, offNu = 0, offFinal = 0, offS = 0, bytes = 0;
+  size_t offUniq = 0, offNu = 0, offPhi = 0, offFinal = 0, offS = 0, bytes = 0;
 };
 
+// the fused rerank for the k of the fused kernels' other forms
+bool use_fused_rerank(const DevProb& pr, int k) { return rerank_supported(pr) && fused_supported(pr, k); }
+
 RerankPlan plan_rerank(const DevProb& pr, int C, int k) {
-  const int B = pr.B;
+  const size_t B = pr.B;
   RerankPlan r;
   StreamPlan& s = r.s;
-  s.rows = B;
+  s.rows = pr.B;
   s.k = k;
   s.T = C;
-  // generic path: keys of every candidate; fused path: per-chunk top-k lists
-  long L0 = C;
-  if (rerank_supported(pr, k)) {
-    const int chunk = rerank_chunk(B, C);
-    L0 = static_cast<long>((C + chunk - 1) / chunk) * k;
-  }
-  const int S0 = segment_size_for(static_cast<int>(L0), k);
-  s.strideA = std::max<long>(L0, k);
-  s.strideB = std::max<long>((L0 + S0 - 1) / S0 * k, k);
   size_t off = 0;
-  s.offA = off;   off = align_up(off + 8ul * B * s.strideA);
-  s.offB = off;   off = align_up(off + 8ul * B * s.strideB);
-  r.offFinal = off; off = align_up(off + 8ul * B * k);
+  if (dense_k(C, k)) {
+    r.ld = (C + 3l) & ~3l;
+    r.offPhi = off; off = align_up(off + 4ul * B * r.ld);
+  } else {
+    const int S0 = segment_size_for(C, k);
+    s.strideA = std::max(C, k);
+    s.strideB = std::max<long>((C + S0 - 1l) / S0 * k, k);
+    s.offA = off;     off = align_up(off + 8ul * B * s.strideA);
+    s.offB = off;     off = align_up(off + 8ul * B * s.strideB);
+    r.offFinal = off; off = align_up(off + 8ul * B * k);
+  }
   r.offUniq = off;  off = align_up(off + 4ul * B * C);
   r.offNu = off;    off = align_up(off + 4ul * B);
-  if (!rerank_supported(pr, k) && pairwise_mfma(pr, dots_buffer_row(C))) {
+  if (!use_fused_rerank(pr, k) && pairwise_mfma(pr, dots_buffer_row(C))) {
     r.sRow = dots_buffer_row(C);
     r.offS = off;   off = align_up(off + 4ul * pr.P * B * r.sRow);
   }
@@ -769,37 +773,43 @@ int run_rerank(const DevProb& pr, const int32_t* cand, int C, const int32_t* can
   const RerankPlan r = plan_rerank(pr, CT, k);
   int32_t* uniq = reinterpret_cast<int32_t*>(w + r.offUniq);
   int32_t* nu = reinterpret_cast<int32_t*>(w + r.offNu);
-  uint64_t* A = reinterpret_cast<uint64_t*>(w + r.s.offA);
-  uint64_t* fin = reinterpret_cast<uint64_t*>(w + r.offFinal);
-  MOL_TRY_HIP(launch_dedup(cand, C, cand2, C2, pr.B, pr.N, uniq, nu, st), "dedup");
-  if (rerank_supported(pr, k)) {
-    const int chunk = rerank_chunk(pr.B, CT);
-    const long L0 = static_cast<long>((CT + chunk - 1) / chunk) * k;
-    MOL_TIMED_LAUNCH(timed_op, st, launch_rerank(pr, uniq, nu, CT, k, negate, A, st), "fused rerank");
-    if ((rc = reduce_rows(r.s, w, L0, fin, k, st))) return rc;
-  } else {
+  MOL_TRY_HIP(launch_dedup(cand, C, cand2, C2, pr.B, pr.N, uniq, nu, out_n_unique, st), "dedup");
+  // scores as dense rows, or as sort keys where k is beyond those
+  float* phi = r.ld ? reinterpret_cast<float*>(w + r.offPhi) : nullptr;
+  uint64_t* A = r.ld ? nullptr : reinterpret_cast<uint64_t*>(w + r.s.offA);
+  const int mode = negate && !phi ? kGenNegPhi : kGenPhi;
+  if (use_fused_rerank(pr, k)) {   // (k of the dense rows)
+    MOL_TIMED_LAUNCH(timed_op, st, launch_rerank(pr, uniq, nu, CT, phi, r.ld, st), "fused rerank");
+  } else if (r.sRow) {
     // candidates' dot products on MFMA where the shape allows, then the
-    // pair-wise gating kernel; float32 otherwise
-    const int mode = negate ? kGenNegPhi : kGenPhi;
-    if (r.sRow) {
-      float* sbuf = reinterpret_cast<float*>(w + r.offS);
-      const long pstride = r.sRow * pr.B;
-      MOL_TRY_HIP(launch_dots_mfma_gather(pr, uniq, nu, CT, CT, sbuf, pstride, r.sRow, st), "rerank dots");
-      MOL_TIMED_LAUNCH(timed_op, st,
-                       launch_phi_mfma(pr, mode, nullptr, 0, CT, uniq, nu, CT, sbuf, pstride, r.sRow, nullptr, 0, A,
-                                       r.s.strideA, st),
-                       "rerank score");
-    } else {
-      MOL_TIMED_LAUNCH(timed_op, st,
-                       launch_mol_f32(pr, mode, nullptr, 0, CT, uniq, nu, CT, nullptr, 0, A, r.s.strideA, st),
-                       "rerank score");
-    }
-    if ((rc = reduce_rows(r.s, w, CT, fin, k, st))) return rc;
+    // pair-wise gating kernel
+    float* sbuf = reinterpret_cast<float*>(w + r.offS);
+    const long pstride = r.sRow * pr.B;
+    MOL_TRY_HIP(launch_dots_mfma_gather(pr, uniq, nu, CT, CT, sbuf, pstride, r.sRow, st), "rerank dots");
+    MOL_TIMED_LAUNCH(timed_op, st,
+                     launch_phi_mfma(pr, mode, nullptr, 0, CT, uniq, nu, CT, sbuf, pstride, r.sRow, phi, r.ld, A,
+                                     r.s.strideA, st),
+                     "rerank score");
+  } else {
+    MOL_TIMED_LAUNCH(timed_op, st,
+                     launch_mol_f32(pr, mode, nullptr, 0, CT, uniq, nu, CT, phi, r.ld, A, r.s.strideA, st),
+                     "rerank score");
   }
+  if (phi) {
+    DenseRows d;
+    d.phi = phi;
+    d.phi_stride = r.ld;
+    d.L = CT;
+    d.row_len = nu;
+    d.ids = uniq;
+    d.ids_stride = CT;
+    d.sign = negate ? -1.f : 1.f;
+    MOL_TRY_HIP(launch_topk_dense(d, pr.B, k, out_score, out_idx, st), "rerank top-k");
+    return MOL_OK;
+  }
+  uint64_t* fin = reinterpret_cast<uint64_t*>(w + r.offFinal);
+  if ((rc = reduce_rows(r.s, w, CT, fin, k, st))) return rc;
   MOL_TRY_HIP(launch_decode(fin, k, pr.B, k, out_score, out_idx, st), "decode");
-  if (out_n_unique)
-    MOL_TRY_HIP(hipMemcpyAsync(out_n_unique, nu, sizeof(int32_t) * pr.B, hipMemcpyDeviceToDevice, st),
-                "copy n_unique");
   return MOL_OK;
 }
 

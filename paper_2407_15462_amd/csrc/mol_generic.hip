@@ -132,7 +132,8 @@ constexpr int kDedupBins = 1024;
 __global__ __launch_bounds__(1024) void k_dedup(const int32_t* __restrict__ cand, int C,
                                                 const int32_t* __restrict__ cand2, int C2, int N,
                                                 int cap_log2, int bin_shift, int32_t* __restrict__ uniq,
-                                                int32_t* __restrict__ n_unique) {
+                                                int32_t* __restrict__ n_unique,
+                                                int32_t* __restrict__ n_out) {
   extern __shared__ int32_t table[];     // cap slots, then kDedupBins bin counters
   __shared__ int count;
   __shared__ int wsum[1024 / 64];
@@ -145,19 +146,29 @@ __global__ __launch_bounds__(1024) void k_dedup(const int32_t* __restrict__ cand
   if (tid == 0) count = 0;
   __syncthreads();
   const int CT = C + C2;                 // both sets; uniq rows hold CT slots
-  for (int i = tid; i < CT; i += blockDim.x) {
-    const int32_t id = i < C ? cand[b * C + i] : cand2[b * C2 + (i - C)];
-    if (id < 0 || id >= N) continue;
-    uint32_t h = (static_cast<uint32_t>(id) * 0x9E3779B1u) >> (32 - cap_log2);
-    for (int probe = 0; probe < cap; ++probe) {
-      const int32_t prev = atomicCAS(&table[h], -1, id);
-      if (prev == -1) {
-        atomicAdd(&count, 1);
-        atomicAdd(&bins[id >> bin_shift], 1);
-        break;
+  constexpr int U = 8;                   // candidates a thread has in flight
+  for (int i0 = tid; i0 < CT; i0 += U * kDedupBins) {
+    int32_t ids[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + u * kDedupBins, CT - 1);
+      ids[u] = i < C ? cand[b * C + i] : cand2[b * C2 + (i - C)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t id = i0 + u * kDedupBins < CT ? ids[u] : -1;
+      if (id < 0 || id >= N) continue;
+      uint32_t h = (static_cast<uint32_t>(id) * 0x9E3779B1u) >> (32 - cap_log2);
+      for (int probe = 0; probe < cap; ++probe) {
+        const int32_t prev = atomicCAS(&table[h], -1, id);
+        if (prev == -1) {
+          atomicAdd(&count, 1);
+          atomicAdd(&bins[id >> bin_shift], 1);
+          break;
+        }
+        if (prev == id) break;
+        h = (h + 1) & (cap - 1);
       }
-      if (prev == id) break;
-      h = (h + 1) & (cap - 1);
     }
   }
   __syncthreads();
@@ -179,7 +190,10 @@ __global__ __launch_bounds__(1024) void k_dedup(const int32_t* __restrict__ cand
     const int32_t id = table[s];
     if (id >= 0) uniq[b * CT + atomicAdd(&bins[id >> bin_shift], 1)] = id;
   }
-  if (tid == 0) n_unique[b] = count;
+  if (tid == 0) {
+    n_unique[b] = count;
+    if (n_out) n_out[b] = count;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -383,7 +397,7 @@ int dedup_cap_log2(int C) {
 }
 
 hipError_t launch_dedup(const int32_t* cand, int C, const int32_t* cand2, int C2, int B, int N,
-                        int32_t* uniq, int32_t* n_unique, hipStream_t st) {
+                        int32_t* uniq, int32_t* n_unique, int32_t* n_out, hipStream_t st) {
   const int lg = dedup_cap_log2(C + C2);
   const size_t smem = (sizeof(int32_t) << lg) + sizeof(int32_t) * kDedupBins;
   int bin_shift = 0;                     // (N - 1) >> bin_shift < kDedupBins
@@ -395,7 +409,7 @@ hipError_t launch_dedup(const int32_t* cand, int C, const int32_t* cand2, int C2
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_dedup, dim3(B), dim3(kDedupBins), smem, st, cand, C, cand2, C2, N, lg, bin_shift, uniq,
-                     n_unique);
+                     n_unique, n_out);
   return hipGetLastError();
 }
 

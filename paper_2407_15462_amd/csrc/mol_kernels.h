@@ -109,8 +109,9 @@ hipError_t launch_copy_rows(const uint64_t* src, long src_stride, int rows, int 
 
 // Approximate path helpers.
 int dedup_cap_log2(int C);
+// n_out: NULL, or a second place for the counts
 hipError_t launch_dedup(const int32_t* cand, int C, const int32_t* cand2, int C2, int B, int N,
-                        int32_t* uniq, int32_t* n_unique, hipStream_t st);
+                        int32_t* uniq, int32_t* n_unique, int32_t* n_out, hipStream_t st);
 hipError_t launch_gap_bound(int B, int P, int m, const float* dots, int k, const float* scores,
                             float* out_S, float* out_SK, float* out_bound, float* out_looser,
                             hipStream_t st);
@@ -203,10 +204,10 @@ hipError_t launch_per_embd_select(const DevProb& pr, int kp, const PerEmbdGrid& 
 namespace mol {
 
 // Fused MFMA rerank of deduplicated candidates (same shapes as the fused scorer).
-bool rerank_supported(const DevProb& pr, int k);
+bool rerank_supported(const DevProb& pr);
 int rerank_chunk(int B, int C);
-// negate: rank by -phi (the smallest scores first)
-hipError_t launch_rerank(const DevProb& pr, const int32_t* uniq, const int32_t* n_unique, int C, int k,
-                         bool negate, uint64_t* partial, hipStream_t st);
+// phi of candidate i < n_unique[b] of query b to phi[b * phi_stride + i]
+hipError_t launch_rerank(const DevProb& pr, const int32_t* uniq, const int32_t* n_unique, int C, float* phi,
+                         long phi_stride, hipStream_t st);
 
 }  // namespace mol

@@ -10,8 +10,10 @@
 // GEMM1 forms the 8 x 16 dot products of the query's components with the
 // items' components in rows 2 pq of the 16x16x32 tile (the odd rows are
 // zero), which leaves them in the run layout of mol_tile.h, and the shared
-// MFMA epilogue evaluates the gating MLP, softmax and phi.  A running
-// top-k per wave is merged across chunks afterwards by segmented sorts.
+// MFMA epilogue evaluates the gating MLP, softmax and phi.  The scores are
+// stored densely, one row per query, and ranked by k_topk_dense (running lists
+// per wave and their merge: 32 x 14,800 candidates 132 -> 117 us, 1024 x 8192
+// 1323 -> 1376 us).
 #include "mol_tile.h"
 
 namespace mol {
@@ -20,16 +22,14 @@ using namespace tile;
 
 namespace {
 constexpr int kWaves = 4;
-constexpr int kTopkRegion = WaveTopk::kList + WaveTopk::kStage;
 }  // namespace
 
-template <int PX, int D, int H, bool NEG, bool X2>
+template <int PX, int D, int H, bool X2>
 __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
     DevProb pr, const int32_t* __restrict__ uniq, const int32_t* __restrict__ n_unique, int C,
-    int k, int chunk, int nchunks, uint64_t* __restrict__ partial) {
+    int chunk, int nchunks, float* __restrict__ phi_out, long phi_stride) {
   using Mlp = MolMlp<PX, H, X2>;   // X2: the two-term gating chain
   constexpr int P = 8 * PX, RUN = 2 * PX, KD = D / 32, PT = P / 16;
-  __shared__ uint64_t sTop[kWaves * kTopkRegion];
   // the wave's gather buffer: block (px, kk) of 1 KB holds lane i's 16 bytes
   // of component px, K block kk at byte 16 i (a direct global -> LDS copy)
   extern __shared__ __attribute__((aligned(16))) unsigned char sGather[];
@@ -47,8 +47,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
   const bf16_t* Q = static_cast<const bf16_t*>(pr.Q);
   const int32_t* ids = uniq + static_cast<long>(b) * C;
 
-  WaveTopk top;
-  top.init(sTop + wave * kTopkRegion, k, lane);
+  float* row = phi_out + b * phi_stride;
   Mlp mlp;
   mlp.load(pr, c, g);
   // log2(e) (a_q + b2) of query b at the lane's p = base(g) + 4 pt + i
@@ -92,11 +91,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
   for (int s0 = i0; s0 < i1; s0 += 16) {
     const int pos = s0 + c;
     const bool ok = pos < i1;
-    const int item = item_n;
-    // this step's copies have landed (only the younger id load may be
-    // outstanding); read the operands, then refill the buffer
+    // this step's copies have landed (the younger a_x and id loads, and the
+    // last step's store, may be outstanding); read the operands, then refill
+    // the buffer
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(1));
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(PT + 1));
     asm volatile("" ::: "memory");
     uint4 xop[PX][KD];
 #pragma unroll
@@ -127,15 +126,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
     for (int mu = 0; mu < RUN; ++mu) s[0][mu] = acc1[mu % PX][2 * (mu / PX)];
     float phi[1];
     mlp.template phi<1>(s, c0, phi);
-    top.offer_score(NEG ? -phi[0] : phi[0], item, g == 0 && ok, lane);
+    if (g == 0 && ok) row[pos] = phi[0];
   }
-  top.flush(lane);
-  uint64_t* dst = partial + (static_cast<long>(b) * nchunks + j) * k;
-  for (int i = lane; i < k; i += 64) dst[i] = top.reg[i];
 }
 
 // ---------------------------------------------------------------------------
-bool rerank_supported(const DevProb& pr, int k) { return fused_supported(pr, k); }
+bool rerank_supported(const DevProb& pr) { return fused_supported(pr, 1); }
 
 // Candidates per wave: the largest of 4096, 2048, 1024, 512 and 256 that
 // still gives at least one round of resident waves (two 4-wave workgroups
@@ -152,46 +148,37 @@ int rerank_chunk(int B, int C) {
   return 256;
 }
 
-template <int PX, int D, int H, bool NEG, bool X2>
+template <int PX, int D, int H, bool X2>
 static hipError_t launch_rerank_x(const DevProb& pr, dim3 grid, const int32_t* uniq, const int32_t* n_unique,
-                                  int C, int k, int chunk, int nchunks, uint64_t* partial, hipStream_t st) {
+                                  int C, int chunk, int nchunks, float* phi, long phi_stride, hipStream_t st) {
   constexpr int kGather = kWaves * PX * (D / 32) * 1024;   // the waves' gather buffers
-  auto kern = &k_mol_rerank<PX, D, H, NEG, X2>;
+  auto kern = &k_mol_rerank<PX, D, H, X2>;
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kGather);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), kGather, st, pr, uniq, n_unique, C, k, chunk, nchunks, partial);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), kGather, st, pr, uniq, n_unique, C, chunk, nchunks, phi,
+                     phi_stride);
   return hipGetLastError();
 }
 
-template <int PX, int D, int H, bool NEG>
+template <int PX, int D, int H>
 static hipError_t launch_rerank_one(const DevProb& pr, dim3 grid, const int32_t* uniq, const int32_t* n_unique,
-                                    int C, int k, int chunk, int nchunks, uint64_t* partial, hipStream_t st) {
-  if (pr.flags & MOL_FLAG_BF16X2_GATING)
-    return launch_rerank_x<PX, D, H, NEG, true>(pr, grid, uniq, n_unique, C, k, chunk, nchunks, partial, st);
-  return launch_rerank_x<PX, D, H, NEG, false>(pr, grid, uniq, n_unique, C, k, chunk, nchunks, partial, st);
+                                    int C, int chunk, int nchunks, float* phi, long phi_stride, hipStream_t st) {
+  auto f = pr.flags & MOL_FLAG_BF16X2_GATING ? &launch_rerank_x<PX, D, H, true> : &launch_rerank_x<PX, D, H, false>;
+  return f(pr, grid, uniq, n_unique, C, chunk, nchunks, phi, phi_stride, st);
 }
 
-template <bool NEG>
-static hipError_t launch_rerank_t(const DevProb& pr, dim3 grid, const int32_t* uniq, const int32_t* n_unique,
-                                  int C, int k, int chunk, int nchunks, uint64_t* partial, hipStream_t st) {
-  if (pr.Px == 8 && pr.d == 32)
-    return launch_rerank_one<8, 32, 64, NEG>(pr, grid, uniq, n_unique, C, k, chunk, nchunks, partial, st);
-  if (pr.Px == 8)
-    return launch_rerank_one<8, 64, 64, NEG>(pr, grid, uniq, n_unique, C, k, chunk, nchunks, partial, st);
-  if (pr.d == 128)
-    return launch_rerank_one<4, 128, 128, NEG>(pr, grid, uniq, n_unique, C, k, chunk, nchunks, partial, st);
-  return launch_rerank_one<4, 64, 64, NEG>(pr, grid, uniq, n_unique, C, k, chunk, nchunks, partial, st);
-}
-
-hipError_t launch_rerank(const DevProb& pr, const int32_t* uniq, const int32_t* n_unique, int C, int k,
-                         bool negate, uint64_t* partial, hipStream_t st) {
+hipError_t launch_rerank(const DevProb& pr, const int32_t* uniq, const int32_t* n_unique, int C, float* phi,
+                         long phi_stride, hipStream_t st) {
   const int chunk = rerank_chunk(pr.B, C);
   const int nchunks = (C + chunk - 1) / chunk;
   const long waves = static_cast<long>(pr.B) * nchunks;
   const dim3 grid(static_cast<unsigned>((waves + kWaves - 1) / kWaves));
-  return negate ? launch_rerank_t<true>(pr, grid, uniq, n_unique, C, k, chunk, nchunks, partial, st)
-                : launch_rerank_t<false>(pr, grid, uniq, n_unique, C, k, chunk, nchunks, partial, st);
+  auto f = pr.Px == 8 && pr.d == 32 ? &launch_rerank_one<8, 32, 64>
+           : pr.Px == 8             ? &launch_rerank_one<8, 64, 64>
+           : pr.d == 128            ? &launch_rerank_one<4, 128, 128>
+                                    : &launch_rerank_one<4, 64, 64>;
+  return f(pr, grid, uniq, n_unique, C, chunk, nchunks, phi, phi_stride, st);
 }
 
 }  // namespace mol

@@ -41,7 +41,8 @@ __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float
 // are ranked by sign * phi, and that is what is written; skip_neg_inf: a score
 // of -inf marks an excluded column.  Rows with fewer than k items are padded
 // with (-inf, -1).
-__global__ __launch_bounds__(kTopThreads) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P, long p_rows, int L_all,
+// (two workgroups a CU: at most 64 registers)
+__global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P, long p_rows, int L_all,
                                                            const int32_t* __restrict__ row_len,
                                                            const float* __restrict__ bmax, long bmax_stride, int SL,
                                                            const int32_t* __restrict__ ids, long ids_stride, int k,
