@@ -225,6 +225,7 @@ struct DensePlan {
   long sRow = 0;                   // dots buffer row (0: no buffer)
   int T = 0;                       // items per dots tile
   bool fused = false;              // scored by the fused kernels
+  bool dphi = false;               // scored by the dots + gating kernel
   FusedDenseGrid g;
   size_t offPhi = 0, offBmax = 0, offS = 0, offRedo = 0, bytes = 0;
 };
@@ -255,7 +256,8 @@ DensePlan plan_dense(const DevProb& pr, int k, DenseBy by) {
     f.offBmax = off;
     off = align_up(off + 4ul * pr.B * bucket_row(pr.N, f.g.SL));
   }
-  if (by == kByPairs && dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
+  f.dphi = by == kByPairs && dots_phi_supported(pr);
+  if (by == kByPairs && !f.dphi && dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
     // dots tiles of at most 512 MB, whole 128-item GEMM tiles
     const long T = std::max(1024l, std::min<long>(pr.N, (512l << 20) / (4l * pr.P * pr.B) / 128 * 128));
     const long sRow = dots_buffer_row(static_cast<int>(T));
@@ -619,7 +621,10 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
                      launch_fused_dense(pr, f.g, 0, pr.N, phi, f.ld, bmax, bstride,
                                         reinterpret_cast<int*>(w + f.offRedo), st),
                      "fused MoL scores");
-  for (long n0 = 0; n0 < pr.N && !f.fused; n0 += f.T) {
+  if (f.dphi)
+    MOL_TIMED_LAUNCH(timed_op, st, launch_dots_phi(pr, mode == kGenBounded ? bound : nullptr, phi, f.ld, bmax, bstride, st),
+                     "dots and gating");
+  for (long n0 = 0; n0 < pr.N && !f.fused && !f.dphi; n0 += f.T) {
     const int nt = static_cast<int>(std::min<long>(f.T, pr.N - n0));
     MOL_TIMED_LAUNCH(timed_op, st,
                      pairwise_score(pr, sbuf, f.sRow, mode, bound, static_cast<int>(n0), nt, phi + n0, f.ld, nullptr,
@@ -634,7 +639,7 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
   r.bmax = bmax;
   r.bmax_stride = bstride;
   r.SL = f.g.SL;
-  if (bmax && !f.fused)
+  if (bmax && !f.fused && !f.dphi)
     MOL_TRY_HIP(launch_bucket_max(phi, f.ld, pr.B, pr.N, 1.f, bmax, bstride, st), "bucket maxima");
   MOL_TRY_HIP(launch_topk_dense(r, pr.B, k, out_score, out_idx, st), "dense top-k");
   return MOL_OK;

@@ -84,6 +84,14 @@ hipError_t launch_phi_mfma(const DevProb& pr, int mode, const float* bound, int 
                            const float* sbuf, long s_pstride, long s_bstride, float* phi, long phi_stride,
                            uint64_t* keys, long key_stride, hipStream_t st);
 
+// Dots and gating in one kernel (bf16, P_x = 4, P_q 1, 2 or 4, d a multiple of
+// 32, H <= 128): dense scores of the whole corpus, bit-identical to the two
+// kernels above.  bound: NULL, or [B] (kGenBounded: excluded items get -inf);
+// bmax: NULL, or bucket maxima (DenseRows, SL = 1).
+bool dots_phi_supported(const DevProb& pr);
+hipError_t launch_dots_phi(const DevProb& pr, const float* bound, float* phi, long phi_stride, float* bmax,
+                           long bmax_stride, hipStream_t st);
+
 // Selection machinery over 64-bit sort keys.  gate: NULL, or a device flag
 // read at the start of every workgroup; the launch does nothing while it is
 // zero (the second of two alternative paths, chosen on the device).

@@ -116,3 +116,32 @@ def test_small_batch_lists(B, Px, d, N, kp, ties):
         got = torch.gather(s, 1, ids[b].long())
         assert (dots[b].double() - got).abs().max() <= tol and (got - want).abs().max() <= 2 * tol
         assert _ordered(dots[b], ids[b])
+
+
+# dots and gating in one kernel (P_x = 4): every vector tile (32, 64, 128, and
+# more than one), ragged items, one to many K steps, padded hidden units, with
+# and without side logits of aligned rows; the pair-wise kernels (the
+# allocation-free form takes them) give the same bits
+@pytest.mark.parametrize("B,Pq,d,H,N,k", [
+    (1, 4, 768, 64, 20011, 100), (8, 4, 768, 64, 70, 50), (9, 4, 64, 64, 3001, 100), (32, 4, 768, 64, 16449, 128),
+    (33, 4, 96, 48, 2000, 64), (75, 4, 32, 32, 1025, 100), (17, 2, 128, 100, 2100, 33), (40, 1, 64, 128, 999, 10),
+    (3, 2, 1024, 17, 65, 65),
+])
+def test_dots_phi_equals_pairwise_kernels(B, Pq, d, H, N, k):
+    log(f"[dots_phi] B={B} P={Pq}x4 d={d} H={H} N={N} k={k}")
+    spec = dataclasses.replace(W["exact_32k"], name="pairwise", B=B, N=N, Pq=Pq, Px=4, d=d, H=H,
+                               clusters=max(1, N // 100))
+    inp = cuda_inputs(spec, seed=N)
+    for flags in (0, mol.MOL_FLAG_BF16X2_GATING):
+        prob = mol.Problem.from_inputs(inp, flags=flags)
+        s, i = mol.topk_exact(prob, k)
+        bs, bi = mol.topk_exact_bounded(prob, k, s[:, k - 1].contiguous())
+        every = torch.arange(N, dtype=torch.int32, device="cuda").repeat(B, 1)
+        if N <= 16384:                                       # the two kernels, through the rerank of all items
+            rs, ri, _ = mol.rerank(prob, every, k)
+            assert torch.equal(rs, s) and torch.equal(ri, i)
+        assert torch.equal(bs, s) and torch.equal(bi, i)
+        f32 = mol.score(mol.Problem.from_inputs(inp, flags=mol.MOL_FLAG_F32_GATING))
+        want = torch.topk(f32, k, dim=1).values
+        got = torch.gather(f32, 1, i.long())
+        assert (s - got).abs().max() <= 2e-5 and (got - want).abs().max() <= 4e-5
