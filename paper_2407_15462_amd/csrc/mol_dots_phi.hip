@@ -109,6 +109,11 @@ __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const floa
   if (nk > 1) stage(1);
   for (int i = tid; i < nq * P; i += 64 * S::W) sAq[i] = pr.a_q[static_cast<long>(b0) * P + i];
 
+  // the gating operands, whose reads the K loop covers
+  const int ci = lane & 15, g = lane >> 4;
+  Mlp mlp;
+  mlp.load_padded(pr, ci, g);
+
   f32x16_t acc[PX][NJ];
 #pragma unroll
   for (int px = 0; px < PX; ++px)
@@ -143,9 +148,6 @@ __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const floa
   }
   __syncthreads();                                      // the ring becomes the waves' s regions
 
-  const int ci = lane & 15, g = lane >> 4;
-  Mlp mlp;
-  mlp.load_padded(pr, ci, g);
   float b2v[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) b2v[e] = kLog2e * pr.b2[min(4 * g + e, P - 1)];
@@ -157,10 +159,8 @@ __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const floa
   for (int rd = 0; rd < 2; ++rd) {
     const int item = i0 + 32 * wm + 16 * rd + ci;
     const bool live = item < N;
-    const float* axr = pr.a_x + static_cast<long>(min(item, N - 1)) * P + 4 * gp;
-    float ax[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) ax[e] = axr[e];
+    float ax[4];                                        // (any alignment)
+    __builtin_memcpy(ax, pr.a_x + static_cast<long>(min(item, N - 1)) * P + 4 * gp, sizeof ax);
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       // lane (c, h) holds vector c's items 8 k + 4 h + i: those of this round
@@ -175,20 +175,37 @@ __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const floa
         }
       wave_lds_sync();
       const int q0 = (NJ * wn + j) * qpb;               // first query of the block, within the tile
+      // the next pair's reads go out before a pair's chain, which covers their
+      // latency
+      struct Pair {
+        float s[2][4];
+        float4 aq[2];
+      };
+      auto fetch = [&](int q, Pair& p) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int qs = min(q, qpb - 2) + u;
+          const float* sr = sw + (qs * Pq + gp) * PX * S::RS + ci;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p.s[u][e] = sr[e * S::RS];
+          p.aq[u] = *reinterpret_cast<const float4*>(sAq + min(q0 + qs, nq - 1) * P + 4 * gp);
+        }
+      };
+      Pair nx;
+      fetch(0, nx);
       for (int q = 0; q < qpb && q0 + q < nq; q += 2) {
+        const Pair cu = nx;
+        fetch(q + 2, nx);
         float s[2][4];
         f32x4_t c0[2][1];
         bool keep[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int ql = min(q0 + q + u, nq - 1);       // (a query past the batch: computed, never stored)
-          const float* sr = sw + ((q + u) * Pq + gp) * PX * S::RS + ci;
-          const float* aq = sAq + ql * P + 4 * gp;
+        for (int u = 0; u < 2; ++u) {                   // (a query past the batch: computed, never stored)
+          const float aq[4] = {cu.aq[u].x, cu.aq[u].y, cu.aq[u].z, cu.aq[u].w};
           float m = -__builtin_inff(), mabs = 0.f;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float v = sr[e * S::RS];
-            s[u][e] = live && comp ? v : 0.f;
+            s[u][e] = live && comp ? cu.s[u][e] : 0.f;
             c0[u][0][e] = comp ? fmaf(kLog2e, ax[e] + aq[e], b2v[e]) : -__builtin_inff();
             if (BOUNDED && comp) {
               m = fmaxf(m, s[u][e]);
@@ -196,7 +213,8 @@ __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const floa
             }
           }
           keep[u] = live;
-          if (BOUNDED) keep[u] = live && !(max_groups(m) + bound_margin(max_groups(mabs)) < bound[b0 + ql]);
+          if (BOUNDED)
+            keep[u] = live && !(max_groups(m) + bound_margin(max_groups(mabs)) < bound[b0 + min(q0 + q + u, nq - 1)]);
         }
         // out[u] is valid in rows 2 u and 2 u + 1
         float out[2] = {0.f, 0.f};
@@ -207,9 +225,7 @@ __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const floa
         const bool mine = (g & 1) == 0 && ql < nq;
         if (mine && live) phi[(b0 + ql) * phi_stride + item] = v;
         if (bmax) {
-          float m = v;
-#pragma unroll
-          for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 16));
+          const float m = row16_max(v);
           if (mine && ci == 0) {
             float* mx = sMax + wm * S::TV + ql;
             *mx = rd == 0 ? m : fmaxf(*mx, m);
@@ -252,11 +268,16 @@ static hipError_t launch_dots_phi_t(const DevProb& pr, const float* bound, float
 template <int HV>
 static hipError_t launch_dots_phi_h(const DevProb& pr, const float* bound, float* phi, long phi_stride, float* bmax,
                                     long bmax_stride, hipStream_t st) {
-  // the smallest tile that holds the batch's vectors, at most 128
+  // the smallest tile that holds the batch's vectors, at most 128 (64 with
+  // H = 128, whose operands leave no registers for two vector blocks a wave)
   const int nvec = pr.B * pr.Pq;
   if (nvec <= 32) return launch_dots_phi_t<1, 1, HV>(pr, bound, phi, phi_stride, bmax, bmax_stride, st);
-  if (nvec <= 64) return launch_dots_phi_t<2, 1, HV>(pr, bound, phi, phi_stride, bmax, bmax_stride, st);
-  return launch_dots_phi_t<2, 2, HV>(pr, bound, phi, phi_stride, bmax, bmax_stride, st);
+  if constexpr (HV > 64) {
+    return launch_dots_phi_t<1, 2, HV>(pr, bound, phi, phi_stride, bmax, bmax_stride, st);
+  } else {
+    if (nvec <= 64) return launch_dots_phi_t<2, 1, HV>(pr, bound, phi, phi_stride, bmax, bmax_stride, st);
+    return launch_dots_phi_t<2, 2, HV>(pr, bound, phi, phi_stride, bmax, bmax_stride, st);
+  }
 }
 
 hipError_t launch_dots_phi(const DevProb& pr, const float* bound, float* phi, long phi_stride, float* bmax,

@@ -115,13 +115,6 @@ __device__ __forceinline__ void wg_coords(int g, int R, int G, int& r, int& qg) 
 // bmax (dense forms): NULL, or [B][bmax_stride] maxima of phi over buckets of
 // 64 items: bucket SL i + s holds the 16-item runs 4 SL i + s + SL j, j < 4
 // (range_len is a multiple of 64 SL then).
-// maximum over the 16 lanes of a row, in all of them
-__device__ __forceinline__ float row16_max(float v) {
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 16));
-  return v;
-}
-
 template <int PX, int D, int H, int EPI, bool X2, int SL>
 __global__ __launch_bounds__(64 * kWaves, 1) void k_mol_fused(
     DevProb pr, int k, int R, int range_len, int G, int n_begin, int n_end,

@@ -83,6 +83,19 @@ __device__ __forceinline__ float max_groups(float x) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Maximum over the 16 lanes of a row, in all of them (row rotations in the
+// vector ALU: no LDS round trips).
+template <int ROR>
+__device__ __forceinline__ float row_ror(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROR, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row16_max(float v) {
+  v = fmaxf(v, row_ror<8>(v));
+  v = fmaxf(v, row_ror<4>(v));
+  v = fmaxf(v, row_ror<2>(v));
+  return fmaxf(v, row_ror<1>(v));
+}
+
 // Margin of the bound phi <= max_p s_p under float32 rounding.  phi is
 // formed as sum_p w_p s_p / sum_p w_p with w_p >= 0: each of the two sums of
 // at most 64 terms is off by under 64 units of 2^-24 relative to
@@ -725,6 +738,34 @@ struct MolMlp16 {   // X2: the two-term chain, as in MolMlp
     const bf16_t* W1 = static_cast<const bf16_t*>(pr.W1);
     const bf16_t* W2 = static_cast<const bf16_t*>(pr.W2);
     const int Pr = pr.P, Hr = pr.H;
+    if (Pr == 16 && Hr == H) {   // nothing padded: whole operand rows a load
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        const uint2 w = load_bf16x4(W1 + (16 * jt + c) * 16 + 4 * g);
+        w1op[jt] = X2 ? w
+                      : make_uint2(neg_bf16_to_f16_bits(static_cast<bf16_t>(w.x & 0xffffu), kLog2e) |
+                                       (neg_bf16_to_f16_bits(static_cast<bf16_t>(w.x >> 16), kLog2e) << 16),
+                                   neg_bf16_to_f16_bits(static_cast<bf16_t>(w.y & 0xffffu), kLog2e) |
+                                       (neg_bf16_to_f16_bits(static_cast<bf16_t>(w.y >> 16), kLog2e) << 16));
+      }
+#pragma unroll
+      for (int m = 0; m < KH; ++m) {
+        const bf16_t* src = W2 + c * H + 32 * m + 4 * g;
+        const uint2 lo = load_bf16x4(src), hi = load_bf16x4(src + 16);
+        uint32_t w[4] = {lo.x, lo.y, hi.x, hi.y};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          w[e] = X2 ? w[e] ^ 0x80008000u
+                    : neg_bf16_to_f16_bits(static_cast<bf16_t>(w[e] & 0xffffu), 1.f) |
+                          (neg_bf16_to_f16_bits(static_cast<bf16_t>(w[e] >> 16), 1.f) << 16);
+        w2op[m] = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b1acc[jt][i] = -kLog2e * pr.b1[16 * jt + 4 * g + i];
+      return;
+    }
     // unconditional reads from clamped indices, masked afterwards
     auto w1 = [&](int j, int p) -> uint32_t {
       const bf16_t w = W1[min(j, Hr - 1) * Pr + min(p, Pr - 1)];

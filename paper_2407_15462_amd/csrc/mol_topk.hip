@@ -17,7 +17,7 @@
 // rows of 109,739 scores 13 us plus 6 us for the maxima (chunked radix
 // selection, segmented sort and decode of 64-bit keys: 52 us; straight from the
 // rows 61 us), of one row of 2^20 19 us.
-#include "mol_kernels.h"
+#include "mol_tile.h"
 
 namespace mol {
 
@@ -377,8 +377,7 @@ __global__ __launch_bounds__(256) void k_bucket_max(const float* __restrict__ ph
     if (col + 2 < L) m = fmaxf(m, sign * v.z);
     if (col + 3 < L) m = fmaxf(m, sign * v.w);
   }
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 16));
+  m = tile::row16_max(m);
   if ((threadIdx.x & 15) == 0 && col < L) bmax[row * bmax_stride + (col >> 6)] = sign * m;
 }
 
