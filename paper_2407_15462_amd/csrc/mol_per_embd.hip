@@ -73,15 +73,16 @@ __device__ __forceinline__ f32x16_t mfma32_bf16(uint4 a, uint4 b, f32x16_t c) {
                                                  __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// MODE: the scan's form (ScanMode)
-template <int D, int KL, int MODE, bool SMALL>
+// MODE: the scan's form (ScanMode); NBP: vector blocks per wave of the pruned
+// pass (0: nb_pick)
+template <int D, int KL, int MODE, bool SMALL, int NBP = 0>
 struct EmbdShape {
   static constexpr bool SCAN2 = MODE == kScanThreshold;
   // per-lane key slots of the LDS staging, per vector block, of the forms
   // that append to key buffers
   static constexpr int HITS = MODE == kScanPruned ? 2 : MODE == kScanAppend ? 8 : 0;
   static constexpr int KD = D / 16;                    // K blocks (32x32x16)
-  static constexpr int NB = nb_pick(D, SCAN2, SMALL);
+  static constexpr int NB = NBP > 0 ? NBP : nb_pick(D, SCAN2, SMALL);
   static constexpr int VEC_WAVE = 32 * NB;             // query vectors per wave
   static constexpr int WAVES = waves_for(KL);
   static constexpr int VEC_WG = WAVES * VEC_WAVE;
@@ -132,7 +133,7 @@ struct PrunedArgs {
 // pa: the pruned pass's work list and outputs.  In the pruned pass R,
 // range_len, bucket_tiles and nbk are the bucket scan's, whose buckets are
 // the pass's work units.
-template <int D, int KL, int MODE, bool SMALL>
+template <int D, int KL, int MODE, bool SMALL, int NBP>
 __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
     DevProb pr, int kp, int R, int range_len, int G, int bucket_tiles, int nbk,
     float* __restrict__ bmax, const float* __restrict__ thr, uint64_t* __restrict__ lists,
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(64 * waves_for(KL), 1) void k_topk_per_embd(
   constexpr bool SCAN2 = MODE == kScanThreshold;
   constexpr bool PRUNED = MODE == kScanPruned;
   constexpr bool APPEND = PRUNED || MODE == kScanAppend;   // keys reaching T go to the lists' key buffers
-  using S = EmbdShape<D, KL, MODE, SMALL>;
+  using S = EmbdShape<D, KL, MODE, SMALL, NBP>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* sX = smem;
   uint64_t* sSort = reinterpret_cast<uint64_t*>(smem + S::LDS_X);
@@ -829,7 +830,6 @@ void per_embd_grid(const DevProb& pr, int kp, PerEmbdGrid& g) {
   const bool small = per_embd_small(pr, kp);
   const int tps = stage_items(pr.d, KL, small) / 32;
   g.vec_wg_pruned = waves_for(KL) * 32 * nb_pick(pr.d, false, false);
-  g.CH = (nvec + g.vec_wg_pruned - 1) / g.vec_wg_pruned;
   g.key_cap = 2 * KL;
   // buckets per list.  The full-scan form: 1024 for k' <= 128 (about
   // k'^2 / 2048 <= 8 collisions among the k' largest items, so the bound
@@ -859,6 +859,15 @@ void per_embd_grid(const DevProb& pr, int kp, PerEmbdGrid& g) {
   // 2 k' buckets: at most about 1.4 k' keys reach T, the buffers hold 2 KL
   g.append = KL <= 256 && small && g.s1.R * g.nbk >= 2 * kp;
   g.groups = pr.Px * g.s1.R * g.nbk;
+  // vector blocks per wave of the pruned pass: the fewest whose slots hold a
+  // bucket's hot vectors with a quarter to spare (a list has about k' +
+  // k'^2 / (2 B) of its B buckets hot).  Empty blocks cost full matrix and
+  // vector work: 512 vectors, k' = 20, 4 x 100,003 items: 77 us with four
+  // blocks, 43 us with one.
+  const long nbuckets = static_cast<long>(g.s1.R) * g.nbk;
+  const double hot = static_cast<double>(nvec) * kp * (1.0 + 0.5 * kp / nbuckets) / nbuckets;
+  while (g.vec_wg_pruned > 32 * waves_for(KL) && 1.25 * hot <= g.vec_wg_pruned / 2) g.vec_wg_pruned /= 2;
+  g.CH = (nvec + g.vec_wg_pruned - 1) / g.vec_wg_pruned;
 }
 
 // compute units of the current device (the pruned pass runs one persistent
@@ -871,12 +880,12 @@ static int resident_cus() {
   return ncu;
 }
 
-template <int D, int KL, int MODE, bool SMALL>
+template <int D, int KL, int MODE, bool SMALL, int NBP = 0>
 static hipError_t launch_pe_t(const DevProb& pr, int kp, const PerEmbdGrid& g, const PerEmbdBufs& b,
                               const uint32_t* gate, hipStream_t st) {
-  using S = EmbdShape<D, KL, MODE, SMALL>;
+  using S = EmbdShape<D, KL, MODE, SMALL, NBP>;
   const PerEmbdGrid::Scan& sc = MODE == kScanThreshold ? g.s2 : g.s1;
-  auto kern = &k_topk_per_embd<D, KL, MODE, SMALL>;
+  auto kern = &k_topk_per_embd<D, KL, MODE, SMALL, NBP>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_TOTAL);
   if (e != hipSuccess) return e;
@@ -931,7 +940,10 @@ static hipError_t launch_pe_s(const DevProb& pr, int kp, const PerEmbdGrid& g, c
                          g.vec_wg_pruned, g.CH, b.hot_v, b.hot_n, b.work, b.ctl + rows + 1);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
-      e = launch_pe_t<D, KL, kScanPruned, false>(pr, kp, g, b, nullptr, st);
+      const int nbp = g.vec_wg_pruned / (32 * waves_for(KL));
+      if (nbp == 1) e = launch_pe_t<D, KL, kScanPruned, false, 1>(pr, kp, g, b, nullptr, st);
+      else if (nbp == 2) e = launch_pe_t<D, KL, kScanPruned, false, 2>(pr, kp, g, b, nullptr, st);
+      else if constexpr (nb_for(D, false) == 4) e = launch_pe_t<D, KL, kScanPruned, false, 4>(pr, kp, g, b, nullptr, st);
       if (e != hipSuccess) return e;
       // the threshold scan only where some list overflowed its key buffer
       return launch_pe_t<D, KL, kScanThreshold, false>(pr, kp, g, b, b.ctl + rows, st);

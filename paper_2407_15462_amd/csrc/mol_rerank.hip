@@ -133,19 +133,20 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
 // ---------------------------------------------------------------------------
 bool rerank_supported(const DevProb& pr) { return fused_supported(pr, 1); }
 
-// Candidates per wave: the largest of 4096, 2048, 1024, 512 and 256 that
-// still gives at least one round of resident waves (two 4-wave workgroups
-// per CU on 256 CUs), so that long lists amortise each wave's operand set-up
-// and small batches still fill the chip.  With the candidates in ascending
-// id bins (the dedup's output order) and every wave resident at once, the
-// waves sweep the corpus together and the several queries that share an
-// item gather it close in time (exact_1m: 1.67 ms with 2048, 1.52 ms with
+// Candidates per wave: the largest power of two from 4096 down to 32 that
+// still gives three quarters of a round of resident waves (two 4-wave workgroups
+// per CU on 256 CUs; 32 x 14,800: 97 us with 256 a wave, 104 with 128), so that long lists amortise each wave's operand set-up and
+// small batches still fill the chip (8 queries x 1260 candidates: 49 us with
+// 256 a wave, 12 us with 32; 64 x 640: 32 and 13 us).  With the candidates in
+// ascending id bins (the dedup's output order) and every wave resident at
+// once, the waves sweep the corpus together and the several queries that share
+// an item gather it close in time (exact_1m: 1.67 ms with 2048, 1.52 ms with
 // 4096; 1.88 ms in hash order).
 int rerank_chunk(int B, int C) {
   constexpr long kResidentWaves = 2l * kWaves * 256;
-  for (int chunk = 4096; chunk > 256; chunk /= 2)
-    if (static_cast<long>(B) * ((C + chunk - 1) / chunk) >= kResidentWaves) return chunk;
-  return 256;
+  for (int chunk = 4096; chunk > 32; chunk /= 2)
+    if (static_cast<long>(B) * ((C + chunk - 1) / chunk) >= kResidentWaves * 3 / 4) return chunk;
+  return 32;
 }
 
 template <int PX, int D, int H, bool X2>
