@@ -225,6 +225,7 @@ struct DensePlan {
   long sRow = 0;                   // dots buffer row (0: no buffer)
   int T = 0;                       // items per dots tile
   bool fused = false;              // scored by the fused kernels
+  int slab = 0;                    // queries per pass (fused form; else all)
   bool dphi = false;               // scored by the dots + gating kernel
   FusedDenseGrid g;
   size_t offPhi = 0, offBmax = 0, offS = 0, offRedo = 0, bytes = 0;
@@ -241,20 +242,42 @@ bool dense_fits(const DevProb& pr, int k) {
 
 enum DenseBy { kByFused, kByPairs, kByMaxDot };   // what scores the rows
 
+// Queries per pass of the fused dense form: the whole batch, or equal slabs of
+// whole 16-query groups whose scores fit kDenseMax (0: not even one group's do).
+int dense_slab(const DevProb& pr) {
+  const long ld = (pr.N + 3l) & ~3l, most = static_cast<long>(kDenseMax / (4 * ld));
+  if (pr.B <= most) return pr.B;
+  if (most < 16) return 0;
+  const long slabs = (pr.B + most / 16 * 16 - 1) / (most / 16 * 16);
+  return static_cast<int>(((pr.B + slabs - 1) / slabs + 15) / 16 * 16);
+}
+
+// the problem of queries [b0, b0 + n)
+DevProb query_slab(const DevProb& pr, int b0, int n) {
+  DevProb s = pr;
+  s.B = n;
+  s.Q = static_cast<const char*>(pr.Q) + (pr.dtype == MOL_BF16 ? 2l : 4l) * b0 * pr.Pq * pr.d;
+  s.a_q = pr.a_q ? pr.a_q + static_cast<long>(b0) * pr.P : nullptr;
+  return s;
+}
+
 DensePlan plan_dense(const DevProb& pr, int k, DenseBy by) {
   DensePlan f;
   f.ld = (pr.N + 3l) & ~3l;
   f.T = pr.N;
-  size_t off = align_up(4ul * pr.B * f.ld);
+  f.slab = by == kByFused ? dense_slab(pr) : pr.B;
+  size_t off = align_up(4ul * f.slab * f.ld);
   if (by == kByFused) {
     f.fused = true;
-    f.g = fused_dense_grid(pr, pr.N);
+    f.g = fused_dense_grid(query_slab(pr, 0, f.slab), pr.N);
+    const int rest = pr.B % f.slab;   // the last slab's grid may need more flags
+    const FusedDenseGrid gl = rest ? fused_dense_grid(query_slab(pr, 0, rest), pr.N) : f.g;
     f.offRedo = off;
-    off = align_up(off + 4ul * fused_redo_flags(f.g.R, f.g.G));
+    off = align_up(off + 4ul * std::max(fused_redo_flags(f.g.R, f.g.G), fused_redo_flags(gl.R, gl.G)));
   }
   if (use_buckets(pr.N, k)) {
     f.offBmax = off;
-    off = align_up(off + 4ul * pr.B * bucket_row(pr.N, f.g.SL));
+    off = align_up(off + 4ul * f.slab * bucket_row(pr.N, 4));   // (any number of slices)
   }
   f.dphi = by == kByPairs && dots_phi_supported(pr);
   if (by == kByPairs && !f.dphi && dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
@@ -542,7 +565,35 @@ size_t exact_list_ws_bytes(const DevProb& pr, int k) {
 // the dense form where its buffer fits; the bounded scan of the fused shapes
 // keeps its lists, whose running threshold prunes it
 bool use_dense(const DevProb& pr, int k, bool bounded) {
-  return dense_fits(pr, k) && !(bounded && fused_supported(pr, k));
+  if (!fused_supported(pr, k)) return dense_fits(pr, k);
+  if (bounded) return false;
+  const int slab = dense_slab(pr);
+  if (slab == pr.B) return true;
+  if (slab == 0) return false;
+  // Slabs of queries where a workgroup's serial walk is shorter: both sides are
+  // counted in items that the busiest CU walks, with weights chosen to fit the
+  // shapes below: 20 k items for a range's lists, 32 for a dense workgroup's
+  // set-up, 180 for a slab's selection and launches.  List form -> slabs, with
+  // the ratio of the two counts (8 x 8, d = 64, k = 100 unless said):
+  //   1082 x 414,714, k = 28             0.80   19.0 -> 15.5 ms
+  //   1090 x 131,101 (8 x 4), k = 50     0.81   4.77 -> 3.65
+  //   700 x 500,001 (d = 32)             0.86   13.7 -> 11.3
+  //   1900 x 150,001                     0.93   10.75 -> 10.0
+  //   300 x 2,000,003                    0.96   21.6 -> 21.2
+  //   256 x 800,001 (d = 32)             0.97   7.10 -> 6.50
+  //   512 x 2^20                         0.99   18.4 -> 18.3
+  //   1024 x 300,007                     0.99   10.8 -> 10.9
+  //   1024 x 2^20                        1.00   36.0 -> 36.5
+  // so the line lies at 0.98.
+  int R, len, G;
+  fused_grid(pr, pr.N, R, len, G, false);
+  const double lists = (static_cast<long>(R) * G + 255) / 256 * (len + 20.0 * k);
+  double dense = 0;
+  for (int b0 = 0; b0 < pr.B; b0 += slab) {
+    const FusedDenseGrid g = fused_dense_grid(query_slab(pr, b0, std::min(slab, pr.B - b0)), pr.N);
+    dense += (static_cast<long>(g.R) * g.G + 255) / 256 * (g.range_len / g.SL + 32.0) + 180.0;
+  }
+  return dense < 0.98 * lists;
 }
 DenseBy dense_by(const DevProb& pr, int k) { return fused_supported(pr, k) ? kByFused : kByPairs; }
 
@@ -614,33 +665,43 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
   const DensePlan f = plan_dense(pr, k, mode == kGenMaxDot ? kByMaxDot : dense_by(pr, k));
   float* phi = reinterpret_cast<float*>(w + f.offPhi);
   float* bmax = f.offBmax ? reinterpret_cast<float*>(w + f.offBmax) : nullptr;
-  const long bstride = bucket_row(pr.N, f.g.SL);
   float* sbuf = f.sRow ? reinterpret_cast<float*>(w + f.offS) : nullptr;
-  if (f.fused)
-    MOL_TIMED_LAUNCH(timed_op, st,
-                     launch_fused_dense(pr, f.g, 0, pr.N, phi, f.ld, bmax, bstride,
-                                        reinterpret_cast<int*>(w + f.offRedo), st),
-                     "fused MoL scores");
-  if (f.dphi)
-    MOL_TIMED_LAUNCH(timed_op, st, launch_dots_phi(pr, mode == kGenBounded ? bound : nullptr, phi, f.ld, bmax, bstride, st),
-                     "dots and gating");
-  for (long n0 = 0; n0 < pr.N && !f.fused && !f.dphi; n0 += f.T) {
-    const int nt = static_cast<int>(std::min<long>(f.T, pr.N - n0));
-    MOL_TIMED_LAUNCH(timed_op, st,
-                     pairwise_score(pr, sbuf, f.sRow, mode, bound, static_cast<int>(n0), nt, phi + n0, f.ld, nullptr,
-                                    0, st),
-                     "score tile");
-  }
   DenseRows r;
   r.phi = phi;
   r.phi_stride = f.ld;
   r.L = pr.N;
   r.skip_neg_inf = mode == kGenBounded;
   r.bmax = bmax;
-  r.bmax_stride = bstride;
-  r.SL = f.g.SL;
-  if (bmax && !f.fused && !f.dphi)
-    MOL_TRY_HIP(launch_bucket_max(phi, f.ld, pr.B, pr.N, 1.f, bmax, bstride, st), "bucket maxima");
+  if (f.fused) {
+    for (int b0 = 0; b0 < pr.B; b0 += f.slab) {
+      const DevProb ps = query_slab(pr, b0, std::min(f.slab, pr.B - b0));
+      const FusedDenseGrid g = ps.B == f.slab ? f.g : fused_dense_grid(ps, pr.N);
+      r.SL = g.SL;
+      r.bmax_stride = bucket_row(pr.N, g.SL);
+      MOL_TIMED_LAUNCH(timed_op, st,
+                       launch_fused_dense(ps, g, 0, pr.N, phi, f.ld, bmax, r.bmax_stride,
+                                          reinterpret_cast<int*>(w + f.offRedo), st),
+                       "fused MoL scores");
+      MOL_TRY_HIP(launch_topk_dense(r, ps.B, k, out_score + static_cast<long>(b0) * k,
+                                    out_idx + static_cast<long>(b0) * k, st),
+                  "dense top-k");
+    }
+    return MOL_OK;
+  }
+  r.bmax_stride = bucket_row(pr.N, 1);
+  if (f.dphi)
+    MOL_TIMED_LAUNCH(timed_op, st,
+                     launch_dots_phi(pr, mode == kGenBounded ? bound : nullptr, phi, f.ld, bmax, r.bmax_stride, st),
+                     "dots and gating");
+  for (long n0 = 0; n0 < pr.N && !f.dphi; n0 += f.T) {
+    const int nt = static_cast<int>(std::min<long>(f.T, pr.N - n0));
+    MOL_TIMED_LAUNCH(timed_op, st,
+                     pairwise_score(pr, sbuf, f.sRow, mode, bound, static_cast<int>(n0), nt, phi + n0, f.ld, nullptr,
+                                    0, st),
+                     "score tile");
+  }
+  if (bmax && !f.dphi)
+    MOL_TRY_HIP(launch_bucket_max(phi, f.ld, pr.B, pr.N, 1.f, bmax, r.bmax_stride, st), "bucket maxima");
   MOL_TRY_HIP(launch_topk_dense(r, pr.B, k, out_score, out_idx, st), "dense top-k");
   return MOL_OK;
 }

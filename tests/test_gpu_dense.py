@@ -145,3 +145,20 @@ def test_dots_phi_equals_pairwise_kernels(B, Pq, d, H, N, k):
         want = torch.topk(f32, k, dim=1).values
         got = torch.gather(f32, 1, i.long())
         assert (s - got).abs().max() <= 2e-5 and (got - want).abs().max() <= 4e-5
+
+
+def test_dense_slabs_of_queries():
+    """A batch whose dense scores pass the buffer and whose list form would
+    leave CUs idle runs in slabs of queries: the rows of the allocation-free
+    (list) form, bit for bit, the last slab included."""
+    spec = W["exact_32k"].scaled(B=1090, N=131101, clusters=512)
+    inp = cuda_inputs(spec, seed=8)
+    for flags in (0, mol.MOL_FLAG_BF16X2_GATING):
+        prob = mol.Problem.from_inputs(inp, flags=flags)
+        # slabs: about half a gigabyte of scores; the list form needs a few MB
+        assert mol.mol_workspace_size(prob, mol.MOL_OP_TOPK_EXACT, k=50) > 256 << 20
+        s, i = mol.topk_exact(prob, 50)
+        ns, ni = torch.empty_like(s), torch.empty_like(i)
+        mol.mol_topk_exact_noalloc(prob, 50, ns, ni)
+        torch.cuda.synchronize()
+        assert torch.equal(ns, s) and torch.equal(ni, i)
