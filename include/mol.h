@@ -137,6 +137,8 @@ typedef struct mol_problem {
 
 /* Bytes of workspace an entry point needs for this problem (k, kprime and C
  * as they will be passed; ignored where irrelevant).  Writes *bytes.
+ * mol_topk_exact also takes a smaller workspace that holds its list form, as
+ * one kept for a larger batch does.
  * Returns MOL_OK or the validation error the entry point would return. */
 int mol_workspace_size(const mol_problem *prob, int op, int32_t k,
                        int32_t kprime, int32_t C, size_t *bytes);

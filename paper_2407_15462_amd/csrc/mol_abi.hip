@@ -708,7 +708,8 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
 
 // Exact MoL top-k over the corpus; with `bound` ([B] floats) only the items
 // whose max_p s_p can reach bound[b] are ranked.  lists: keep to the form
-// with per-range lists or key tiles (mol_topk_exact_noalloc's small scratch).
+// with per-range lists or key tiles (a workspace without room for the scores,
+// mol_topk_exact_noalloc's scratch).
 int run_exact(const DevProb& pr, int k, const float* bound, float* out_score, int32_t* out_idx,
               char* w, int timed_op, hipStream_t st, bool lists = false) {
   int rc;
@@ -1046,9 +1047,15 @@ int mol_topk_exact(const mol_problem* prob, int32_t k, float* out_score, int32_t
   if ((rc = check_k(k, prob->N, "k"))) return rc;
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  if ((rc = check_ws(ws, ws_bytes, exact_ws_bytes(pr, k, false)))) return rc;
+  // A program may keep one workspace, sized for its largest batch.  The dense
+  // form ends where its scores pass kDenseMax, so a smaller batch can ask for
+  // more than the largest one does (8 x 8, d = 64, 2^20 items: 520 MB at 256
+  // queries, 4.7 MB at 1024): without room for it a call takes the lists.
+  const size_t dense = exact_ws_bytes(pr, k, false), least = exact_list_ws_bytes(pr, k);
+  const bool lists = ws_bytes < dense && ws_bytes >= least;
+  if ((rc = check_ws(ws, ws_bytes, lists ? least : dense))) return rc;
   return run_exact(pr, k, nullptr, out_score, out_idx, static_cast<char*>(ws), MOL_OP_TOPK_EXACT,
-                   static_cast<hipStream_t>(stream));
+                   static_cast<hipStream_t>(stream), lists);
 }
 
 int mol_topk_exact_noalloc(const mol_problem* prob, int32_t k, float* out_score, int32_t* out_idx,

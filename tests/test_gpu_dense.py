@@ -162,3 +162,18 @@ def test_dense_slabs_of_queries():
         mol.mol_topk_exact_noalloc(prob, 50, ns, ni)
         torch.cuda.synchronize()
         assert torch.equal(ns, s) and torch.equal(ni, i)
+
+
+def test_workspace_without_room_for_dense_scores():
+    """A workspace kept for a larger batch can be smaller than the dense form
+    of this batch: the calls take the lists and return the same rows."""
+    spec = W["exact_32k"].scaled(B=40, N=70001, clusters=256)
+    prob = mol.Problem.from_inputs(cuda_inputs(spec, seed=5))
+    small = mol.workspace(prob, mol.MOL_OP_TOPK_BOUNDED, k=50)      # the lists' size
+    assert small.numel() < mol.mol_workspace_size(prob, mol.MOL_OP_TOPK_EXACT, k=50)
+    s, i = mol.topk_exact(prob, 50)
+    ls, li = mol.topk_exact(prob, 50, ws=small)
+    torch.cuda.synchronize()
+    assert torch.equal(s, ls) and torch.equal(i, li)
+    with pytest.raises(mol.MolError):
+        mol.topk_exact(prob, 50, ws=small[:-256])
