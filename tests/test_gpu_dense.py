@@ -177,3 +177,28 @@ def test_workspace_without_room_for_dense_scores():
     assert torch.equal(s, ls) and torch.equal(i, li)
     with pytest.raises(mol.MolError):
         mol.topk_exact(prob, 50, ws=small[:-256])
+
+
+# lists of more than 256 keys are ranked by bins of the score range: the bin
+# limit (64 keys of one score), more (the bitonic network), more than the list
+# holds (the radix search), and k with a few and with all keys above it
+@pytest.mark.parametrize("ties,kp,N", [
+    (0, 300, 3000), (63, 300, 20011), (65, 1000, 60001), (64, 513, 50000), (3000, 2048, 60001), (5000, 2048, 200001),
+    (0, 2048, 200001),
+])
+def test_long_lists_with_ties(ties, kp, N):
+    log(f"[long lists] ties={ties} k'={kp} N={N}")
+    g = torch.Generator(device="cuda").manual_seed(N + ties)
+    Q = torch.nn.functional.normalize(torch.randn((3, 1, 64), generator=g, device="cuda"), dim=-1).bfloat16()
+    X = torch.nn.functional.normalize(torch.randn((1, N, 64), generator=g, device="cuda"), dim=-1).bfloat16()
+    if ties:
+        at = torch.randperm(N, generator=torch.Generator().manual_seed(4))[:ties].cuda()
+        X[:, at] = torch.nn.functional.normalize(Q[0, 0].float() + 2 * X[0, at[0]].float(), dim=-1).bfloat16()
+    dots, ids = mol.topk_per_embd(mol.Problem(Q, X), kp)
+    torch.cuda.synchronize()
+    s = Q[:, 0].double() @ X[0].double().t().contiguous()
+    want = torch.topk(s, kp, dim=1).values
+    got = torch.gather(s, 1, ids[:, 0].long())
+    tol = 64 * 2.0 ** -24                                    # float32 sums of 64 products of unit rows
+    assert (dots[:, 0].double() - got).abs().max() <= tol and (got - want).abs().max() <= 2 * tol
+    assert _ordered(dots[:, 0], ids[:, 0]) and all(torch.unique(ids[b, 0]).numel() == kp for b in range(3))
