@@ -2,21 +2,24 @@
 // workgroup per row, straight to the decoded outputs.
 //
 // Every thread takes the maximum of its own share of the row (1024 disjoint
-// buckets; for k > 512 every bucket of bmax, or score, counts by itself).  k buckets whose maxima reach T hold k items scoring at least T,
-// so T = the k-th largest bucket maximum bounds the row's k-th score from
-// below, and about k + k^2 / 2048 items of the row reach it: those are
-// collected in LDS, ranked by counting and written out.  A row whose items
-// reaching T exceed the LDS list (massive ties, an adversarial order) is
-// finished by a radix search over its 64-bit sort keys, 8 bits a pass.
+// buckets; for k > 512 every bucket of bmax, or score, counts by itself).  k
+// buckets whose maxima reach T hold k items scoring at least T, so T = the
+// k-th largest bucket maximum bounds the row's k-th score from below, and
+// about k + k^2 / 2048 items of the row reach it: those are collected in LDS,
+// ranked by counting (long lists inside bins of the score range) and written
+// out.  A row whose items reaching T exceed the LDS list (massive ties, an
+// adversarial order) is finished by a radix search over its 64-bit sort keys,
+// 8 bits a pass.
 //
 // What bounds it: one read of the row at a workgroup's rate (about 100 GB/s)
 // and a dozen barriers.  With per-bucket maxima from the kernel that scored
-// the row (64 items a bucket)
-// it reads those instead, a 64th of the row, and then only the items of the k
-// buckets that reach T: one CU draws some 20 GB/s from memory other CUs wrote.  Measured: top-100 of 32
-// rows of 109,739 scores 13 us plus 6 us for the maxima (chunked radix
-// selection, segmented sort and decode of 64-bit keys: 52 us; straight from the
-// rows 61 us), of one row of 2^20 19 us.
+// the row (64 items a bucket) it reads those instead, a 64th of the row, and
+// then only the items of the buckets that reach T, by the loads a CU can keep
+// in flight to memory other CUs wrote (about 20 GB/s with 16 KB of them).
+// Measured: top-100 of 32 rows of 109,739 scores 13 us plus 6 us for the
+// maxima (chunked radix selection, segmented sort and decode of 64-bit keys:
+// 52 us; straight from the rows 61 us), of one row of 2^20 19 us; top-2000 of
+// 32 rows of 674,044 71 us.
 #include <type_traits>
 
 #include "mol_tile.h"
