@@ -70,7 +70,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
   // Each step's 16 items are gathered one step ahead: the component
   // operands by direct global -> LDS copies into the wave's buffer (read
   // back into registers at the start of the step, after which the next
-  // step's copies are issued into it), the item logits a_x into registers.
+  // step's copies are issued into it), the item logits a_x into registers by
+  // PT loads behind the copies.  (The id load behind those is clamped at once,
+  // for which the compiler waits before the step's MFMAs, copies included: the
+  // gathers of a wave run under the other wave of its SIMD, not under its own
+  // chain.)
   unsigned char* gbuf = sGather + __builtin_amdgcn_readfirstlane(wave) * (PX * KD * 1024);
   auto item_at = [&](int pos) { return pos < i1 ? min(max(ids[pos], 0), N - 1) : 0; };   // ids are in range
   float4 axn[PT];
@@ -91,11 +95,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
   for (int s0 = i0; s0 < i1; s0 += 16) {
     const int pos = s0 + c;
     const bool ok = pos < i1;
-    // this step's copies have landed (the younger a_x and id loads, and the
-    // last step's store, may be outstanding); read the operands, then refill
-    // the buffer
+    // this step's copies have landed: every gather ends in PT a_x loads, and
+    // only those may be outstanding (an id load or a store behind them makes
+    // the wait stricter, but a chunk of one step has neither); read the
+    // operands, then refill the buffer
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(PT + 1));
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(PT));
     asm volatile("" ::: "memory");
     uint4 xop[PX][KD];
 #pragma unroll
