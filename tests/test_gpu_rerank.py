@@ -18,8 +18,8 @@ W = synth.WORKLOADS
 @pytest.mark.parametrize("wl", ["exact_32k", "exact_1m", "hybrid_8m", "paper_books"])
 @pytest.mark.parametrize("flags", [0, mol.MOL_FLAG_BF16X2_GATING])
 def test_rerank_chunk_ends(wl, flags):
-    counts = [1, 15, 16, 17, 31, 32, 33, 0, 64, 65, 127, 129]
-    C = max(counts)
+    counts = [1, 15, 16, 17, 31, 32, 33, 0, 64, 65, 97, 128]
+    C = max(counts)                              # = k, the largest of the fused rerank
     log(f"[rerank ends] {wl} flags={flags} counts={counts}")
     spec = W[wl].scaled(B=len(counts), N=5003, clusters=16)
     prob = mol.Problem.from_inputs(cuda_inputs(spec, seed=29), flags=flags)
