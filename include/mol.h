@@ -137,8 +137,12 @@ typedef struct mol_problem {
 
 /* Bytes of workspace an entry point needs for this problem (k, kprime and C
  * as they will be passed; ignored where irrelevant).  Writes *bytes.
- * mol_topk_exact also takes a smaller workspace that holds its list form, as
- * one kept for a larger batch does.
+ * The size is that of the entry point's fastest form.  The entry points also
+ * take a smaller workspace that holds another of their forms, as one kept for
+ * a larger batch may, whose dense scores would pass the half gigabyte that the
+ * library gives them; the least they take is in the message of
+ * MOL_EWORKSPACE.  The rows are the same (mol_rerank's within the precision of
+ * the gating MLP: without room for its dot products it scores in float32).
  * Returns MOL_OK or the validation error the entry point would return. */
 int mol_workspace_size(const mol_problem *prob, int op, int32_t k,
                        int32_t kprime, int32_t C, size_t *bytes);
@@ -165,12 +169,11 @@ int mol_topk_exact(const mol_problem *prob, int32_t k, float *out_score,
 /* mol_topk_exact without a workspace argument and without allocating, for
  * callers that cannot allocate device memory at call time (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc).
- * Same computation, outputs, ordering and limits as mol_topk_exact; the
- * workspace mol_topk_exact would take (mol_workspace_size with
- * MOL_OP_TOPK_EXACT) must be at most MOL_NOALLOC_SCRATCH_BYTES, which
- * covers the fused shapes at up to 1024 queries and k <= 128 (e.g. B = 1024,
- * N = 2^20, P = 8 x 8, d = 64: 4.7 MiB); larger needs return
- * MOL_EWORKSPACE and launch nothing.  The scratch is a static device array
+ * Same computation, outputs, ordering and limits as mol_topk_exact, always in
+ * its form with per-range lists or key tiles, which must need at most
+ * MOL_NOALLOC_SCRATCH_BYTES.  That covers the fused shapes at up to 1024
+ * queries and k <= 128 (e.g. B = 1024, N = 2^20, P = 8 x 8, d = 64: 4.7 MiB);
+ * larger needs return MOL_EWORKSPACE and launch nothing.  The scratch is a static device array
  * of the library, one per GPU, kept until the process ends and located on
  * each device's first call.  Every call on a GPU uses that GPU's one array:
  * calls that overlap on the same GPU (two streams, two threads) race and

@@ -1,6 +1,7 @@
 // Host side of the C ABI declared in include/mol.h: argument validation,
 // workspace planning and kernel sequencing on the caller's stream.
 #include <algorithm>
+#include <climits>
 #include <cstdarg>
 #include <cstdio>
 #include <mutex>
@@ -101,6 +102,17 @@ void timing_stop(int op, const EvPair& p, hipStream_t st, bool launched) {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
+// Workspace of an entry point: what its preferred form needs, which is the
+// size that mol_workspace_size gives, and what the smallest form that it can
+// fall back to needs.  A program may keep one workspace, sized for its largest
+// call; the dense forms end where their buffers pass kDenseMax, so a smaller
+// call can prefer more than the largest one does (exact top-k, 8 x 8, d = 64,
+// 2^20 items: 520 MB at 256 queries, 4.7 MB at 1024).  Without room for it a
+// call takes its other form.
+struct WsBytes {
+  size_t best = 0, least = 0;
+};
+
 // Shape / pointer validation shared by every entry point.
 int check_problem(const mol_problem* p, bool gating) {
   if (!p) return fail(MOL_EINVAL, "prob is NULL");
@@ -148,6 +160,7 @@ struct StreamPlan {
   long strideA = 0, strideB = 0;
   long sRow = 0;                   // dot buffer: floats per (p, b) row (0: no buffer)
   size_t offRun = 0, offA = 0, offB = 0, offS = 0, bytes = 0;
+  size_t most = 0;                 // bytes of any smaller problem's plan
 };
 
 // dots_P, dots_B: when nonzero, a buffer of the tile's component dot
@@ -177,6 +190,17 @@ StreamPlan plan_stream(int rows, int N, int k, int dots_P = 0, int dots_B = 0) {
     s.offS = off;  off = align_up(off + 4ul * dots_P * dots_B * s.sRow);
   }
   s.bytes = off;
+  // The tile's rounding makes the plan of a smaller problem larger than this
+  // one now and then (by up to 256 items a row): bounds that only grow with
+  // rows, N and k.
+  const size_t item = 8ul * rows, n256 = (std::max(1024l, static_cast<long>(N)) + 255) / 256 * 256;
+  const size_t a = item * k + std::min<size_t>(item * n256, std::max<size_t>(item * 1024, budget + item * 256));
+  const size_t b = item * k + (n256 + k <= 4096 ? 0 : a / 4096 * k + k);
+  s.most = align_up(item * k) + align_up(a) + align_up(b);
+  if (dots_P > 0) {
+    const size_t dots = 4ul * dots_P * dots_B;
+    s.most += align_up(std::min<size_t>(dots * n256, std::max<size_t>(dots * 1024, (512ul << 20) + dots * 256)));
+  }
   return s;
 }
 
@@ -188,12 +212,11 @@ bool pairwise_mfma(const DevProb& pr, long sRow) {
          static_cast<long>(pr.P) * pr.B * sRow < (1l << 32);   // the gating kernel's element offsets
 }
 
+WsBytes stream_ws(const StreamPlan& s) { return {s.most, s.bytes}; }
+
 // Plan of the tile-streamed pair-wise path of a MoL-scored selection.
 StreamPlan plan_pairwise(const DevProb& pr, int k) {
-  if (dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
-    const StreamPlan s = plan_stream(pr.B, pr.N, k, pr.P, pr.B);
-    if (pairwise_mfma(pr, s.sRow)) return s;
-  }
+  if (dots_mfma_supported(pr) && phi_mfma_supported(pr)) return plan_stream(pr.B, pr.N, k, pr.P, pr.B);
   return plan_stream(pr.B, pr.N, k);
 }
 
@@ -220,6 +243,9 @@ constexpr size_t kDenseMax = size_t(512) << 20;
 // their own (about 5 us); the top-k kernel reads other rows directly.
 constexpr int kBucketMinN = 1 << 14;
 
+// The sizes of the dense plans grow with the batch, the corpus and k (nothing
+// depends on a tile's rounding or on a rule of k), so that a workspace kept for
+// a larger problem holds the dense form of a smaller one.
 struct DensePlan {
   long ld = 0;                     // floats per phi row (a multiple of 4)
   long sRow = 0;                   // dots buffer row (0: no buffer)
@@ -236,9 +262,10 @@ bool use_buckets(long N, int k) { return N >= kBucketMinN && N >= 96l * k; }
 // scores (about 60 us) that is still the faster way
 bool dense_k(long N, int k) { return k <= 512 || (k <= kTopkDenseMaxK && (use_buckets(N, k) || N <= 65536)); }
 
-bool dense_fits(const DevProb& pr, int k) {
-  return dense_k(pr.N, k) && 4ul * pr.B * ((pr.N + 3l) & ~3l) <= kDenseMax;
+bool can_dense(const DevProb& pr, int k) {
+  return k <= kTopkDenseMaxK && 4ul * pr.B * ((pr.N + 3l) & ~3l) <= kDenseMax;
 }
+bool dense_fits(const DevProb& pr, int k) { return dense_k(pr.N, k) && can_dense(pr, k); }
 
 enum DenseBy { kByFused, kByPairs, kByMaxDot };   // what scores the rows
 
@@ -270,26 +297,22 @@ DensePlan plan_dense(const DevProb& pr, int k, DenseBy by) {
   if (by == kByFused) {
     f.fused = true;
     f.g = fused_dense_grid(query_slab(pr, 0, f.slab), pr.N);
-    const int rest = pr.B % f.slab;   // the last slab's grid may need more flags
-    const FusedDenseGrid gl = rest ? fused_dense_grid(query_slab(pr, 0, rest), pr.N) : f.g;
     f.offRedo = off;
-    off = align_up(off + 4ul * std::max(fused_redo_flags(f.g.R, f.g.G), fused_redo_flags(gl.R, gl.G)));
+    off = align_up(off + 4ul * fused_dense_redo_flags(f.slab, pr.N));
   }
-  if (use_buckets(pr.N, k)) {
-    f.offBmax = off;
-    off = align_up(off + 4ul * f.slab * bucket_row(pr.N, 4));   // (any number of slices)
-  }
+  const size_t offBmax = off;
+  off = align_up(off + 4ul * f.slab * bucket_row(pr.N, 4));   // (any number of slices)
+  if (use_buckets(pr.N, k)) f.offBmax = offBmax;
   f.dphi = by == kByPairs && dots_phi_supported(pr);
   if (by == kByPairs && !f.dphi && dots_mfma_supported(pr) && phi_mfma_supported(pr)) {
-    // dots tiles of at most 512 MB, whole 128-item GEMM tiles
-    const long T = std::max(1024l, std::min<long>(pr.N, (512l << 20) / (4l * pr.P * pr.B) / 128 * 128));
-    const long sRow = dots_buffer_row(static_cast<int>(T));
-    if (pairwise_mfma(pr, sRow)) {
-      f.T = static_cast<int>(T);
-      f.sRow = sRow;
-      f.offS = off;
-      off = align_up(off + 4ul * pr.P * pr.B * sRow);
-    }
+    // dots tiles of at most 512 MB (but 1024 items), whole 128-item GEMM tiles
+    const size_t item = 4ul * pr.P * pr.B, whole = item * dots_buffer_row(pr.N);
+    const size_t room = std::min(whole, std::max(size_t(512) << 20, 1024 * item));
+    const long T = std::min<long>(pr.N, room / item / 128 * 128);
+    f.T = static_cast<int>(T);
+    f.sRow = dots_buffer_row(f.T);
+    f.offS = off;
+    off = align_up(off + room);
   }
   f.bytes = off;
   return f;
@@ -372,7 +395,10 @@ struct RerankPlan {
 // the fused rerank for the k of the fused kernels' other forms
 bool use_fused_rerank(const DevProb& pr, int k) { return rerank_supported(pr) && fused_supported(pr, k); }
 
-RerankPlan plan_rerank(const DevProb& pr, int C, int k) {
+// have: bytes of workspace; without room for the dots buffer (a call with the
+// workspace of a larger batch, whose buffer would pass the gating kernel's
+// element offsets) the candidates are scored in float32 without one.
+RerankPlan plan_rerank(const DevProb& pr, int C, int k, size_t have = SIZE_MAX) {
   const size_t B = pr.B;
   RerankPlan r;
   StreamPlan& s = r.s;
@@ -393,9 +419,10 @@ RerankPlan plan_rerank(const DevProb& pr, int C, int k) {
   }
   r.offUniq = off;  off = align_up(off + 4ul * B * C);
   r.offNu = off;    off = align_up(off + 4ul * B);
-  if (!use_fused_rerank(pr, k) && pairwise_mfma(pr, dots_buffer_row(C))) {
+  const size_t dots = 4ul * pr.P * B * dots_buffer_row(C);
+  if (!use_fused_rerank(pr, k) && pairwise_mfma(pr, dots_buffer_row(C)) && align_up(off + dots) <= have) {
     r.sRow = dots_buffer_row(C);
-    r.offS = off;   off = align_up(off + 4ul * pr.P * B * r.sRow);
+    r.offS = off;   off = align_up(off + dots);
   }
   r.bytes = off;
   return r;
@@ -428,6 +455,8 @@ FusedExactPlan plan_fused_exact(const DevProb& pr, int k, bool maxdot = false) {
   return f;
 }
 
+WsBytes fused_list_ws(const FusedExactPlan& f) { return {f.bytes, f.bytes}; }
+
 // Per-component top-k' through the MFMA kernel: lists [P*B rows][R][KL]
 // are reduced to [rows][k'] by segmented sorts.
 struct PerEmbdPlan {
@@ -438,9 +467,11 @@ struct PerEmbdPlan {
   size_t offCtl = 0, offKeys = 0, offHotV = 0, offHotN = 0, offWork = 0, bytes = 0;
 };
 
-PerEmbdPlan plan_per_embd(const DevProb& pr, int kp) {
+// max_ranges: most item ranges of the threshold scan, whose lists and staging
+// take most of the workspace
+PerEmbdPlan plan_per_embd_ranges(const DevProb& pr, int kp, int max_ranges) {
   PerEmbdPlan f;
-  per_embd_grid(pr, kp, f.g);
+  per_embd_grid(pr, kp, max_ranges, f.g);
   f.KL = per_embd_list_cap(kp);
   StreamPlan& s = f.s;
   s.rows = pr.B * pr.P;
@@ -468,6 +499,14 @@ PerEmbdPlan plan_per_embd(const DevProb& pr, int kp) {
     f.offWork = off;  off = align_up(off + 4ul * f.g.groups * f.g.CH);
   }
   f.bytes = off;
+  return f;
+}
+
+// in `have` bytes: fewer ranges where the preferred plan does not fit (the
+// appending forms reach the threshold scan only after an overflow)
+PerEmbdPlan plan_per_embd(const DevProb& pr, int kp, size_t have = SIZE_MAX) {
+  PerEmbdPlan f = plan_per_embd_ranges(pr, kp, INT_MAX);
+  for (int r = f.g.s2.R / 2; f.bytes > have && r >= 1; r /= 2) f = plan_per_embd_ranges(pr, kp, r);
   return f;
 }
 
@@ -543,28 +582,44 @@ DenseListPlan plan_dense_lists(const DevProb& pr) {
   return f;
 }
 
-// where the score buffer fits, and the shape has no per-component kernel or
-// the list is longer than its pruned form takes
-bool use_dense_lists(const DevProb& pr, int kp) {
-  return dots_mfma_supported(pr) && dense_k(pr.N, kp) && 4ul * pr.B * pr.P * dots_buffer_row(pr.N) <= kDenseMax &&
-         !(per_embd_supported(pr, kp) && kp <= 256);
+// where the score buffer fits
+bool can_dense_lists(const DevProb& pr, int kp) {
+  return dots_mfma_supported(pr) && kp <= kTopkDenseMaxK && 4ul * pr.B * pr.P * dots_buffer_row(pr.N) <= kDenseMax;
 }
 
-size_t per_embd_ws_bytes(const DevProb& pr, int kp) {
-  if (use_dense_lists(pr, kp)) return plan_dense_lists(pr).bytes;
-  if (per_embd_supported(pr, kp)) return plan_per_embd(pr, kp).bytes;
-  if (use_thresh_per_embd(pr, kp)) return plan_thresh(pr, kp).bytes;
-  return plan_stream(pr.B * pr.P, pr.N, kp).bytes;
+
+// the form without dense dot products
+WsBytes per_embd_list_ws(const DevProb& pr, int kp) {
+  if (per_embd_supported(pr, kp)) return {plan_per_embd(pr, kp).bytes, plan_per_embd(pr, kp, 0).bytes};
+  const WsBytes stream = stream_ws(plan_stream(pr.B * pr.P, pr.N, kp));
+  if (!use_thresh_per_embd(pr, kp)) return stream;
+  const size_t thresh = plan_thresh(pr, kp).bytes;
+  return {thresh, std::min(thresh, stream.least)};
+}
+
+// The dense lists, of the forms that `have` bytes hold: where the shape has no
+// per-component kernel or the list is longer than its pruned form takes.
+bool use_dense_lists(const DevProb& pr, int kp, size_t have = SIZE_MAX) {
+  if (!can_dense_lists(pr, kp) || plan_dense_lists(pr).bytes > have) return false;
+  if (dense_k(pr.N, kp) && !(per_embd_supported(pr, kp) && kp <= 256)) return true;
+  return per_embd_list_ws(pr, kp).least > have;
+}
+
+WsBytes per_embd_ws(const DevProb& pr, int kp) {
+  const WsBytes list = per_embd_list_ws(pr, kp);
+  if (!can_dense_lists(pr, kp)) return list;
+  const size_t dense = plan_dense_lists(pr).bytes;
+  return {use_dense_lists(pr, kp) ? dense : list.best, std::min(dense, list.least)};
 }
 
 // per-range lists or streamed key tiles: the form of every k and size
-size_t exact_list_ws_bytes(const DevProb& pr, int k) {
-  return fused_supported(pr, k) ? plan_fused_exact(pr, k).bytes : plan_pairwise(pr, k).bytes;
+WsBytes exact_list_ws(const DevProb& pr, int k) {
+  return fused_supported(pr, k) ? fused_list_ws(plan_fused_exact(pr, k)) : stream_ws(plan_pairwise(pr, k));
 }
 
 // the dense form where its buffer fits; the bounded scan of the fused shapes
 // keeps its lists, whose running threshold prunes it
-bool use_dense(const DevProb& pr, int k, bool bounded) {
+bool prefer_dense(const DevProb& pr, int k, bool bounded) {
   if (!fused_supported(pr, k)) return dense_fits(pr, k);
   if (bounded) return false;
   const int slab = dense_slab(pr);
@@ -597,21 +652,54 @@ bool use_dense(const DevProb& pr, int k, bool bounded) {
 }
 DenseBy dense_by(const DevProb& pr, int k) { return fused_supported(pr, k) ? kByFused : kByPairs; }
 
-size_t exact_ws_bytes(const DevProb& pr, int k, bool bounded) {
-  return use_dense(pr, k, bounded) ? plan_dense(pr, k, dense_by(pr, k)).bytes : exact_list_ws_bytes(pr, k);
+// the dense form, of the forms that `have` bytes hold
+bool use_dense(const DevProb& pr, int k, bool bounded, size_t have = SIZE_MAX) {
+  const bool prefer = prefer_dense(pr, k, bounded);
+  if (!prefer && (fused_supported(pr, k) || !can_dense(pr, k))) return false;
+  if (plan_dense(pr, k, dense_by(pr, k)).bytes > have) return false;
+  return prefer || exact_list_ws(pr, k).least > have;
 }
 
-size_t maxdot_ws_bytes(const DevProb& pr, int k) {
-  if (fused_maxdot_supported(pr, k)) return plan_fused_exact(pr, k, true).bytes;
-  if (!dots_maxkeys_supported(pr) && dense_fits(pr, k)) return plan_dense(pr, k, kByMaxDot).bytes;
-  return plan_stream(pr.B, pr.N, k).bytes;
+WsBytes exact_ws(const DevProb& pr, int k, bool bounded) {
+  const WsBytes list = exact_list_ws(pr, k);
+  const bool prefer = prefer_dense(pr, k, bounded);
+  if (!prefer && (fused_supported(pr, k) || !can_dense(pr, k))) return list;
+  const size_t dense = plan_dense(pr, k, dense_by(pr, k)).bytes;
+  return {prefer ? dense : list.best, std::min(dense, list.least)};
+}
+
+// the dense max-dot form: the shapes without a max-dot kernel
+bool can_dense_maxdot(const DevProb& pr, int k) {
+  return !fused_maxdot_supported(pr, k) && !dots_maxkeys_supported(pr) && can_dense(pr, k);
+}
+
+WsBytes maxdot_list_ws(const DevProb& pr, int k) {
+  return fused_maxdot_supported(pr, k) ? fused_list_ws(plan_fused_exact(pr, k, true))
+                                       : stream_ws(plan_stream(pr.B, pr.N, k));
+}
+
+bool use_dense_maxdot(const DevProb& pr, int k, size_t have = SIZE_MAX) {
+  if (!can_dense_maxdot(pr, k) || plan_dense(pr, k, kByMaxDot).bytes > have) return false;
+  return dense_k(pr.N, k) || maxdot_list_ws(pr, k).least > have;
+}
+
+WsBytes maxdot_ws(const DevProb& pr, int k) {
+  const WsBytes list = maxdot_list_ws(pr, k);
+  if (!can_dense_maxdot(pr, k)) return list;
+  const size_t dense = plan_dense(pr, k, kByMaxDot).bytes;
+  return {dense_k(pr.N, k) ? dense : list.best, std::min(dense, list.least)};
+}
+
+WsBytes rerank_ws(const DevProb& pr, int C, int k) {
+  return {plan_rerank(pr, C, k).bytes, plan_rerank(pr, C, k, 0).bytes};
 }
 
 // Algorithm 1 workspace: per-component lists, the rerank output over G,
 // the bound, and one region shared by the three phases (they run in order
 // on one stream).
 struct TwoPassPlan {
-  size_t offDots = 0, offIdx = 0, offScore = 0, offRidx = 0, offBound = 0, offWork = 0, bytes = 0;
+  size_t offDots = 0, offIdx = 0, offScore = 0, offRidx = 0, offBound = 0, offWork = 0;
+  WsBytes ws;
 };
 
 TwoPassPlan plan_two_pass(const DevProb& pr, int k) {
@@ -624,9 +712,8 @@ TwoPassPlan plan_two_pass(const DevProb& pr, int k) {
   t.offRidx = off;  off = align_up(off + 4ul * pr.B * k);
   t.offBound = off; off = align_up(off + 4ul * pr.B);
   t.offWork = off;
-  const size_t work = std::max({per_embd_ws_bytes(pr, k), plan_rerank(pr, pr.P * k, k).bytes,
-                                exact_ws_bytes(pr, k, true)});
-  t.bytes = off + align_up(work);
+  const WsBytes a = per_embd_ws(pr, k), b = rerank_ws(pr, pr.P * k, k), c = exact_ws(pr, k, true);
+  t.ws = {off + align_up(std::max({a.best, b.best, c.best})), off + align_up(std::max({a.least, b.least, c.least}))};
   return t;
 }
 
@@ -707,13 +794,13 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
 }
 
 // Exact MoL top-k over the corpus; with `bound` ([B] floats) only the items
-// whose max_p s_p can reach bound[b] are ranked.  lists: keep to the form
-// with per-range lists or key tiles (a workspace without room for the scores,
-// mol_topk_exact_noalloc's scratch).
+// whose max_p s_p can reach bound[b] are ranked.  have: bytes of workspace;
+// without room for the dense scores (and with 0, mol_topk_exact_noalloc's
+// scratch) the form with per-range lists or key tiles.
 int run_exact(const DevProb& pr, int k, const float* bound, float* out_score, int32_t* out_idx,
-              char* w, int timed_op, hipStream_t st, bool lists = false) {
+              char* w, size_t have, int timed_op, hipStream_t st) {
   int rc;
-  if (!lists && use_dense(pr, k, bound != nullptr))
+  if (use_dense(pr, k, bound != nullptr, have))
     return run_dense(pr, k, bound ? kGenBounded : kGenPhi, bound, out_score, out_idx, w, timed_op, st);
   if (fused_supported(pr, k)) {
     const FusedExactPlan f = plan_fused_exact(pr, k);
@@ -736,7 +823,7 @@ int run_exact(const DevProb& pr, int k, const float* bound, float* out_score, in
 }
 
 // Top-k by the largest component dot product max_p s_p.
-int run_maxdot(const DevProb& pr, int k, float* out_score, int32_t* out_idx, char* w, int timed_op,
+int run_maxdot(const DevProb& pr, int k, float* out_score, int32_t* out_idx, char* w, size_t have, int timed_op,
                hipStream_t st) {
   int rc;
   if (fused_maxdot_supported(pr, k)) {
@@ -757,7 +844,8 @@ int run_maxdot(const DevProb& pr, int k, float* out_score, int32_t* out_idx, cha
     };
     return stream_topk(s, pr.N, w, tile, out_score, out_idx, st);
   }
-  if (dense_fits(pr, k)) return run_dense(pr, k, kGenMaxDot, nullptr, out_score, out_idx, w, timed_op, st);
+  if (use_dense_maxdot(pr, k, have))
+    return run_dense(pr, k, kGenMaxDot, nullptr, out_score, out_idx, w, timed_op, st);
   const StreamPlan s = plan_stream(pr.B, pr.N, k);
   auto tile = [&](int n0, int nt, uint64_t* A, long strideA) {
     return launch_mol_f32(pr, kGenMaxDot, nullptr, n0, nt, nullptr, nullptr, 0, nullptr, 0, A, strideA, st);
@@ -765,11 +853,11 @@ int run_maxdot(const DevProb& pr, int k, float* out_score, int32_t* out_idx, cha
   return stream_topk(s, pr.N, w, tile, out_score, out_idx, st);
 }
 
-int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx, char* w, int timed_op,
-                 hipStream_t st) {
+int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx, char* w, size_t have,
+                 int timed_op, hipStream_t st) {
   int rc;
   const int rows = pr.B * pr.P;
-  if (use_dense_lists(pr, kprime)) {
+  if (use_dense_lists(pr, kprime, have)) {
     const DenseListPlan f = plan_dense_lists(pr);
     DenseRows r;
     float* sbuf = reinterpret_cast<float*>(w + f.offS);
@@ -789,7 +877,7 @@ int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx
     return MOL_OK;
   }
   if (per_embd_supported(pr, kprime)) {
-    const PerEmbdPlan f = plan_per_embd(pr, kprime);
+    const PerEmbdPlan f = plan_per_embd(pr, kprime, have);
     const PerEmbdBufs b = per_embd_bufs(f, w);
     uint64_t* fin = reinterpret_cast<uint64_t*>(w + f.offFinal);
     MOL_TIMED_LAUNCH(timed_op, st, launch_per_embd(pr, kprime, f.g, b, st), "per-component top-k'");
@@ -804,7 +892,7 @@ int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx
     MOL_TRY_HIP(launch_decode(fin, kprime, rows, kprime, out_dot, out_idx, st, gate), "decode");
     return MOL_OK;
   }
-  if (use_thresh_per_embd(pr, kprime)) {
+  if (use_thresh_per_embd(pr, kprime) && plan_thresh(pr, kprime).bytes <= have) {
     const ThreshPlan t = plan_thresh(pr, kprime);
     uint32_t* counts = reinterpret_cast<uint32_t*>(w + t.offCnt);
     uint64_t* smp = reinterpret_cast<uint64_t*>(w + t.offSmp);
@@ -833,11 +921,11 @@ int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx
 // Union + dedup of two candidate sets, then MoL top-k over the distinct ids
 // (by -phi when `negate`: the smallest scores first).
 int run_rerank(const DevProb& pr, const int32_t* cand, int C, const int32_t* cand2, int C2, int k,
-               bool negate, float* out_score, int32_t* out_idx, int32_t* out_n_unique, char* w,
+               bool negate, float* out_score, int32_t* out_idx, int32_t* out_n_unique, char* w, size_t have,
                int timed_op, hipStream_t st) {
   int rc;
   const int CT = C + C2;
-  const RerankPlan r = plan_rerank(pr, CT, k);
+  const RerankPlan r = plan_rerank(pr, CT, k, have);
   int32_t* uniq = reinterpret_cast<int32_t*>(w + r.offUniq);
   int32_t* nu = reinterpret_cast<int32_t*>(w + r.offNu);
   MOL_TRY_HIP(launch_dedup(cand, C, cand2, C2, pr.B, pr.N, uniq, nu, out_n_unique, st), "dedup");
@@ -884,23 +972,25 @@ int run_rerank(const DevProb& pr, const int32_t* cand, int C, const int32_t* can
 // MoL scores over G; then the exact top-k over the items whose max_p s_p
 // reaches the bound (RangeDotProduct + BruteForceTopKMoL in one pass).
 int run_two_pass(const DevProb& pr, int k, int mode, float* out_score, int32_t* out_idx,
-                 float* out_bound, char* w, hipStream_t st) {
+                 float* out_bound, char* w, size_t have, hipStream_t st) {
   int rc;
   const TwoPassPlan t = plan_two_pass(pr, k);
+  have -= t.offWork;                 // (checked: at least the least of every phase)
   float* dots = reinterpret_cast<float*>(w + t.offDots);
   int32_t* ids = reinterpret_cast<int32_t*>(w + t.offIdx);
   float* rscore = reinterpret_cast<float*>(w + t.offScore);
   int32_t* ridx = reinterpret_cast<int32_t*>(w + t.offRidx);
   float* bound = reinterpret_cast<float*>(w + t.offBound);
   char* work = w + t.offWork;
-  if ((rc = run_per_embd(pr, k, dots, ids, work, -1, st))) return rc;
+  if ((rc = run_per_embd(pr, k, dots, ids, work, have, -1, st))) return rc;
   const bool smallest = mode == MOL_TWO_PASS_MIN;
   const int kk = smallest ? 1 : k;
-  if ((rc = run_rerank(pr, ids, pr.P * k, nullptr, 0, kk, smallest, rscore, ridx, nullptr, work, -1, st)))
+  if ((rc = run_rerank(pr, ids, pr.P * k, nullptr, 0, kk, smallest, rscore, ridx, nullptr, work, have, -1,
+                       st)))
     return rc;
   // MIN: bound = min over G of phi = -(top-1 of -phi); KTH: the k-th largest
   MOL_TRY_HIP(launch_pick_bound(rscore, kk, kk - 1, smallest ? -1.f : 1.f, pr.B, bound, st), "bound");
-  if ((rc = run_exact(pr, k, bound, out_score, out_idx, work, -1, st))) return rc;
+  if ((rc = run_exact(pr, k, bound, out_score, out_idx, work, have, -1, st))) return rc;
   if (out_bound)
     MOL_TRY_HIP(hipMemcpyAsync(out_bound, bound, sizeof(float) * pr.B, hipMemcpyDeviceToDevice, st),
                 "copy bound");
@@ -984,33 +1074,33 @@ int mol_workspace_size(const mol_problem* prob, int op, int32_t k, int32_t kprim
     case MOL_OP_TOPK_EXACT:
       if ((rc = check_problem(prob, true))) return rc;
       if ((rc = check_k(k, prob->N, "k"))) return rc;
-      *bytes = exact_ws_bytes(dev_prob(prob), k, false);
+      *bytes = exact_ws(dev_prob(prob), k, false).best;
       return MOL_OK;
     case MOL_OP_TOPK_PER_EMBD:
       if ((rc = check_problem(prob, false))) return rc;
       if ((rc = check_k(kprime, prob->N, "kprime"))) return rc;
-      *bytes = per_embd_ws_bytes(dev_prob(prob), kprime);
+      *bytes = per_embd_ws(dev_prob(prob), kprime).best;
       return MOL_OK;
     case MOL_OP_RERANK:
       if ((rc = check_problem(prob, true))) return rc;
       if (k < 1 || k > MOL_MAX_K) return fail(MOL_EINVAL, "k = %d outside [1, %d]", k, MOL_MAX_K);
       if (C < 1 || C > MOL_MAX_C) return fail(MOL_EINVAL, "C = %d outside [1, %d]", C, MOL_MAX_C);
-      *bytes = plan_rerank(dev_prob(prob), C, k).bytes;
+      *bytes = rerank_ws(dev_prob(prob), C, k).best;
       return MOL_OK;
     case MOL_OP_TOPK_MAXDOT:
       if ((rc = check_problem(prob, false))) return rc;
       if ((rc = check_k(k, prob->N, "k"))) return rc;
-      *bytes = maxdot_ws_bytes(dev_prob(prob), k);
+      *bytes = maxdot_ws(dev_prob(prob), k).best;
       return MOL_OK;
     case MOL_OP_TOPK_BOUNDED:
       if ((rc = check_problem(prob, true))) return rc;
       if ((rc = check_k(k, prob->N, "k"))) return rc;
-      *bytes = exact_ws_bytes(dev_prob(prob), k, true);
+      *bytes = exact_ws(dev_prob(prob), k, true).best;
       return MOL_OK;
     case MOL_OP_TOPK_TWO_PASS:
       if ((rc = check_problem(prob, true))) return rc;
       if ((rc = check_two_pass_k(prob, k))) return rc;
-      *bytes = plan_two_pass(dev_prob(prob), k).bytes;
+      *bytes = plan_two_pass(dev_prob(prob), k).ws.best;
       return MOL_OK;
     default:
       return fail(MOL_EINVAL, "unknown op %d", op);
@@ -1047,15 +1137,9 @@ int mol_topk_exact(const mol_problem* prob, int32_t k, float* out_score, int32_t
   if ((rc = check_k(k, prob->N, "k"))) return rc;
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  // A program may keep one workspace, sized for its largest batch.  The dense
-  // form ends where its scores pass kDenseMax, so a smaller batch can ask for
-  // more than the largest one does (8 x 8, d = 64, 2^20 items: 520 MB at 256
-  // queries, 4.7 MB at 1024): without room for it a call takes the lists.
-  const size_t dense = exact_ws_bytes(pr, k, false), least = exact_list_ws_bytes(pr, k);
-  const bool lists = ws_bytes < dense && ws_bytes >= least;
-  if ((rc = check_ws(ws, ws_bytes, lists ? least : dense))) return rc;
-  return run_exact(pr, k, nullptr, out_score, out_idx, static_cast<char*>(ws), MOL_OP_TOPK_EXACT,
-                   static_cast<hipStream_t>(stream), lists);
+  if ((rc = check_ws(ws, ws_bytes, exact_ws(pr, k, false).least))) return rc;
+  return run_exact(pr, k, nullptr, out_score, out_idx, static_cast<char*>(ws), ws_bytes, MOL_OP_TOPK_EXACT,
+                   static_cast<hipStream_t>(stream));
 }
 
 int mol_topk_exact_noalloc(const mol_problem* prob, int32_t k, float* out_score, int32_t* out_idx,
@@ -1065,13 +1149,13 @@ int mol_topk_exact_noalloc(const mol_problem* prob, int32_t k, float* out_score,
   if ((rc = check_k(k, prob->N, "k"))) return rc;
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  const size_t need = exact_list_ws_bytes(pr, k);
+  const size_t need = exact_list_ws(pr, k).least;
   if (need > MOL_NOALLOC_SCRATCH_BYTES)
     return fail(MOL_EWORKSPACE, "this problem needs %zu bytes of scratch; the library holds %zu "
                 "(use mol_topk_exact with a workspace)", need, static_cast<size_t>(MOL_NOALLOC_SCRATCH_BYTES));
   char* w = static_cast<char*>(scratch_ptr());
   if (!w) return MOL_EHIP;
-  return run_exact(pr, k, nullptr, out_score, out_idx, w, MOL_OP_TOPK_EXACT, static_cast<hipStream_t>(stream), true);
+  return run_exact(pr, k, nullptr, out_score, out_idx, w, 0, MOL_OP_TOPK_EXACT, static_cast<hipStream_t>(stream));
 }
 
 int mol_topk_exact_bounded(const mol_problem* prob, int32_t k, const float* bound, float* out_score,
@@ -1082,8 +1166,8 @@ int mol_topk_exact_bounded(const mol_problem* prob, int32_t k, const float* boun
   if (!bound) return fail(MOL_EINVAL, "bound is NULL");
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  if ((rc = check_ws(ws, ws_bytes, exact_ws_bytes(pr, k, true)))) return rc;
-  return run_exact(pr, k, bound, out_score, out_idx, static_cast<char*>(ws), MOL_OP_TOPK_BOUNDED,
+  if ((rc = check_ws(ws, ws_bytes, exact_ws(pr, k, true).least))) return rc;
+  return run_exact(pr, k, bound, out_score, out_idx, static_cast<char*>(ws), ws_bytes, MOL_OP_TOPK_BOUNDED,
                    static_cast<hipStream_t>(stream));
 }
 
@@ -1094,8 +1178,8 @@ int mol_topk_maxdot(const mol_problem* prob, int32_t k, float* out_score, int32_
   if ((rc = check_k(k, prob->N, "k"))) return rc;
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  if ((rc = check_ws(ws, ws_bytes, maxdot_ws_bytes(pr, k)))) return rc;
-  return run_maxdot(pr, k, out_score, out_idx, static_cast<char*>(ws), MOL_OP_TOPK_MAXDOT,
+  if ((rc = check_ws(ws, ws_bytes, maxdot_ws(pr, k).least))) return rc;
+  return run_maxdot(pr, k, out_score, out_idx, static_cast<char*>(ws), ws_bytes, MOL_OP_TOPK_MAXDOT,
                     static_cast<hipStream_t>(stream));
 }
 
@@ -1108,10 +1192,10 @@ int mol_topk_two_pass(const mol_problem* prob, int32_t k, int32_t mode, float* o
     return fail(MOL_EINVAL, "mode = %d is not MOL_TWO_PASS_MIN or MOL_TWO_PASS_KTH", mode);
   if (!out_score || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  if ((rc = check_ws(ws, ws_bytes, plan_two_pass(pr, k).bytes))) return rc;
+  if ((rc = check_ws(ws, ws_bytes, plan_two_pass(pr, k).ws.least))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const EvPair tp = timing_start(st);
-  rc = run_two_pass(pr, k, mode, out_score, out_idx, out_bound, static_cast<char*>(ws), st);
+  rc = run_two_pass(pr, k, mode, out_score, out_idx, out_bound, static_cast<char*>(ws), ws_bytes, st);
   timing_stop(MOL_OP_TOPK_TWO_PASS, tp, st, rc == MOL_OK);
   return rc;
 }
@@ -1123,8 +1207,8 @@ int mol_topk_per_embd(const mol_problem* prob, int32_t kprime, float* out_dot, i
   if ((rc = check_k(kprime, prob->N, "kprime"))) return rc;
   if (!out_dot || !out_idx) return fail(MOL_EINVAL, "output pointer is NULL");
   const DevProb pr = dev_prob(prob);
-  if ((rc = check_ws(ws, ws_bytes, per_embd_ws_bytes(pr, kprime)))) return rc;
-  return run_per_embd(pr, kprime, out_dot, out_idx, static_cast<char*>(ws), MOL_OP_TOPK_PER_EMBD,
+  if ((rc = check_ws(ws, ws_bytes, per_embd_ws(pr, kprime).least))) return rc;
+  return run_per_embd(pr, kprime, out_dot, out_idx, static_cast<char*>(ws), ws_bytes, MOL_OP_TOPK_PER_EMBD,
                       static_cast<hipStream_t>(stream));
 }
 
@@ -1139,9 +1223,9 @@ int mol_rerank(const mol_problem* prob, const int32_t* cand, int32_t C, const in
   if (!cand || !out_score || !out_idx) return fail(MOL_EINVAL, "cand or output pointer is NULL");
   if (C2 > 0 && !cand2) return fail(MOL_EINVAL, "cand2 is NULL with C2 = %d", C2);
   const DevProb pr = dev_prob(prob);
-  if ((rc = check_ws(ws, ws_bytes, plan_rerank(pr, C + C2, k).bytes))) return rc;
+  if ((rc = check_ws(ws, ws_bytes, rerank_ws(pr, C + C2, k).least))) return rc;
   return run_rerank(pr, cand, C, cand2, C2, k, false, out_score, out_idx, out_n_unique, static_cast<char*>(ws),
-                    MOL_OP_RERANK, static_cast<hipStream_t>(stream));
+                    ws_bytes, MOL_OP_RERANK, static_cast<hipStream_t>(stream));
 }
 
 int mol_avg_embed(const mol_problem* prob, void* q_avg, void* x_avg, void* stream) {

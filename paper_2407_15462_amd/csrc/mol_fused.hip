@@ -709,6 +709,13 @@ FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count) {
   return f;
 }
 
+// at most 16 rounds of 256 workgroups, or one range a query group; ranges of at
+// least 64 items
+long fused_dense_redo_flags(int B, int n_count) {
+  const long G = (B + 3l) / 4, blocks = (n_count + 63l) / 64;   // G: most groups of any number of slices
+  return kWaves * std::max(G, std::min(G * blocks, 16l * 256));
+}
+
 template <int PX, int D, int H, int EPI, bool X2, int SL>
 static hipError_t launch_fused_x(const DevProb& pr, const FusedArgs& a, hipStream_t st) {
   using S = FusedShape<PX, D, H, EPI != kEpiMaxDot, SL, EPI != kEpiDense && EPI != kEpiDensePipe>;

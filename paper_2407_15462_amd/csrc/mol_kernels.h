@@ -160,6 +160,8 @@ struct FusedDenseGrid {
   int R = 1, range_len = 0, G = 1;    // item ranges, items per range, query groups
 };
 FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count);
+// flags of any grid of the dense form of up to B queries and n_count items
+long fused_dense_redo_flags(int B, int n_count);
 hipError_t launch_fused_dense(const DevProb& pr, const FusedDenseGrid& f, int n_begin, int n_count, float* phi,
                               long phi_stride, float* bmax, long bmax_stride, int* redo, hipStream_t st);
 
@@ -198,7 +200,8 @@ struct PerEmbdBufs {
 bool per_embd_supported(const DevProb& pr, int kp);
 int per_embd_list_cap(int kp);
 int per_embd_stage_cap(int kp);
-void per_embd_grid(const DevProb& pr, int kp, PerEmbdGrid& g);
+// max_ranges: most item ranges of the threshold scan
+void per_embd_grid(const DevProb& pr, int kp, int max_ranges, PerEmbdGrid& g);
 // the scans (and, for the pruned form, its work list and pass); the lists
 // are then finished by launch_per_embd_select (appending forms) and, gated on
 // ctl[rows] (every list when it is set; always without the appending forms),

@@ -39,6 +39,8 @@
 // could not drop a key), so the bound is exact.
 #include <type_traits>
 
+#include <climits>
+
 #include "mol_tile.h"
 
 namespace mol {
@@ -803,7 +805,7 @@ int per_embd_stage_cap(int kp) {
 // items of one LDS stage (EmbdShape::ST) for width d and list capacity kl
 static int stage_items(int d, int kl, bool small) { return stage_bytes(kl, small) / (2 * d); }
 
-static void scan_grid(const DevProb& pr, int kp, bool scan2, PerEmbdGrid::Scan& sc) {
+static void scan_grid(const DevProb& pr, int kp, bool scan2, int max_ranges, PerEmbdGrid::Scan& sc) {
   const int nvec = pr.B * pr.Pq;
   const int vec_wg = waves_for(per_embd_list_cap(kp)) * 32 * nb_pick(pr.d, scan2, per_embd_small(pr, kp));
   sc.G = (nvec + vec_wg - 1) / vec_wg;
@@ -812,7 +814,7 @@ static void scan_grid(const DevProb& pr, int kp, bool scan2, PerEmbdGrid::Scan& 
   // appending scans), with ranges of at least 512 items
   const bool small = per_embd_small(pr, kp);
   int R = std::max(1, ((small && !scan2 ? 512 : 256) + units - 1) / units);
-  R = std::min(R, std::max(1, pr.N / 512));
+  R = std::min({R, std::max(1, pr.N / 512), max_ranges});
   // whole stages per range: a range's tile walk then covers exactly
   // range_len / 32 tiles, the count the bucket layout is sized for
   const int unit = std::max(128, stage_items(pr.d, per_embd_list_cap(kp), small));
@@ -821,9 +823,9 @@ static void scan_grid(const DevProb& pr, int kp, bool scan2, PerEmbdGrid::Scan& 
   sc.R = (pr.N + sc.range_len - 1) / sc.range_len;
 }
 
-void per_embd_grid(const DevProb& pr, int kp, PerEmbdGrid& g) {
-  scan_grid(pr, kp, false, g.s1);
-  scan_grid(pr, kp, true, g.s2);
+void per_embd_grid(const DevProb& pr, int kp, int max_ranges, PerEmbdGrid& g) {
+  scan_grid(pr, kp, false, INT_MAX, g.s1);
+  scan_grid(pr, kp, true, max_ranges, g.s2);
   const int KL = per_embd_list_cap(kp);
   const int nvec = pr.B * pr.Pq;
   const int ntiles = g.s1.range_len / 32;
