@@ -31,7 +31,12 @@
  * Ordering: every top-k output row is sorted by score descending, ties
  * broken by item index ascending.  Where a row has fewer than k valid items
  * (mol_rerank, mol_topk_exact_bounded) it is padded with index -1 and score
- * -INFINITY.
+ * -INFINITY.  Finite inputs can still score NaN: dot products past the range
+ * of float32, or past 65504 in the float16 chain of the default gating.  Such
+ * an item is ranked behind every number, by index, except by the bf16 kernels
+ * that keep running lists (MoL scores with Pq = 8 and k <= 128, lists and max
+ * dots of their shapes): those never rank it, and pad a row that is left with
+ * fewer than k items.
  *
  * Errors: each entry point validates all arguments on the host before it
  * launches anything.  On error it returns a nonzero mol_status, launches

@@ -757,7 +757,7 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
   r.phi = phi;
   r.phi_stride = f.ld;
   r.L = pr.N;
-  r.skip_neg_inf = mode == kGenBounded;
+  r.rank_nan = !f.fused;
   r.bmax = bmax;
   if (f.fused) {
     for (int b0 = 0; b0 < pr.B; b0 += f.slab) {
@@ -788,7 +788,7 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
                      "score tile");
   }
   if (bmax && !f.dphi)
-    MOL_TRY_HIP(launch_bucket_max(phi, f.ld, pr.B, pr.N, 1.f, bmax, r.bmax_stride, st), "bucket maxima");
+    MOL_TRY_HIP(launch_bucket_max(phi, f.ld, pr.B, pr.N, bmax, r.bmax_stride, st), "bucket maxima");
   MOL_TRY_HIP(launch_topk_dense(r, pr.B, k, out_score, out_idx, st), "dense top-k");
   return MOL_OK;
 }
@@ -873,6 +873,7 @@ int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx
     r.L = pr.N;
     r.bmax = bmax;
     r.bmax_stride = f.bstride;
+    r.rank_nan = !per_embd_supported(pr, kprime);   // (the per-component kernels keep no NaN)
     MOL_TRY_HIP(launch_topk_dense(r, rows, kprime, out_dot, out_idx, st), "list top-k'");
     return MOL_OK;
   }
@@ -958,7 +959,8 @@ int run_rerank(const DevProb& pr, const int32_t* cand, int C, const int32_t* can
     d.row_len = nu;
     d.ids = uniq;
     d.ids_stride = CT;
-    d.sign = negate ? -1.f : 1.f;
+    d.negate = negate;
+    d.rank_nan = !use_fused_rerank(pr, k);
     MOL_TRY_HIP(launch_topk_dense(d, pr.B, k, out_score, out_idx, st), "rerank top-k");
     return MOL_OK;
   }

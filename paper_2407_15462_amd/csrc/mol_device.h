@@ -57,6 +57,11 @@ __device__ __forceinline__ int32_t key_item(uint64_t key) {
   return key == 0 ? -1 : static_cast<int32_t>(~static_cast<uint32_t>(key));
 }
 
+// Score of an excluded column in a dense row (kGenBounded): a NaN that no
+// arithmetic produces, which maxima pass over and the selection never ranks.
+constexpr uint32_t kExcludedBits = 0x7FFFFFFFu;
+__device__ __forceinline__ float excluded_score() { return __uint_as_float(kExcludedBits); }
+
 // Round a float64 value to bf16, nearest-even, returning the bit pattern.
 __device__ __forceinline__ bf16_t f64_to_bf16_rne(double x) {
   uint64_t bits = static_cast<uint64_t>(__double_as_longlong(x));

@@ -61,7 +61,7 @@ struct DotsPhiShape {
 }  // namespace
 
 // phi [B][phi_stride], bmax NULL or [B][bmax_stride] (64-item buckets);
-// BOUNDED: items that cannot reach bound[b] get -inf.
+// BOUNDED: items that cannot reach bound[b] get excluded_score().
 template <int NJ, int WV, int HV, bool BOUNDED, bool X2>
 __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const float* __restrict__ bound, int ny,
                                                          float* __restrict__ phi, long phi_stride,
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const floa
         if (!BOUNDED || __any(keep[0] || keep[1])) mlp.template phi<2>(s, c0, out);
         const int u = g >> 1, ql = q0 + q + u;
         const bool kept = u == 0 ? keep[0] : keep[1];
-        const float v = kept ? (u == 0 ? out[0] : out[1]) : -__builtin_inff();
+        const float v = kept ? (u == 0 ? out[0] : out[1]) : excluded_score();
         const bool mine = (g & 1) == 0 && ql < nq;
         if (mine && live) phi[(b0 + ql) * phi_stride + item] = v;
         if (bmax) {

@@ -276,7 +276,7 @@ __global__ __launch_bounds__(64 * f32_waves<PV>(), 4) void k_mol_f32(
         for (int mu = 0; mu < RUN; ++mu) s[t][mu] = src[mu * TIP];
         out[t] = 0.f;
         if (mode == kGenBounded || mode == kGenMaxDot) {
-          float mx = -__builtin_inff(), mabs = 0.f;
+          float mx = -__builtin_nanf(""), mabs = 0.f;   // (nothing but NaN: NaN, which is kept)
 #pragma unroll
           for (int mu = 0; mu < RUN; ++mu)
             if (RUN * g + mu < P) {
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(64 * f32_waves<PV>(), 4) void k_mol_f32(
         const long b = b0 + q[t];
         const int i = i0 + it[t];
         if (!keep[t]) {
-          if (phi && live[t]) phi[b * phi_stride + i] = -__builtin_inff();
+          if (phi && live[t]) phi[b * phi_stride + i] = excluded_score();
           if (keys) keys[b * key_stride + i] = 0;
         } else {
           if (phi) phi[b * phi_stride + i] = out[t];

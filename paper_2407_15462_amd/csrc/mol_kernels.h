@@ -12,15 +12,19 @@ namespace mol {
 enum GenMode { kGenPhi = 0, kGenBounded = 1, kGenMaxDot = 2, kGenNegPhi = 3, kGenDotKeys = 4 };
 // Items n_begin + i, i < n_count, or (items != NULL) candidate i of query
 // b's list items[b * item_stride ..], item_count[b] of them.  Writes phi
-// (float32) and / or sort keys; an excluded item gets -inf or an empty key.
+// (float32) and / or sort keys; an excluded item gets excluded_score() or an
+// empty key.
 hipError_t launch_mol_f32(const DevProb& pr, int mode, const float* bound, int n_begin, int n_count,
                           const int32_t* items, const int32_t* item_count, long item_stride, float* phi,
                           long phi_stride, uint64_t* keys, long key_stride, hipStream_t st);
 
 // Top-k of dense score rows, decoded (mol_topk.hip): phi [rows][phi_stride],
 // L scores a row (row_len: NULL or valid counts), bmax: NULL or per-bucket
-// maxima (of sign * phi, times sign; rows then hold L scores), ids: NULL or the item of each column.  Rows are
-// ranked by sign * phi; skip_neg_inf: a score of -inf is an excluded column.
+// maxima (not with row_len or negate), ids: NULL or the item of each column.
+// Rows are ranked by phi, or by -phi with negate.  A column of excluded_score()
+// is never ranked.  Any other NaN is ranked by its bit pattern with rank_nan, as
+// the sort keys of the streamed forms are (the NaN that the scoring kernels
+// produce is negative: behind every number), and never without.
 constexpr int kTopkDenseMaxK = 2048;
 struct DenseRows {
   const float* phi = nullptr;
@@ -34,14 +38,14 @@ struct DenseRows {
   int SL = 1;
   const int32_t* ids = nullptr;
   long ids_stride = 0;
-  float sign = 1.f;
-  bool skip_neg_inf = false;
+  bool negate = false;
+  bool rank_nan = false;
 };
 // floats of a row of bucket maxima (and a multiple of 4)
 inline long bucket_row(long L, int SL) { return ((L + 64 * SL - 1) / (64 * SL) * SL + 3) / 4 * 4; }
-// bucket maxima of sign * phi, SL = 1 (rows 16-byte aligned)
-hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L, float sign, float* bmax,
-                             long bmax_stride, hipStream_t st);
+// bucket maxima, SL = 1 (rows 16-byte aligned)
+hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L, float* bmax, long bmax_stride,
+                             hipStream_t st);
 hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_score, int32_t* out_idx, hipStream_t st);
 
 // Component dot products on MFMA for the generic shapes (bf16, d % 32 == 0):
@@ -86,7 +90,7 @@ hipError_t launch_phi_mfma(const DevProb& pr, int mode, const float* bound, int 
 
 // Dots and gating in one kernel (bf16, P_x = 4, P_q 1, 2 or 4, d a multiple of
 // 32, H <= 128): dense scores of the whole corpus, bit-identical to the two
-// kernels above.  bound: NULL, or [B] (kGenBounded: excluded items get -inf);
+// kernels above.  bound: NULL, or [B] (kGenBounded: excluded items get excluded_score());
 // bmax: NULL, or bucket maxima (DenseRows, SL = 1).
 bool dots_phi_supported(const DevProb& pr);
 hipError_t launch_dots_phi(const DevProb& pr, const float* bound, float* phi, long phi_stride, float* bmax,

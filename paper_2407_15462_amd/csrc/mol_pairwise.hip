@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void k_phi_mfma(
     // one lane per item writes
     if (g == 0 && i < n_count) {
       if (!keep) {
-        if (phi && live) phi[b * phi_stride + i] = -__builtin_inff();
+        if (phi && live) phi[b * phi_stride + i] = excluded_score();
         if (keys) keys[b * key_stride + i] = 0;
       } else {
         if (phi) phi[b * phi_stride + i] = v;

@@ -35,7 +35,7 @@ constexpr int kTopHot = 4096;          // buckets collected before their items a
 constexpr int kTopRankMax = 256;       // up to this many keys are ranked by counting, more are sorted
 constexpr uint32_t kTopBinMax = 64;    // keys of one bin of the binned sort
 
-// score image, 0 for "no item" (NaN: never ranked)
+// score image, 0 for NaN (which no bound on the k-th score counts)
 __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float_to_ordered(f) : 0u; }
 
 }  // namespace
@@ -43,16 +43,15 @@ __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float
 // phi [rows][phi_stride] (P lists a query: list p of query b is row p * p_rows
 // + b, written as row b * P + p), L scores a row (row_len: NULL or the valid count of
 // each row); bmax: NULL, or [rows][bmax_stride] bucket maxima; ids: NULL (item
-// = column), or the item of each column [rows][ids_stride]; sign: the rows
-// are ranked by sign * phi, and that is what is written; skip_neg_inf: a score
-// of -inf marks an excluded column.  Rows with fewer than k items are padded
-// with (-inf, -1).
+// = column), or the item of each column [rows][ids_stride]; negate: the rows
+// are ranked by -phi, and that is what is written; rank_nan: see DenseRows.
+// Rows with fewer than k items are padded with (-inf, -1).
 // (two workgroups a CU: at most 64 registers)
 __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P, long p_rows, int L_all,
                                                            const int32_t* __restrict__ row_len,
                                                            const float* __restrict__ bmax, long bmax_stride, int SL,
                                                            const int32_t* __restrict__ ids, long ids_stride, int k,
-                                                           float sign, int skip_neg_inf, float* __restrict__ out_score,
+                                                           int negate, int rank_nan, float* __restrict__ out_score,
                                                            int32_t* __restrict__ out_idx) {
   __shared__ uint64_t buf[kTopCap];
   __shared__ uint32_t hist[256];
@@ -65,11 +64,13 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
   const int L = row_len ? min(row_len[row], L_all) : L_all;
   const float* src = phi + at * phi_stride;
   const int32_t* id = ids ? ids + row * ids_stride : nullptr;
-  const uint32_t none = skip_neg_inf ? float_to_ordered(-__builtin_inff()) : 0u;
-  // image of column i's score: 0 for an excluded one
+  // (a NaN keeps its payload and takes part in the sign)
+  const uint32_t flip = negate ? 0x80000000u : 0u;
+  auto value = [&](float f) { return __uint_as_float(__float_as_uint(f) ^ flip); };
+  // image of a score: 0 for a column that is not ranked
   auto image = [&](float f) {
-    const uint32_t u = score_image(sign * f);
-    return u > none ? u : 0u;
+    const bool ranked = f == f || (rank_nan && __float_as_uint(f) != kExcludedBits);
+    return ranked ? float_to_ordered(value(f)) : 0u;
   };
   // f(index of the first, 4 values, how many are valid) over n floats: four
   // consecutive ones a thread and load, or single ones where those would leave
@@ -112,9 +113,9 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
   // fmaxf passes NaN over)
   float fm = __builtin_nanf("");
   for_values(val, nb, [&](int, const float4& v, int) {
-    fm = fmaxf(fm, fmaxf(fmaxf(sign * v.x, sign * v.y), fmaxf(sign * v.z, sign * v.w)));
+    fm = fmaxf(fm, fmaxf(fmaxf(value(v.x), value(v.y)), fmaxf(value(v.z), value(v.w))));
   });
-  const uint32_t mx = image(sign * fm);
+  const uint32_t mx = score_image(fm);
   // beyond kTopCoarse every value counts by itself: the thread maxima are too
   // few to hold the k-th
   const bool fine = k > kTopCoarse;
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
       const float v[4] = {v4.x, v4.y, v4.z, v4.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const uint32_t im = e < nv ? image(v[e]) : 0u;
+        const uint32_t im = e < nv ? score_image(value(v[e])) : 0u;
         if (im) f(im);
       }
     });
@@ -229,14 +230,14 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
   __syncthreads();
   // the float compare decides almost every value; images decide the rest
   const float Tf = T > float_to_ordered(-__builtin_inff()) ? ordered_to_float(T) : -__builtin_inff();
-  // f(index, image) of the values at or above T of an array
-  auto for_hits = [&](const float* v0, int n, auto&& f) {
+  // f(index, image) of the values at or above T of an array (NaN is looked at)
+  auto for_hits = [&](const float* v0, int n, auto&& image_of, auto&& f) {
     for_values(v0, n, [&](int i, const float4& v4, int nv) {
-      const float v[4] = {sign * v4.x, sign * v4.y, sign * v4.z, sign * v4.w};
-      if (!(v[0] >= Tf || v[1] >= Tf || v[2] >= Tf || v[3] >= Tf)) return;
+      const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+      if (value(v[0]) < Tf && value(v[1]) < Tf && value(v[2]) < Tf && value(v[3]) < Tf) return;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const uint32_t im = e < nv ? image(sign * v[e]) : 0u;
+        const uint32_t im = e < nv ? image_of(v[e]) : 0u;
         if (im >= T) f(i + e, im);
       }
     });
@@ -253,7 +254,9 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
   if (bmax) {
     // the buckets that reach T, then their items, a wave a bucket: the loads
     // of all buckets in flight instead of one bucket's after another's
-    for_hits(val, nb, [&](int i, uint32_t) {
+    // (a bucket of nothing but NaN only where every column counts)
+    const auto bucket_image = [&](float f) { return f == f ? float_to_ordered(f) : rank_nan ? 1u : 0u; };
+    for_hits(val, nb, bucket_image, [&](int i, uint32_t) {
       const uint32_t pos = atomicAdd(&s_hot, 1u);
       if (pos < static_cast<uint32_t>(kTopHot)) hot[pos] = i;
     });
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
         gather(std::integral_constant<int, 1>{});
     }
   }
-  if (hot_n > static_cast<uint32_t>(kTopHot)) for_hits(src, L, collect);
+  if (hot_n > static_cast<uint32_t>(kTopHot)) for_hits(src, L, image, collect);
   __syncthreads();
   uint32_t n = s_count;
   if (n > static_cast<uint32_t>(kTopCap)) {
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
       __syncthreads();
       if (tid < 256) hist[tid] = 0u;
       __syncthreads();
-      for_hits(src, L, [&](int col, uint32_t u) {
+      for_hits(src, L, image, [&](int col, uint32_t u) {
         const uint64_t key = key_of(u, col);
         if (shift == 56 || (key >> (shift + 8)) == (prefix >> (shift + 8)))
           atomicAdd(&hist[static_cast<uint32_t>(key >> shift) & 255u], 1u);
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
     __syncthreads();
     if (tid == 0) s_count = 0u;
     __syncthreads();
-    for_hits(src, L, [&](int col, uint32_t u) {
+    for_hits(src, L, image, [&](int col, uint32_t u) {
       const uint64_t key = key_of(u, col);
       if (key >= prefix) {
         const uint32_t pos = atomicAdd(&s_count, 1u);
@@ -467,25 +470,25 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
 // Bucket maxima of dense rows (SL = 1: 64 consecutive columns a bucket): a
 // lane reads four columns, 16 lanes a bucket.  The rows' strides keep the
 // reads aligned and inside the buffer (a multiple of 4 floats).
-__global__ __launch_bounds__(256) void k_bucket_max(const float* __restrict__ phi, long phi_stride, int L, float sign,
+__global__ __launch_bounds__(256) void k_bucket_max(const float* __restrict__ phi, long phi_stride, int L,
                                                     float* __restrict__ bmax, long bmax_stride) {
   const long row = blockIdx.y;
   const int col = (blockIdx.x * 256 + threadIdx.x) * 4;
   float m = __builtin_nanf("");
   if (col < L) {
     const float4 v = *reinterpret_cast<const float4*>(phi + row * phi_stride + col);
-    m = sign * v.x;
-    if (col + 1 < L) m = fmaxf(m, sign * v.y);
-    if (col + 2 < L) m = fmaxf(m, sign * v.z);
-    if (col + 3 < L) m = fmaxf(m, sign * v.w);
+    m = v.x;
+    if (col + 1 < L) m = fmaxf(m, v.y);
+    if (col + 2 < L) m = fmaxf(m, v.z);
+    if (col + 3 < L) m = fmaxf(m, v.w);
   }
   m = tile::row16_max(m);
-  if ((threadIdx.x & 15) == 0 && col < L) bmax[row * bmax_stride + (col >> 6)] = sign * m;
+  if ((threadIdx.x & 15) == 0 && col < L) bmax[row * bmax_stride + (col >> 6)] = m;
 }
 
-hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L, float sign, float* bmax,
-                             long bmax_stride, hipStream_t st) {
-  hipLaunchKernelGGL(k_bucket_max, dim3((L + 1023) / 1024, rows), dim3(256), 0, st, phi, phi_stride, L, sign, bmax,
+hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L, float* bmax, long bmax_stride,
+                             hipStream_t st) {
+  hipLaunchKernelGGL(k_bucket_max, dim3((L + 1023) / 1024, rows), dim3(256), 0, st, phi, phi_stride, L, bmax,
                      bmax_stride);
   return hipGetLastError();
 }
@@ -494,7 +497,7 @@ hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_sco
                              hipStream_t st) {
   if (k > kTopkDenseMaxK) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_topk_dense, dim3(rows), dim3(kTopThreads), 0, st, r.phi, r.phi_stride, r.P, r.p_rows, r.L, r.row_len, r.bmax,
-                     r.bmax_stride, r.SL, r.ids, r.ids_stride, k, r.sign, r.skip_neg_inf ? 1 : 0, out_score, out_idx);
+                     r.bmax_stride, r.SL, r.ids, r.ids_stride, k, r.negate ? 1 : 0, r.rank_nan ? 1 : 0, out_score, out_idx);
   return hipGetLastError();
 }
 
