@@ -920,7 +920,7 @@ int run_per_embd(const DevProb& pr, int kprime, float* out_dot, int32_t* out_idx
 }
 
 // Union + dedup of two candidate sets, then MoL top-k over the distinct ids
-// (by -phi when `negate`: the smallest scores first).
+// (by -phi when `negate`, for k = 1: the smallest score; the dense rows hold it).
 int run_rerank(const DevProb& pr, const int32_t* cand, int C, const int32_t* cand2, int C2, int k,
                bool negate, float* out_score, int32_t* out_idx, int32_t* out_n_unique, char* w, size_t have,
                int timed_op, hipStream_t st) {
@@ -933,7 +933,6 @@ int run_rerank(const DevProb& pr, const int32_t* cand, int C, const int32_t* can
   // scores as dense rows, or as sort keys where k is beyond those
   float* phi = r.ld ? reinterpret_cast<float*>(w + r.offPhi) : nullptr;
   uint64_t* A = r.ld ? nullptr : reinterpret_cast<uint64_t*>(w + r.s.offA);
-  const int mode = negate && !phi ? kGenNegPhi : kGenPhi;
   if (use_fused_rerank(pr, k)) {   // (k of the dense rows)
     MOL_TIMED_LAUNCH(timed_op, st, launch_rerank(pr, uniq, nu, CT, phi, r.ld, st), "fused rerank");
   } else if (r.sRow) {
@@ -943,12 +942,12 @@ int run_rerank(const DevProb& pr, const int32_t* cand, int C, const int32_t* can
     const long pstride = r.sRow * pr.B;
     MOL_TRY_HIP(launch_dots_mfma_gather(pr, uniq, nu, CT, CT, sbuf, pstride, r.sRow, st), "rerank dots");
     MOL_TIMED_LAUNCH(timed_op, st,
-                     launch_phi_mfma(pr, mode, nullptr, 0, CT, uniq, nu, CT, sbuf, pstride, r.sRow, phi, r.ld, A,
+                     launch_phi_mfma(pr, kGenPhi, nullptr, 0, CT, uniq, nu, CT, sbuf, pstride, r.sRow, phi, r.ld, A,
                                      r.s.strideA, st),
                      "rerank score");
   } else {
     MOL_TIMED_LAUNCH(timed_op, st,
-                     launch_mol_f32(pr, mode, nullptr, 0, CT, uniq, nu, CT, phi, r.ld, A, r.s.strideA, st),
+                     launch_mol_f32(pr, kGenPhi, nullptr, 0, CT, uniq, nu, CT, phi, r.ld, A, r.s.strideA, st),
                      "rerank score");
   }
   if (phi) {

@@ -355,7 +355,6 @@ __global__ __launch_bounds__(64 * f32_waves<PV>(), 4) void k_mol_f32(
               num = fmaf(w, s[t][4 * pt + i], num);
             }
           out[t] = sum_groups(num) * __builtin_amdgcn_rcpf(sum_groups(den));
-          if (mode == kGenNegPhi) out[t] = -out[t];
         }
       }
       // one lane per item writes; slots past the count are cleared keys

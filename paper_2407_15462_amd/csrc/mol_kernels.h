@@ -7,9 +7,9 @@ namespace mol {
 
 // Float32 scoring on f32 MFMAs, any shape and storage type (mol_f32.hip).
 // Score by mode: phi; phi restricted to items whose max_p s_p can reach
-// bound[b]; max_p s_p; -phi; or no score, the component dot products
-// themselves as sort keys in rows (b, p).
-enum GenMode { kGenPhi = 0, kGenBounded = 1, kGenMaxDot = 2, kGenNegPhi = 3, kGenDotKeys = 4 };
+// bound[b]; max_p s_p; or no score, the component dot products themselves as
+// sort keys in rows (b, p).
+enum GenMode { kGenPhi = 0, kGenBounded = 1, kGenMaxDot = 2, kGenDotKeys = 3 };
 // Items n_begin + i, i < n_count, or (items != NULL) candidate i of query
 // b's list items[b * item_stride ..], item_count[b] of them.  Writes phi
 // (float32) and / or sort keys; an excluded item gets excluded_score() or an

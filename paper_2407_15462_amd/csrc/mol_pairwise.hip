@@ -37,12 +37,12 @@ constexpr int kPairQB = 8;         // queries per workgroup
 constexpr int kPairMinIters = 16;
 }  // namespace
 
-// BOUNDED: Algorithm 1's second pass (kGenBounded); otherwise phi, negated
-// when `neg` is set (kGenPhi, kGenNegPhi).  GATHER: per-query candidate
+// BOUNDED: Algorithm 1's second pass (kGenBounded); otherwise phi
+// (kGenPhi).  GATHER: per-query candidate
 // lists (items != NULL) rather than a contiguous range.
 template <int PXV, int HV, bool BOUNDED, bool GATHER, bool X2>
 __global__ __launch_bounds__(256) void k_phi_mfma(
-    DevProb pr, bool neg, const float* __restrict__ bound, int n_begin, int n_count, int steps,
+    DevProb pr, const float* __restrict__ bound, int n_begin, int n_count, int steps,
     const int32_t* __restrict__ items, const int32_t* __restrict__ item_count, long item_stride,
     const float* __restrict__ sbuf, long s_pstride, long s_bstride,
     float* __restrict__ phi, long phi_stride, uint64_t* __restrict__ keys, long key_stride) {
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void k_phi_mfma(
                                                : -__builtin_inff();
       float out[1];
       mlp.template phi<1>(sv, c0, out);
-      v = neg ? -out[0] : out[0];
+      v = out[0];
     }
     // one lane per item writes
     if (g == 0 && i < n_count) {
@@ -207,7 +207,7 @@ static long pair_resident_waves() {
 // whole launch (a wave that lives longer amortises its operand set-up), but
 // no more than one workgroup of 4 waves needs for the whole range.
 template <int PXV, int HV, bool BOUNDED, bool GATHER, bool X2>
-static void launch_phi_mfma_x(long per_query, long groups, long qb, const DevProb& pr, bool neg,
+static void launch_phi_mfma_x(long per_query, long groups, long qb, const DevProb& pr,
                               const float* bound, int n_begin, int n_count, const int32_t* items,
                               const int32_t* item_count, long item_stride, const float* sbuf, long s_pstride,
                               long s_bstride, float* phi, long phi_stride, uint64_t* keys, long key_stride,
@@ -216,40 +216,40 @@ static void launch_phi_mfma_x(long per_query, long groups, long qb, const DevPro
   long steps = std::max<long>((kPairMinIters + qb - 1) / qb, (per_query * groups + waves - 1) / waves);
   steps = std::max<long>(1, std::min<long>(steps, (per_query + 3) / 4));
   const dim3 grid(static_cast<unsigned>((per_query + 4 * steps - 1) / (4 * steps)), static_cast<unsigned>(groups));
-  hipLaunchKernelGGL((k_phi_mfma<PXV, HV, BOUNDED, GATHER, X2>), grid, dim3(256), 0, st, pr, neg, bound, n_begin,
+  hipLaunchKernelGGL((k_phi_mfma<PXV, HV, BOUNDED, GATHER, X2>), grid, dim3(256), 0, st, pr, bound, n_begin,
                      n_count, static_cast<int>(steps), items, item_count, item_stride, sbuf, s_pstride, s_bstride,
                      phi, phi_stride, keys, key_stride);
 }
 
 // the two-term chain where the problem asks for it (MOL_FLAG_BF16X2_GATING)
 template <int PXV, int HV, bool BOUNDED, bool GATHER>
-static void launch_phi_mfma_k(long per_query, long groups, long qb, const DevProb& pr, bool neg,
+static void launch_phi_mfma_k(long per_query, long groups, long qb, const DevProb& pr,
                               const float* bound, int n_begin, int n_count, const int32_t* items,
                               const int32_t* item_count, long item_stride, const float* sbuf, long s_pstride,
                               long s_bstride, float* phi, long phi_stride, uint64_t* keys, long key_stride,
                               hipStream_t st) {
   if (pr.flags & MOL_FLAG_BF16X2_GATING)
-    launch_phi_mfma_x<PXV, HV, BOUNDED, GATHER, true>(per_query, groups, qb, pr, neg, bound, n_begin, n_count,
+    launch_phi_mfma_x<PXV, HV, BOUNDED, GATHER, true>(per_query, groups, qb, pr, bound, n_begin, n_count,
                                                       items, item_count, item_stride, sbuf, s_pstride, s_bstride,
                                                       phi, phi_stride, keys, key_stride, st);
   else
-    launch_phi_mfma_x<PXV, HV, BOUNDED, GATHER, false>(per_query, groups, qb, pr, neg, bound, n_begin, n_count,
+    launch_phi_mfma_x<PXV, HV, BOUNDED, GATHER, false>(per_query, groups, qb, pr, bound, n_begin, n_count,
                                                        items, item_count, item_stride, sbuf, s_pstride, s_bstride,
                                                        phi, phi_stride, keys, key_stride, st);
 }
 
 template <int PXV, int HV, bool BOUNDED>
-static void launch_phi_mfma_m(long per_query, long groups, long qb, const DevProb& pr, bool neg,
+static void launch_phi_mfma_m(long per_query, long groups, long qb, const DevProb& pr,
                               const float* bound, int n_begin, int n_count, const int32_t* items,
                               const int32_t* item_count, long item_stride, const float* sbuf, long s_pstride,
                               long s_bstride, float* phi, long phi_stride, uint64_t* keys, long key_stride,
                               hipStream_t st) {
   if (items)
-    launch_phi_mfma_k<PXV, HV, BOUNDED, true>(per_query, groups, qb, pr, neg, bound, n_begin, n_count, items,
+    launch_phi_mfma_k<PXV, HV, BOUNDED, true>(per_query, groups, qb, pr, bound, n_begin, n_count, items,
                                               item_count, item_stride, sbuf, s_pstride, s_bstride, phi, phi_stride,
                                               keys, key_stride, st);
   else
-    launch_phi_mfma_k<PXV, HV, BOUNDED, false>(per_query, groups, qb, pr, neg, bound, n_begin, n_count, items,
+    launch_phi_mfma_k<PXV, HV, BOUNDED, false>(per_query, groups, qb, pr, bound, n_begin, n_count, items,
                                                item_count, item_stride, sbuf, s_pstride, s_bstride, phi, phi_stride,
                                                keys, key_stride, st);
 }
@@ -261,10 +261,10 @@ static void launch_phi_mfma_t(long per_query, long groups, long qb, const DevPro
                               long s_bstride, float* phi, long phi_stride, uint64_t* keys, long key_stride,
                               hipStream_t st) {
   if (mode == kGenBounded)
-    launch_phi_mfma_m<PXV, HV, true>(per_query, groups, qb, pr, false, bound, n_begin, n_count, items, item_count,
+    launch_phi_mfma_m<PXV, HV, true>(per_query, groups, qb, pr, bound, n_begin, n_count, items, item_count,
                                      item_stride, sbuf, s_pstride, s_bstride, phi, phi_stride, keys, key_stride, st);
   else
-    launch_phi_mfma_m<PXV, HV, false>(per_query, groups, qb, pr, mode == kGenNegPhi, nullptr, n_begin, n_count,
+    launch_phi_mfma_m<PXV, HV, false>(per_query, groups, qb, pr, nullptr, n_begin, n_count,
                                       items, item_count, item_stride, sbuf, s_pstride, s_bstride, phi, phi_stride,
                                       keys, key_stride, st);
 }

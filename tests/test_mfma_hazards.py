@@ -10,7 +10,8 @@ from mfma_hazards import early_reads
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2407_15462_amd", "csrc")
-SOURCES = ["mol_fused.hip", "mol_rerank.hip", "mol_pairwise.hip", "mol_per_embd.hip", "mol_dots.hip"]
+SOURCES = ["mol_fused.hip", "mol_rerank.hip", "mol_pairwise.hip", "mol_per_embd.hip", "mol_dots.hip",
+           "mol_f32.hip", "mol_dots_phi.hip"]
 HIPCC = "/opt/rocm/bin/hipcc"
 
 
