@@ -1,11 +1,14 @@
 // Top-k of dense float32 score rows (Definition 1's selection step), one
 // workgroup per row, straight to the decoded outputs.
 //
-// Every thread takes the maximum of its own share of the row (1024 disjoint
-// buckets; for k > 512 every bucket of bmax, or score, counts by itself).  k
-// buckets whose maxima reach T hold k items scoring at least T, so T = the
-// k-th largest bucket maximum bounds the row's k-th score from below, and
-// about k + k^2 / 2048 items of the row reach it: those are collected in LDS,
+// Every thread takes the maximum of its own share of the row (256 or 1024
+// disjoint buckets; for k beyond half of them every bucket of bmax, or score,
+// counts by itself).  k buckets whose maxima reach T hold k items scoring at
+// least T, so T = the k-th largest bucket maximum bounds the row's k-th score
+// from below.  Of M buckets, k hold one of the best -M ln(1 - k / M) scores in
+// a random order, so about that many items of the row reach T: 105 for k = 100
+// of 1024 buckets, 1.65 k where the kernel's rules leave the fewest, M = 1.5 k
+// (3,375 of the list's 4,096 slots at k = 2048).  Those are collected in LDS,
 // ranked by counting (long lists inside bins of the score range) and written
 // out.  A row whose items reaching T exceed the LDS list (massive ties, an
 // adversarial order) is finished by a radix search over its 64-bit sort keys,
@@ -28,10 +31,7 @@ namespace mol {
 
 namespace {
 
-constexpr int kTopThreads = 1024;
-constexpr int kTopCap = 4096;          // keys held in LDS
-constexpr int kTopCoarse = 512;        // largest k ranked by the threads' maxima
-constexpr int kTopHot = 4096;          // buckets collected before their items are read
+constexpr int kTopWhole = 128;          // rows of up to this many scores are ranked without a threshold
 constexpr int kTopRankMax = 256;       // up to this many keys are ranked by counting, more are sorted
 constexpr uint32_t kTopBinMax = 64;    // keys of one bin of the binned sort
 
@@ -46,13 +46,18 @@ __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float
 // = column), or the item of each column [rows][ids_stride]; negate: the rows
 // are ranked by -phi, and that is what is written; rank_nan: see DenseRows.
 // Rows with fewer than k items are padded with (-inf, -1).
-// (two workgroups a CU: at most 64 registers)
-__global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P, long p_rows, int L_all,
+// NT threads a row.  (1024: two workgroups a CU, at most 64 registers.)
+template <int NT>
+__global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P, long p_rows, int L_all,
                                                            const int32_t* __restrict__ row_len,
                                                            const float* __restrict__ bmax, long bmax_stride, int SL,
                                                            const int32_t* __restrict__ ids, long ids_stride, int k,
                                                            int negate, int rank_nan, float* __restrict__ out_score,
                                                            int32_t* __restrict__ out_idx) {
+  constexpr int kTopThreads = NT;
+  constexpr int kTopCap = 4 * NT;        // keys held in LDS
+  constexpr int kTopCoarse = NT / 2;     // largest k ranked by the threads' maxima
+  constexpr int kTopHot = 4 * NT;        // buckets collected before their items are read
   __shared__ uint64_t buf[kTopCap];
   __shared__ uint32_t hist[256];
   __shared__ int hot[kTopHot];
@@ -202,14 +207,14 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
     }
     __syncthreads();
   };
-  if (nonzero >= static_cast<uint32_t>(k)) {
+  if (nonzero >= static_cast<uint32_t>(k) && L > kTopWhole) {   // (a short row is ranked whole)
     uint32_t kk = static_cast<uint32_t>(k);
     int bits = diff ? 32 - __clz(static_cast<int>(diff)) : 0;   // low bits that may differ
     T = bits >= 32 ? 0u : s_hi >> bits << bits;
     for (int pass = 0; pass < 3 && bits > 0; ++pass) {
       const int shift = max(0, bits - 8);
       __syncthreads();
-      if (tid < 256) hist[tid] = 0u;
+      for (int i = tid; i < 256; i += NT) hist[i] = 0u;
       __syncthreads();
       for_images([&](uint32_t im) {
         if (bits >= 32 || (im >> bits) == (T >> bits))
@@ -317,7 +322,7 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
     uint32_t kk = static_cast<uint32_t>(k);
     for (int shift = 56; shift >= 0; shift -= 8) {
       __syncthreads();
-      if (tid < 256) hist[tid] = 0u;
+      for (int i = tid; i < 256; i += NT) hist[i] = 0u;
       __syncthreads();
       for_hits(src, L, image, [&](int col, uint32_t u) {
         const uint64_t key = key_of(u, col);
@@ -356,7 +361,8 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
     static_assert(kTopCap == kTopHot && kTopCap == 4 * kTopThreads, "four keys and four bins a thread");
     uint32_t* cnt = reinterpret_cast<uint32_t*>(hot);
     const uint32_t span = max(s_hi, T) - T;
-    const int sh = max(0, 20 - __clz(static_cast<int>(span | 1u)));   // span >> sh < kTopHot = 2^12
+    constexpr int kBinBits = 31 - __builtin_clz(kTopHot);
+    const int sh = max(0, 32 - kBinBits - __clz(static_cast<int>(span | 1u)));   // span >> sh < kTopHot
 #pragma unroll
     for (int j = 0; j < 4; ++j) cnt[tid + j * kTopThreads] = 0u;
     if (tid == 0) s_bin = 0u;
@@ -421,8 +427,8 @@ __global__ __launch_bounds__(kTopThreads, 8) void k_topk_dense(const float* __re
   };
   if (ni <= kTopRankMax) {
     // a key's rank is the number of larger ones (keys are distinct)
-    if (tid < ni) {
-      const uint64_t key = buf[tid];
+    for (int i = tid; i < ni; i += NT) {
+      const uint64_t key = buf[i];
       int rank = 0;
       int j = 0;
       for (; j + 8 <= ni; j += 8) {
@@ -493,10 +499,25 @@ hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L,
   return hipGetLastError();
 }
 
+// Threads a row, for k <= 128 (the smaller workgroup's coarse threshold).  With
+// more rows than the chip holds of the large workgroups (two a CU), the small
+// ones (eight a CU) give every CU more rows in flight; rows of up to four
+// values a thread gain by their cheaper barriers at any count.  Top-10, the
+// dots before it included, 1024 -> 256 threads: 32 rows of 1000 13.4 -> 12.2
+// us, of 8192 17.9 -> 16.8, 32 rows of 8192 and k = 128 19.9 -> 23.3 (left
+// large); 600 rows of 8192 40.8 -> 32.7, 2000 of 16,000 104 -> 100, 5000 of 300
+// 79 -> 30, 20,000 of 1000 314 -> 100; 1000 of 60,000 (bucket maxima) 90 -> 80.
+constexpr int kTopSmall = 256, kTopLarge = 1024;
+static int topk_threads(int rows, int L, int k) {
+  return k <= kTopSmall / 2 && (L <= 4 * kTopSmall || rows > 512) ? kTopSmall : kTopLarge;
+}
+
 hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_score, int32_t* out_idx,
                              hipStream_t st) {
   if (k > kTopkDenseMaxK) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_topk_dense, dim3(rows), dim3(kTopThreads), 0, st, r.phi, r.phi_stride, r.P, r.p_rows, r.L, r.row_len, r.bmax,
+  const int nt = topk_threads(rows, r.L, k);
+  auto kern = nt == kTopSmall ? &k_topk_dense<kTopSmall> : &k_topk_dense<kTopLarge>;
+  hipLaunchKernelGGL(kern, dim3(rows), dim3(nt), 0, st, r.phi, r.phi_stride, r.P, r.p_rows, r.L, r.row_len, r.bmax,
                      r.bmax_stride, r.SL, r.ids, r.ids_stride, k, r.negate ? 1 : 0, r.rank_nan ? 1 : 0, out_score, out_idx);
   return hipGetLastError();
 }

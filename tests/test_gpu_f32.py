@@ -123,3 +123,26 @@ def test_dense_topk_is_exact(N, k, ties):
     torch.cuda.synchronize()
     ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
     assert torch.equal(s, ws[:, :k]) and torch.equal(i.long(), wi[:, :k])
+
+
+# both workgroup sizes of the selection: rows up to four values a thread of the
+# small one and more, few and many rows, k around half its threads, with and
+# without bucket maxima; rows ranked whole and just not; more tied items than
+# the small list holds (the radix finish)
+@pytest.mark.parametrize("B,N,k,ties", [
+    (2, 128, 128, 0), (2, 129, 128, 0), (5, 1024, 128, 0), (5, 1025, 128, 0), (5, 1024, 129, 0), (513, 1025, 128, 0),
+    (512, 1025, 1, 0), (600, 3001, 129, 0), (600, 16383, 128, 0), (520, 20011, 100, 0), (520, 20011, 10, 4000),
+    (600, 2000, 100, 1500), (3, 1000, 128, 900),
+])
+def test_dense_topk_workgroups(B, N, k, ties):
+    log(f"[dense topk] B={B} N={N} k={k} ties={ties}")
+    prob, t = _problem(B, N, 2, 2, 16, 16, torch.float32, seed=N + k)
+    if ties:
+        at = torch.randperm(N, generator=torch.Generator().manual_seed(1))[:ties].cuda()
+        t[1][:, at] = t[1][:, at[:1]]
+        t[3][at] = t[3][at[:1]]
+    phi = mol.score(prob)
+    s, i = mol.topk_exact(prob, k)
+    torch.cuda.synchronize()
+    ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
+    assert torch.equal(s, ws[:, :k]) and torch.equal(i.long(), wi[:, :k])
