@@ -12,8 +12,11 @@
 // zero), which leaves them in the run layout of mol_tile.h, and the shared
 // MFMA epilogue evaluates the gating MLP, softmax and phi.  The scores are
 // stored densely, one row per query, and ranked by k_topk_dense (running lists
-// per wave and their merge: 32 x 14,800 candidates 132 -> 117 us, 1024 x 8192
-// 1323 -> 1376 us).
+// per wave and their merge, 8 x 8, d = 64, k = 10, dedup included -> now: 8 x
+// 8192 candidates 91 -> 53 us, 64 x 8192 130 -> 116, 1024 x 8192 1211 -> 1197,
+// 2048 x 200 119 -> 104).
+#include <type_traits>
+
 #include "mol_tile.h"
 
 namespace mol {
@@ -34,14 +37,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
   // of component px, K block kk at byte 16 i (a direct global -> LDS copy)
   extern __shared__ __attribute__((aligned(16))) unsigned char sGather[];
 
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int c = lane & 15, g = lane >> 4;
   const int base = lane_base(g, PX);
   const long wid = static_cast<long>(blockIdx.x) * kWaves + wave;
   if (wid >= static_cast<long>(pr.B) * nchunks) return;     // whole wave exits
   const int b = static_cast<int>(wid / nchunks), j = static_cast<int>(wid % nchunks);
-  const int nu = n_unique[b];
+  const int nu = __builtin_amdgcn_readfirstlane(n_unique[b]);
   const int i0 = j * chunk, i1 = min(nu, i0 + chunk);
+  if (i0 >= i1) return;                                     // no candidates left
   const int N = pr.N;
   const bf16_t* X = static_cast<const bf16_t*>(pr.X);
   const bf16_t* Q = static_cast<const bf16_t*>(pr.Q);
@@ -71,14 +75,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
   // operands by direct global -> LDS copies into the wave's buffer (read
   // back into registers at the start of the step, after which the next
   // step's copies are issued into it), the item logits a_x into registers by
-  // PT loads behind the copies.  (The id load behind those is clamped at once,
-  // for which the compiler waits before the step's MFMAs, copies included: the
-  // gathers of a wave run under the other wave of its SIMD, not under its own
-  // chain.)
-  unsigned char* gbuf = sGather + __builtin_amdgcn_readfirstlane(wave) * (PX * KD * 1024);
-  auto item_at = [&](int pos) { return pos < i1 ? min(max(ids[pos], 0), N - 1) : 0; };   // ids are in range
+  // PT loads behind the copies.  The id of the step after that is loaded
+  // before the copies, from a position that is always valid, and the last step
+  // is outside the loop: nothing waits between the copies and the end of the
+  // step's chain.  (With the id clamped right behind its load, and one store of
+  // 16 scores a step, the compiler's waits drained the copies before the MFMAs
+  // and the store behind them: 1024 x 8192 candidates of 8 x 4, d = 64 697 ->
+  // 645 us, of 8 x 8 1257 -> 1197, dedup and selection included.)
+  unsigned char* gbuf = sGather + wave * (PX * KD * 1024);
+  auto id_at = [&](int pos) { return ids[min(pos, i1 - 1)]; };
   float4 axn[PT];
-  auto gather = [&](int it) {
+  auto gather = [&](int id) {
+    const int it = min(max(id, 0), N - 1);                  // ids are in range
 #pragma unroll
     for (int px = 0; px < PX; ++px)
 #pragma unroll
@@ -89,16 +97,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
     for (int pt = 0; pt < PT; ++pt)
       axn[pt] = *reinterpret_cast<const float4*>(pr.a_x + static_cast<long>(it) * P + base + 4 * pt);
   };
-  int item_n = item_at(i0 + c);
-  if (i0 < i1) gather(item_n);
-  int item_nn = item_at(i0 + 16 + c);
-  for (int s0 = i0; s0 < i1; s0 += 16) {
-    const int pos = s0 + c;
-    const bool ok = pos < i1;
-    // this step's copies have landed: every gather ends in PT a_x loads, and
-    // only those may be outstanding (an id load or a store behind them makes
-    // the wait stricter, but a chunk of one step has neither); read the
-    // operands, then refill the buffer
+  const int id_first = id_at(i0 + c);
+  int id_next = id_at(i0 + 16 + c);
+  gather(id_first);
+  float out = 0.f;           // of candidate 64 u + lane of the chunk, u steps of four
+  auto step = [&](int s0, auto last) {
+    constexpr bool LAST = decltype(last)::value;
+    // this step's copies have landed: every gather ends in exactly PT a_x
+    // loads, and only those may be outstanding (a store behind them makes the
+    // wait stricter); read the operands, then refill the buffer
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(PT));
     asm volatile("" ::: "memory");
@@ -113,10 +120,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
     for (int pt = 0; pt < PT; ++pt)
       c0[0][pt] = f32x4_t{kLog2e * axn[pt].x, kLog2e * axn[pt].y, kLog2e * axn[pt].z, kLog2e * axn[pt].w} + cbf[pt];
     wave_lds_sync();
-    if (s0 + 16 < i1) {
-      item_n = item_nn;
-      gather(item_n);
-      item_nn = item_at(s0 + 32 + c);
+    if constexpr (!LAST) {
+      const int id = id_next;
+      id_next = id_at(s0 + 32 + c);
+      gather(id);
     }
     f32x4_t acc1[PX];
 #pragma unroll
@@ -131,8 +138,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_mol_rerank(
     for (int mu = 0; mu < RUN; ++mu) s[0][mu] = acc1[mu % PX][2 * (mu / PX)];
     float phi[1];
     mlp.template phi<1>(s, c0, phi);
-    if (g == 0 && ok) row[pos] = phi[0];
-  }
+    // lane group g keeps the scores of every fourth step, and one store of 64
+    // scores follows four steps
+    const int t = (s0 - i0) >> 4;
+    if ((t & 3) == g) out = phi[0];
+    if (LAST || (t & 3) == 3) {
+      const int pos = i0 + 64 * (t >> 2) + lane;
+      if (pos < i1) row[pos] = out;
+    }
+  };
+  int s0 = i0;
+  for (; s0 + 16 < i1; s0 += 16) step(s0, std::false_type{});
+  step(s0, std::true_type{});
 }
 
 // ---------------------------------------------------------------------------

@@ -49,3 +49,32 @@ def copy_waits(asm: str, kernel: str) -> List[Tuple[str, int, int]]:
         assert younger and waits, name
         out.append((name, max(int(w) for w in waits), min(younger)))
     return out
+
+
+def copy_drains(asm: str, kernel: str) -> List[Tuple[str, int]]:
+    """(function, number of runs of copies that a vector-memory wait follows
+    before the block's last MFMA) where the copies and MFMAs share a block."""
+    out = []
+    for func in re.split(r"\n(?=_Z\w+:)", asm)[1:]:
+        func = func.split(".Lfunc_end")[0]
+        name = func.split(":")[0]
+        if kernel not in name:
+            continue
+        blocks, blk = [], []
+        for s in _lines(func):
+            if s.startswith(".LBB") or s.split()[0].startswith(("s_cbranch", "s_branch", "s_endpgm")):
+                blocks.append(blk)
+                blk = []
+            else:
+                blk.append(s)
+        shared, drained = 0, 0
+        for blk in blocks:
+            copies = [i for i, s in enumerate(blk) if s.startswith("global_load_lds")]
+            mfmas = [i for i, s in enumerate(blk) if s.startswith("v_mfma")]
+            if not copies or not mfmas:
+                continue
+            shared += 1
+            drained += any(s.startswith("s_waitcnt") and "vmcnt" in s for s in blk[copies[0]:mfmas[-1]])
+        assert shared, name
+        out.append((name, drained))
+    return out
