@@ -151,11 +151,14 @@ __global__ __launch_bounds__(1024) void k_dedup(const int32_t* __restrict__ cand
     int32_t ids[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      ids[u] = -1;
+      if (i0 - tid + u * kDedupBins >= CT) continue;          // uniform: a short set takes one load
       const int i = min(i0 + u * kDedupBins, CT - 1);
       ids[u] = i < C ? cand[b * C + i] : cand2[b * C2 + (i - C)];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      if (i0 - tid + u * kDedupBins >= CT) break;
       const int32_t id = i0 + u * kDedupBins < CT ? ids[u] : -1;
       if (id < 0 || id >= N) continue;
       uint32_t h = (static_cast<uint32_t>(id) * 0x9E3779B1u) >> (32 - cap_log2);
