@@ -296,7 +296,7 @@ DensePlan plan_dense(const DevProb& pr, int k, DenseBy by) {
   size_t off = align_up(4ul * f.slab * f.ld);
   if (by == kByFused) {
     f.fused = true;
-    f.g = fused_dense_grid(query_slab(pr, 0, f.slab), pr.N);
+    f.g = fused_dense_grid(query_slab(pr, 0, f.slab), pr.N, use_buckets(pr.N, k));
     f.offRedo = off;
     off = align_up(off + 4ul * fused_dense_redo_flags(f.slab, pr.N));
   }
@@ -645,7 +645,7 @@ bool prefer_dense(const DevProb& pr, int k, bool bounded) {
   const double lists = (static_cast<long>(R) * G + 255) / 256 * (len + 20.0 * k);
   double dense = 0;
   for (int b0 = 0; b0 < pr.B; b0 += slab) {
-    const FusedDenseGrid g = fused_dense_grid(query_slab(pr, b0, std::min(slab, pr.B - b0)), pr.N);
+    const FusedDenseGrid g = fused_dense_grid(query_slab(pr, b0, std::min(slab, pr.B - b0)), pr.N, use_buckets(pr.N, k));
     dense += (static_cast<long>(g.R) * g.G + 255) / 256 * (g.range_len / g.SL + 32.0) + 180.0;
   }
   return dense < 0.98 * lists;
@@ -762,7 +762,7 @@ int run_dense(const DevProb& pr, int k, int mode, const float* bound, float* out
   if (f.fused) {
     for (int b0 = 0; b0 < pr.B; b0 += f.slab) {
       const DevProb ps = query_slab(pr, b0, std::min(f.slab, pr.B - b0));
-      const FusedDenseGrid g = ps.B == f.slab ? f.g : fused_dense_grid(ps, pr.N);
+      const FusedDenseGrid g = ps.B == f.slab ? f.g : fused_dense_grid(ps, pr.N, bmax != nullptr);
       r.SL = g.SL;
       r.bmax_stride = bucket_row(pr.N, g.SL);
       MOL_TIMED_LAUNCH(timed_op, st,
@@ -1119,7 +1119,7 @@ int mol_score(const mol_problem* prob, int32_t n_begin, int32_t n_count, float* 
   const DevProb pr = dev_prob(prob);
   if (fused_supported(pr, 1)) {
     MOL_TIMED_LAUNCH(MOL_OP_SCORE, st,
-                     launch_fused_dense(pr, fused_dense_grid(pr, n_count), n_begin, n_count, phi, n_count, nullptr, 0,
+                     launch_fused_dense(pr, fused_dense_grid(pr, n_count, false), n_begin, n_count, phi, n_count, nullptr, 0,
                                         nullptr, st),
                      "mol_score (fused)");
     return MOL_OK;

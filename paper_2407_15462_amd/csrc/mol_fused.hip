@@ -683,12 +683,14 @@ void fused_grid(const DevProb& pr, int n_count, int& R, int& range_len, int& G, 
 // about 8 steps): a batch of 1201 is 76 groups, and 3 ranges each left 28 of
 // 256 CUs idle (exact top-50 of 100,003 items 3.74 ms; 10 rounds of 34 ranges
 // 3.05 ms).  Multiples of 8 are preferred at equal cost: the groups sharing a
-// range then run on one XCD and meet in its L2.
-FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count) {
+// range then run on one XCD and meet in its L2.  Ranges are whole bucket blocks
+// with bucket maxima, else whole tiles.
+FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count, bool buckets) {
   FusedDenseGrid f;
   const bool sl4 = pr.Px * 64l * (2 * pr.d + 32) * kRing <= 150 * 1024;   // X and a_x stages of 64 items
   f.SL = pr.B <= 4 && sl4 ? 4 : pr.B <= 8 ? 2 : 1;
-  const int qwg = 2 * kWaves / f.SL, unit = 64 * f.SL;
+  const int qwg = 2 * kWaves / f.SL, unit = buckets ? 64 * f.SL : f.SL == 4 ? 64 : 32;
+  const long steps = unit / (16 * f.SL);
   f.G = (pr.B + qwg - 1) / qwg;
   const int blocks = (n_count + unit - 1) / unit;
   long best = -1;
@@ -699,7 +701,7 @@ FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count) {
       const int len = (blocks + R - 1) / R;                 // units of a range
       R = (blocks + len - 1) / len;
       const long waves = (static_cast<long>(R) * f.G + 255) / 256;
-      const long cost = waves * (4l * len + 8) * (R % 8 == 0 || R == 1 || f.G == 1 ? 100 : 101);
+      const long cost = waves * (steps * len + 8) * (R % 8 == 0 || R == 1 || f.G == 1 ? 100 : 101);
       if (best < 0 || cost < best) {
         best = cost;
         f.R = R;
@@ -710,9 +712,9 @@ FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count) {
 }
 
 // at most 16 rounds of 256 workgroups, or one range a query group; ranges of at
-// least 64 items
+// least 32 items
 long fused_dense_redo_flags(int B, int n_count) {
-  const long G = (B + 3l) / 4, blocks = (n_count + 63l) / 64;   // G: most groups of any number of slices
+  const long G = (B + 3l) / 4, blocks = (n_count + 31l) / 32;   // G: most groups of any number of slices
   return kWaves * std::max(G, std::min(G * blocks, 16l * 256));
 }
 

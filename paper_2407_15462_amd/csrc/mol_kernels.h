@@ -163,7 +163,7 @@ struct FusedDenseGrid {
   int SL = 1;                         // slices
   int R = 1, range_len = 0, G = 1;    // item ranges, items per range, query groups
 };
-FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count);
+FusedDenseGrid fused_dense_grid(const DevProb& pr, int n_count, bool buckets);
 // flags of any grid of the dense form of up to B queries and n_count items
 long fused_dense_redo_flags(int B, int n_count);
 hipError_t launch_fused_dense(const DevProb& pr, const FusedDenseGrid& f, int n_begin, int n_count, float* phi,
