@@ -499,17 +499,27 @@ hipError_t launch_bucket_max(const float* phi, long phi_stride, int rows, int L,
   return hipGetLastError();
 }
 
-// Threads a row, for k <= 128 (the smaller workgroup's coarse threshold).  With
-// more rows than the chip holds of the large workgroups (two a CU), the small
-// ones (eight a CU) give every CU more rows in flight; rows of up to four
-// values a thread gain by their cheaper barriers at any count.  Top-10, the
-// dots before it included, 1024 -> 256 threads: 32 rows of 1000 13.4 -> 12.2
-// us, of 8192 17.9 -> 16.8, 32 rows of 8192 and k = 128 19.9 -> 23.3 (left
-// large); 600 rows of 8192 40.8 -> 32.7, 2000 of 16,000 104 -> 100, 5000 of 300
-// 79 -> 30, 20,000 of 1000 314 -> 100; 1000 of 60,000 (bucket maxima) 90 -> 80.
+// Threads a row.  With more rows than the chip holds of the large workgroups
+// (two a CU), the small ones (eight a CU) give every CU more rows in flight;
+// rows of up to four values a thread gain by their cheaper barriers at any
+// count, rows of up to 3,072 scores from more than one row a CU on.  Longer
+// rows only for k <= 128, the small workgroup's coarse threshold; rows that its
+// list holds whole up to k = 512, while its share of the ranking stays the
+// smaller part.
+// Top-10, the dots before it included, 1024 -> 256 threads: 32 rows of 1000
+// 13.4 -> 12.2 us, of 2196 15.4 -> 16.4 (left large); 300 rows of 2196 27.6 ->
+// 26.2, of 4096 36.1 -> 35.7 and for k = 128 38.2 -> 38.9 (left large); 600 of
+// 8192 40.8 -> 32.7, 2000 of 16,000 104 -> 100, 5000 of 300 79 -> 30, 20,000 of
+// 1000 314 -> 100; 1000 of 60,000 (bucket maxima) 90 -> 80.
+// k of L whole rows, the same way: 3000 rows, 172 of 172 69.5 -> 36.9 us, 200 of
+// 700 99.5 -> 67.6, 512 of 1000 122 -> 94; 800 rows, 512 of 1000 44.4 -> 40.5,
+// 600 of 1000 48 -> 53; 300 rows, 200 of 700 20.5 -> 19.2, 512 of 1000 26.2 ->
+// 30.2 (these three left large).
 constexpr int kTopSmall = 256, kTopLarge = 1024;
 static int topk_threads(int rows, int L, int k) {
-  return k <= kTopSmall / 2 && (L <= 4 * kTopSmall || rows > 512) ? kTopSmall : kTopLarge;
+  const bool whole = L <= 4 * kTopSmall, many = rows > 512 || (rows > 256 && L <= 3 * kTopLarge);
+  if (k <= kTopSmall / 2) return whole || many ? kTopSmall : kTopLarge;
+  return whole && rows > 512 && k <= 2 * kTopSmall ? kTopSmall : kTopLarge;
 }
 
 hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_score, int32_t* out_idx,

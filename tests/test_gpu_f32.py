@@ -132,7 +132,9 @@ def test_dense_topk_is_exact(N, k, ties):
 @pytest.mark.parametrize("B,N,k,ties", [
     (2, 128, 128, 0), (2, 129, 128, 0), (5, 1024, 128, 0), (5, 1025, 128, 0), (5, 1024, 129, 0), (513, 1025, 128, 0),
     (512, 1025, 1, 0), (600, 3001, 129, 0), (600, 16383, 128, 0), (520, 20011, 100, 0), (520, 20011, 10, 4000),
-    (600, 2000, 100, 1500), (3, 1000, 128, 900),
+    (600, 2000, 100, 1500), (3, 1000, 128, 900), (513, 172, 172, 0), (513, 1024, 512, 0), (513, 1024, 513, 0),
+    (512, 1024, 200, 0), (600, 1000, 300, 900), (513, 1025, 200, 0), (257, 3072, 128, 0),
+    (257, 3073, 128, 0), (256, 3072, 10, 0), (300, 3000, 50, 1200),
 ])
 def test_dense_topk_workgroups(B, N, k, ties):
     log(f"[dense topk] B={B} N={N} k={k} ties={ties}")
