@@ -10,9 +10,15 @@
 // of 1024 buckets, 1.65 k where the kernel's rules leave the fewest, M = 1.5 k
 // (3,375 of the list's 4,096 slots at k = 2048).  Those are collected in LDS,
 // ranked by counting (long lists inside bins of the score range) and written
-// out.  A row whose items reaching T exceed the LDS list (massive ties, an
-// adversarial order) is finished by a radix search over its 64-bit sort keys,
-// 8 bits a pass.
+// out.  A row whose items reaching T exceed the LDS list (massive ties, as a
+// query of zeros makes them, or an adversarial order) is finished by a radix
+// search over its 64-bit sort keys, 8 bits a pass, that begins at the bits in
+// which they can differ, counts the lanes of one bin with one add, ends where
+// the list holds the rest, and with nothing but ties above reads only the
+// buckets that hold the first k of them.  (All 64 bits, one add a lane, and every
+// score a pass: 32 rows of 100,000 equal scores 721 us, now 169, with the chunked
+// radix selection of keys 257; one query of zeros against 2^20 items of 8 x 8, d
+// = 64 6,460 us in all, now 286, with per-range lists 653.)
 //
 // What bounds it: one read of the row at a workgroup's rate (about 100 GB/s)
 // and a dozen barriers.  With per-bucket maxima from the kernel that scored
@@ -32,8 +38,8 @@ namespace mol {
 namespace {
 
 constexpr int kTopWhole = 128;          // rows of up to this many scores are ranked without a threshold
-constexpr int kTopRankMax = 256;       // up to this many keys are ranked by counting, more are sorted
-constexpr uint32_t kTopBinMax = 64;    // keys of one bin of the binned sort
+constexpr int kTopRankMax = 256;        // up to this many keys are ranked by counting, more are sorted
+constexpr uint32_t kTopBinMax = 64;     // keys of one bin of the binned sort
 
 // score image, 0 for NaN (which no bound on the k-th score counts)
 __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float_to_ordered(f) : 0u; }
@@ -43,21 +49,22 @@ __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float
 // phi [rows][phi_stride] (P lists a query: list p of query b is row p * p_rows
 // + b, written as row b * P + p), L scores a row (row_len: NULL or the valid count of
 // each row); bmax: NULL, or [rows][bmax_stride] bucket maxima; ids: NULL (item
-// = column), or the item of each column [rows][ids_stride]; negate: the rows
-// are ranked by -phi, and that is what is written; rank_nan: see DenseRows.
-// Rows with fewer than k items are padded with (-inf, -1).
-// NT threads a row.  (1024: two workgroups a CU, at most 64 registers.)
-template <int NT>
+// = column), or the item of each column [rows][ids_stride]; rank_nan: see
+// DenseRows.  Rows with fewer than k items are padded with (-inf, -1).
+// NT threads a row (1024: two workgroups a CU, at most 64 registers).  NEG: the rows are ranked by -phi, and that is what is
+// written (a runtime sign is 500 instructions more, 0.3 us a call).
+template <int NT, bool NEG>
 __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P, long p_rows, int L_all,
                                                            const int32_t* __restrict__ row_len,
                                                            const float* __restrict__ bmax, long bmax_stride, int SL,
                                                            const int32_t* __restrict__ ids, long ids_stride, int k,
-                                                           int negate, int rank_nan, float* __restrict__ out_score,
+                                                           int rank_nan, float* __restrict__ out_score,
                                                            int32_t* __restrict__ out_idx) {
   constexpr int kTopThreads = NT;
   constexpr int kTopCap = 4 * NT;        // keys held in LDS
   constexpr int kTopCoarse = NT / 2;     // largest k ranked by the threads' maxima
   constexpr int kTopHot = 4 * NT;        // buckets collected before their items are read
+  static_assert(NT >= 256 && NT >= kTopRankMax, "a thread a histogram bin, and a key ranked by counting");
   __shared__ uint64_t buf[kTopCap];
   __shared__ uint32_t hist[256];
   __shared__ int hot[kTopHot];
@@ -70,8 +77,7 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
   const float* src = phi + at * phi_stride;
   const int32_t* id = ids ? ids + row * ids_stride : nullptr;
   // (a NaN keeps its payload and takes part in the sign)
-  const uint32_t flip = negate ? 0x80000000u : 0u;
-  auto value = [&](float f) { return __uint_as_float(__float_as_uint(f) ^ flip); };
+  auto value = [](float f) { return NEG ? __uint_as_float(__float_as_uint(f) ^ 0x80000000u) : f; };
   // image of a score: 0 for a column that is not ranked
   auto image = [&](float f) {
     const bool ranked = f == f || (rank_nan && __float_as_uint(f) != kExcludedBits);
@@ -214,7 +220,7 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
     for (int pass = 0; pass < 3 && bits > 0; ++pass) {
       const int shift = max(0, bits - 8);
       __syncthreads();
-      for (int i = tid; i < 256; i += NT) hist[i] = 0u;
+      if (tid < 256) hist[tid] = 0u;
       __syncthreads();
       for_images([&](uint32_t im) {
         if (bits >= 32 || (im >> bits) == (T >> bits))
@@ -251,16 +257,18 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
     const int32_t item = id ? id[col] : col;
     return (static_cast<uint64_t>(u) << 32) | static_cast<uint32_t>(~static_cast<uint32_t>(item));
   };
+  uint32_t top = 0u;                                 // largest image collected
   auto collect = [&](int col, uint32_t u) {
+    top = max(top, u);
     const uint32_t pos = atomicAdd(&s_count, 1u);
     if (pos < static_cast<uint32_t>(kTopCap)) buf[pos] = key_of(u, col);
   };
+  // (a bucket of nothing but NaN only where every column counts)
+  const auto bucket_image = [&](float f) { return f == f ? float_to_ordered(f) : rank_nan ? 1u : 0u; };
   uint32_t hot_n = kTopHot + 1;
   if (bmax) {
     // the buckets that reach T, then their items, a wave a bucket: the loads
     // of all buckets in flight instead of one bucket's after another's
-    // (a bucket of nothing but NaN only where every column counts)
-    const auto bucket_image = [&](float f) { return f == f ? float_to_ordered(f) : rank_nan ? 1u : 0u; };
     for_hits(val, nb, bucket_image, [&](int i, uint32_t) {
       const uint32_t pos = atomicAdd(&s_hot, 1u);
       if (pos < static_cast<uint32_t>(kTopHot)) hot[pos] = i;
@@ -296,7 +304,8 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int e = 0; e < W; ++e) {
-            const uint32_t im = col[u] + e < L ? image(x[u][e]) : 0u;
+            if (col[u] + e >= L || value(x[u][e]) < Tf) continue;
+            const uint32_t im = image(x[u][e]);
             if (im >= T) collect(col[u] + e, im);
           }
       }
@@ -312,32 +321,77 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
         gather(std::integral_constant<int, 1>{});
     }
   }
-  if (hot_n > static_cast<uint32_t>(kTopHot)) for_hits(src, L, image, collect);
+  int cols = L;                                      // the k best lie in the first so many columns
+  if (bmax && hot_n > static_cast<uint32_t>(kTopHot) && T > 1u) {
+    // more items than the list holds, one in each of those buckets (T is a score).  Where no
+    // score is above T, the k lowest columns at T lie in the first k of them: a
+    // histogram over the buckets' places ends the row behind those
+    if (rank_nan) for_hits(src, L, image, [&](int, uint32_t u) { top = max(top, u); });
+    else top = s_hi;
+    if (tid < 256) hist[tid] = 0u;
+    if (tid == 0) s_count = 0u;
+    __syncthreads();
+    if (__any(top > T) && lane == 0) s_count = 1u;
+    int sh = 0;
+    while (nb >> sh >= 256) ++sh;
+    for_hits(val, nb, bucket_image, [&](int i, uint32_t) { atomicAdd(&hist[255 - (i >> sh)], 1u); });
+    __syncthreads();
+    if (s_count == 0u) {
+      find_bin(static_cast<uint32_t>(k));
+      const int last = min(nb, static_cast<int>(256u - s_bin) << sh) - 1;   // a bucket at or behind the k-th
+      cols = min(L, 64 * SL * (last / SL + 1));
+    }
+    __syncthreads();
+    if (tid == 0) s_count = kTopCap + 1u;
+  } else if (hot_n > static_cast<uint32_t>(kTopHot)) {
+    for_hits(src, L, image, collect);
+  }
   __syncthreads();
   uint32_t n = s_count;
   if (n > static_cast<uint32_t>(kTopCap)) {
     // the k-th largest key, 8 bits a pass over the items at or above T (at
-    // least k of them: more than kTopCap >= k reach T)
-    uint64_t prefix = 0;
+    // least k of them: more than kTopCap >= k reach T), from the highest bit in
+    // which they can differ until no more than kTopCap keys are left above
+    s_hi = 0u;                                       // (all write the same)
+    __syncthreads();
+    atomicMax(&s_hi, top);
+    __syncthreads();
+    const uint32_t span = s_hi ^ T;                  // images lie in [T, s_hi]
+    const int ibits = id ? 32 : 32 - __clz(L);       // items: columns up to L, or any
+    int bits = span ? 64 - __clz(static_cast<int>(span)) : ibits;   // low bits of the key that are open
+    auto above = [&](uint64_t key) { return bits < 64 ? key >> bits : 0ull; };
+    uint64_t prefix = bits < 64 ? above(static_cast<uint64_t>(T) << 32 | 0xFFFFFFFFu) << bits : 0ull;
     uint32_t kk = static_cast<uint32_t>(k);
-    for (int shift = 56; shift >= 0; shift -= 8) {
+    while (bits > 0) {
+      const int shift = bits > 32 ? max(32, bits - 8) : max(0, bits - 8);
       __syncthreads();
-      for (int i = tid; i < 256; i += NT) hist[i] = 0u;
+      if (tid < 256) hist[tid] = 0u;
       __syncthreads();
-      for_hits(src, L, image, [&](int col, uint32_t u) {
+      for_hits(src, cols, image, [&](int col, uint32_t u) {
         const uint64_t key = key_of(u, col);
-        if (shift == 56 || (key >> (shift + 8)) == (prefix >> (shift + 8)))
-          atomicAdd(&hist[static_cast<uint32_t>(key >> shift) & 255u], 1u);
+        if (above(key) != above(prefix)) return;
+        // tied scores share a bin: one add for the lanes of the first one's
+        const uint32_t bin = static_cast<uint32_t>(key >> shift) & ((1u << (bits - shift)) - 1u);
+        const uint32_t lead = __builtin_amdgcn_readfirstlane(bin);
+        const uint64_t same = __ballot(bin == lead);
+        if (bin != lead) atomicAdd(&hist[bin], 1u);
+        else if (lane == __ffsll(static_cast<long long>(same)) - 1) atomicAdd(&hist[bin], __popcll(same));
       });
       __syncthreads();
       find_bin(kk);
       kk -= s_above;
       prefix |= static_cast<uint64_t>(s_bin) << shift;
+      bits = shift;
+      if (static_cast<uint32_t>(k) - kk + hist[s_bin] <= static_cast<uint32_t>(kTopCap)) break;
+      if (bits == 32 && !id) {                       // the items' bits above those of L are set
+        prefix |= 0xFFFFFFFFu >> ibits << ibits;
+        bits = ibits;
+      }
     }
     __syncthreads();
     if (tid == 0) s_count = 0u;
     __syncthreads();
-    for_hits(src, L, image, [&](int col, uint32_t u) {
+    for_hits(src, cols, image, [&](int col, uint32_t u) {
       const uint64_t key = key_of(u, col);
       if (key >= prefix) {
         const uint32_t pos = atomicAdd(&s_count, 1u);
@@ -427,8 +481,8 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
   };
   if (ni <= kTopRankMax) {
     // a key's rank is the number of larger ones (keys are distinct)
-    for (int i = tid; i < ni; i += NT) {
-      const uint64_t key = buf[i];
+    if (tid < ni) {
+      const uint64_t key = buf[tid];
       int rank = 0;
       int j = 0;
       for (; j + 8 <= ni; j += 8) {
@@ -526,9 +580,10 @@ hipError_t launch_topk_dense(const DenseRows& r, int rows, int k, float* out_sco
                              hipStream_t st) {
   if (k > kTopkDenseMaxK) return hipErrorInvalidValue;
   const int nt = topk_threads(rows, r.L, k);
-  auto kern = nt == kTopSmall ? &k_topk_dense<kTopSmall> : &k_topk_dense<kTopLarge>;
+  auto kern = nt == kTopSmall ? (r.negate ? &k_topk_dense<kTopSmall, true> : &k_topk_dense<kTopSmall, false>)
+                              : (r.negate ? &k_topk_dense<kTopLarge, true> : &k_topk_dense<kTopLarge, false>);
   hipLaunchKernelGGL(kern, dim3(rows), dim3(nt), 0, st, r.phi, r.phi_stride, r.P, r.p_rows, r.L, r.row_len, r.bmax,
-                     r.bmax_stride, r.SL, r.ids, r.ids_stride, k, r.negate ? 1 : 0, r.rank_nan ? 1 : 0, out_score, out_idx);
+                     r.bmax_stride, r.SL, r.ids, r.ids_stride, k, r.rank_nan ? 1 : 0, out_score, out_idx);
   return hipGetLastError();
 }
 

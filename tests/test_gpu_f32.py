@@ -148,3 +148,76 @@ def test_dense_topk_workgroups(B, N, k, ties):
     torch.cuda.synchronize()
     ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
     assert torch.equal(s, ws[:, :k]) and torch.equal(i.long(), wi[:, :k])
+
+
+# more tied items than the list holds: a query of zeros, ties of the best item,
+# ties behind k / 3 others, two blocks, and ties of a negative score behind five
+# positive ones; both workgroup sizes, with and without bucket maxima
+@pytest.mark.parametrize("B,N,k", [(3, 9000, 100), (3, 20011, 200), (2, 200003, 100), (2, 300003, 2000), (2, 300003, 1),
+                                   (600, 3001, 100), (520, 20000, 128)])
+@pytest.mark.parametrize("tied", ["all", "best", "behind", "two", "negative"])
+def test_dense_topk_ties(B, N, k, tied):
+    log(f"[dense topk ties] B={B} N={N} k={k} {tied}")
+    prob, t = _problem(B, N, 2, 2, 16, 16, torch.float32, seed=N + k)
+    Q, X, a_x = t[0], t[1], t[3]
+    order = torch.argsort(mol.score(prob)[0], descending=True)
+
+    def tie(at, to):
+        X[:, at] = X[:, to:to + 1].clone()
+        a_x[at] = a_x[to:to + 1].clone()
+
+    if tied == "all":
+        Q.zero_()
+    elif tied == "negative":
+        tie(order[5:N - 500], int(order[N - 500]))
+    else:
+        first = k // 3 if tied == "behind" else 0
+        if tied == "two":
+            tie(order[1:k // 2], int(order[0]))
+            first = k // 2
+        tie(order[first:N - 300], int(order[first]))
+    phi = mol.score(prob)
+    s, i = mol.topk_exact(prob, k)
+    torch.cuda.synchronize()
+    ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
+    assert torch.equal(s, ws[:, :k]) and torch.equal(i.long(), wi[:, :k])
+
+
+def test_long_rows_without_scores():
+    """Every column excluded, or all but a few, of more buckets than the
+    selection collects."""
+    prob, _ = _problem(2, 300001, 2, 2, 16, 16, torch.float32, seed=1)
+    m, at = mol.topk_maxdot(prob, 6)
+    s, i = mol.topk_exact_bounded(prob, 100, torch.tensor([torch.inf, (m[1, 4] + 0.01).item()], device="cuda"))
+    torch.cuda.synchronize()
+    assert bool((i[0] == -1).all()) and bool(torch.isneginf(s[0]).all())
+    n = int((i[1] >= 0).sum())
+    assert n < 100 and bool((i[1, n:] == -1).all()) and set(i[1, :n].tolist()) <= set(range(prob.N))
+    assert torch.equal(s[1, :n], mol.score(prob)[1, i[1, :n].long()])
+
+
+def test_rerank_of_tied_candidates():
+    """A query of zeros: the k smallest ids of more candidates than the list holds."""
+    prob, t = _problem(3, 100003, 2, 2, 16, 16, torch.float32)
+    t[0][1].zero_()
+    cand = torch.stack([torch.randperm(prob.N, generator=torch.Generator().manual_seed(b))[:9001] for b in range(3)])
+    s, i, nu = mol.rerank(prob, cand.int().cuda(), 100)
+    torch.cuda.synchronize()
+    assert nu.tolist() == [9001] * 3
+    assert torch.equal(i[1].long().cpu(), torch.sort(cand[1]).values[:100]) and bool((s[1] == 0).all())
+    phi = mol.score(prob)
+    for b in (0, 2):
+        assert torch.equal(s[b], torch.sort(phi[b, cand[b].cuda()], descending=True).values[:100])
+
+
+@pytest.mark.parametrize("B", [1, 8, 16])     # four, two and one slices of bucket maxima
+def test_query_of_zeros(B):
+    """Every item tied, of more buckets than the selection collects: the first k."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    r = lambda *s: 0.1 * torch.randn(s, generator=g, device="cuda")   # noqa: E731
+    Q, X = r(B, 8, 32).bfloat16(), r(8, 400003, 32).bfloat16()
+    Q[B - 1] = 0
+    prob = mol.Problem(Q, X, r(B, 64), r(400003, 64), r(64, 64).bfloat16(), r(64), r(64, 64).bfloat16(), r(64))
+    s, i = mol.topk_exact(prob, 100)
+    torch.cuda.synchronize()
+    assert bool((s[B - 1] == 0).all()) and torch.equal(i[B - 1].long().cpu(), torch.arange(100))
