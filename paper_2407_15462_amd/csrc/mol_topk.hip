@@ -16,9 +16,9 @@
 // which they can differ, counts the lanes of one bin with one add, ends where
 // the list holds the rest, and with nothing but ties above reads only the
 // buckets that hold the first k of them.  (All 64 bits, one add a lane, and every
-// score a pass: 32 rows of 100,000 equal scores 721 us, now 169, with the chunked
+// score a pass: 32 rows of 100,000 equal scores 721 us, now 190, with the chunked
 // radix selection of keys 257; one query of zeros against 2^20 items of 8 x 8, d
-// = 64 6,460 us in all, now 286, with per-range lists 653.)
+// = 64 6,460 us in all, now 283, with per-range lists 653.)
 //
 // What bounds it: one read of the row at a workgroup's rate (about 100 GB/s)
 // and a dozen barriers.  With per-bucket maxima from the kernel that scored
@@ -257,9 +257,7 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
     const int32_t item = id ? id[col] : col;
     return (static_cast<uint64_t>(u) << 32) | static_cast<uint32_t>(~static_cast<uint32_t>(item));
   };
-  uint32_t top = 0u;                                 // largest image collected
   auto collect = [&](int col, uint32_t u) {
-    top = max(top, u);
     const uint32_t pos = atomicAdd(&s_count, 1u);
     if (pos < static_cast<uint32_t>(kTopCap)) buf[pos] = key_of(u, col);
   };
@@ -304,8 +302,7 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int e = 0; e < W; ++e) {
-            if (col[u] + e >= L || value(x[u][e]) < Tf) continue;
-            const uint32_t im = image(x[u][e]);
+            const uint32_t im = col[u] + e < L ? image(x[u][e]) : 0u;
             if (im >= T) collect(col[u] + e, im);
           }
       }
@@ -321,41 +318,35 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
         gather(std::integral_constant<int, 1>{});
     }
   }
-  int cols = L;                                      // the k best lie in the first so many columns
-  if (bmax && hot_n > static_cast<uint32_t>(kTopHot) && T > 1u) {
-    // more items than the list holds, one in each of those buckets (T is a score).  Where no
-    // score is above T, the k lowest columns at T lie in the first k of them: a
-    // histogram over the buckets' places ends the row behind those
-    if (rank_nan) for_hits(src, L, image, [&](int, uint32_t u) { top = max(top, u); });
-    else top = s_hi;
-    if (tid < 256) hist[tid] = 0u;
-    if (tid == 0) s_count = 0u;
-    __syncthreads();
-    if (__any(top > T) && lane == 0) s_count = 1u;
-    int sh = 0;
-    while (nb >> sh >= 256) ++sh;
-    for_hits(val, nb, bucket_image, [&](int i, uint32_t) { atomicAdd(&hist[255 - (i >> sh)], 1u); });
-    __syncthreads();
-    if (s_count == 0u) {
+  // (one item at least in each of more buckets than the list has places; T > 1: a score)
+  const bool over = bmax && hot_n > static_cast<uint32_t>(kTopHot) && T > 1u;
+  if (!over && hot_n > static_cast<uint32_t>(kTopHot)) for_hits(src, L, image, collect);
+  __syncthreads();
+  uint32_t n = over ? kTopCap + 1u : s_count;
+  if (n > static_cast<uint32_t>(kTopCap)) {
+    int cols = L;                                    // the k best lie in the first so many columns
+    if (rank_nan) {                                  // the largest image may be a NaN's
+      uint32_t top = 0u;
+      for_hits(src, L, image, [&](int, uint32_t u) { top = max(top, u); });
+      atomicMax(&s_hi, top);
+      __syncthreads();
+    }
+    if (over && s_hi == T) {
+      // nothing above T: the k lowest columns at T lie in the first k of those
+      // buckets, and a histogram over their places ends the row behind them
+      if (tid < 256) hist[tid] = 0u;
+      __syncthreads();
+      int sh = 0;
+      while (nb >> sh >= 256) ++sh;
+      for_hits(val, nb, bucket_image, [&](int i, uint32_t) { atomicAdd(&hist[255 - (i >> sh)], 1u); });
+      __syncthreads();
       find_bin(static_cast<uint32_t>(k));
       const int last = min(nb, static_cast<int>(256u - s_bin) << sh) - 1;   // a bucket at or behind the k-th
       cols = min(L, 64 * SL * (last / SL + 1));
     }
-    __syncthreads();
-    if (tid == 0) s_count = kTopCap + 1u;
-  } else if (hot_n > static_cast<uint32_t>(kTopHot)) {
-    for_hits(src, L, image, collect);
-  }
-  __syncthreads();
-  uint32_t n = s_count;
-  if (n > static_cast<uint32_t>(kTopCap)) {
     // the k-th largest key, 8 bits a pass over the items at or above T (at
     // least k of them: more than kTopCap >= k reach T), from the highest bit in
     // which they can differ until no more than kTopCap keys are left above
-    s_hi = 0u;                                       // (all write the same)
-    __syncthreads();
-    atomicMax(&s_hi, top);
-    __syncthreads();
     const uint32_t span = s_hi ^ T;                  // images lie in [T, s_hi]
     const int ibits = id ? 32 : 32 - __clz(L);       // items: columns up to L, or any
     int bits = span ? 64 - __clz(static_cast<int>(span)) : ibits;   // low bits of the key that are open
