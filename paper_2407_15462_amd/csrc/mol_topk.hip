@@ -11,14 +11,15 @@
 // (3,375 of the list's 4,096 slots at k = 2048).  Those are collected in LDS,
 // ranked by counting (long lists inside bins of the score range) and written
 // out.  A row whose items reaching T exceed the LDS list (massive ties, as a
-// query of zeros makes them, or an adversarial order) is finished by a radix
-// search over its 64-bit sort keys, 8 bits a pass, that begins at the bits in
-// which they can differ, counts the lanes of one bin with one add, ends where
-// the list holds the rest, and with nothing but ties above reads only the
-// buckets that hold the first k of them.  (All 64 bits, one add a lane, and every
-// score a pass: 32 rows of 100,000 equal scores 721 us, now 190, with the chunked
-// radix selection of keys 257; one query of zeros against 2^20 items of 8 x 8, d
-// = 64 6,460 us in all, now 283, with per-range lists 653.)
+// query of zeros makes them, or the best items side by side) is finished by a
+// radix search over its 64-bit sort keys, 8 bits a pass: it begins at the bits in
+// which they can differ, reads only the buckets that reach T while their list
+// holds them, and with nothing but ties above only the columns of the first k,
+// counts the lanes of one bin with one add and ends where the list holds the
+// rest.  (All 64 bits, every score a pass, one add a lane -> now, and the list
+// form or the chunked radix selection of keys: 32 rows of 100,000 equal scores
+// 721 -> 230, 257 us; a query of zeros against 2^20 items of 8 x 8, d = 64, in
+// all, 6,460 -> 284, 653; one ascending row of 2^20 2,069 -> 109, 136.)
 //
 // What bounds it: one read of the row at a workgroup's rate (about 100 GB/s)
 // and a dozen barriers.  With per-bucket maxima from the kernel that scored
@@ -323,11 +324,25 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
   if (!over && hot_n > static_cast<uint32_t>(kTopHot)) for_hits(src, L, image, collect);
   __syncthreads();
   uint32_t n = over ? kTopCap + 1u : s_count;
-  if (n > static_cast<uint32_t>(kTopCap)) {
+  if (__builtin_expect(n > static_cast<uint32_t>(kTopCap), 0)) {
     int cols = L;                                    // the k best lie in the first so many columns
+    // f(column, image) of the items at or above T: the buckets' in `hot`, else the columns'
+    auto for_items = [&](auto&& f) {
+      if (hot_n > static_cast<uint32_t>(kTopHot)) {
+        for_hits(src, cols, image, f);
+        return;
+      }
+#pragma unroll 1
+      for (int t = tid; t < 64 * static_cast<int>(hot_n); t += kTopThreads) {
+        const int bk = hot[t >> 6], blk = bk / SL;
+        const int col = 16 * (4 * SL * blk + (bk - blk * SL) + SL * (t >> 4 & 3)) + (t & 15);
+        const uint32_t im = col < L ? image(src[col]) : 0u;
+        if (im >= T) f(col, im);
+      }
+    };
     if (rank_nan) {                                  // the largest image may be a NaN's
       uint32_t top = 0u;
-      for_hits(src, L, image, [&](int, uint32_t u) { top = max(top, u); });
+      for_items([&](int, uint32_t u) { top = max(top, u); });
       atomicMax(&s_hi, top);
       __syncthreads();
     }
@@ -358,7 +373,7 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
       __syncthreads();
       if (tid < 256) hist[tid] = 0u;
       __syncthreads();
-      for_hits(src, cols, image, [&](int col, uint32_t u) {
+      for_items([&](int col, uint32_t u) {
         const uint64_t key = key_of(u, col);
         if (above(key) != above(prefix)) return;
         // tied scores share a bin: one add for the lanes of the first one's
@@ -382,7 +397,7 @@ __global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ 
     __syncthreads();
     if (tid == 0) s_count = 0u;
     __syncthreads();
-    for_hits(src, cols, image, [&](int col, uint32_t u) {
+    for_items([&](int col, uint32_t u) {
       const uint64_t key = key_of(u, col);
       if (key >= prefix) {
         const uint32_t pos = atomicAdd(&s_count, 1u);

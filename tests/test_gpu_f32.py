@@ -183,6 +183,21 @@ def test_dense_topk_ties(B, N, k, tied):
     assert torch.equal(s, ws[:, :k]) and torch.equal(i.long(), wi[:, :k])
 
 
+@pytest.mark.parametrize("B,N,k", [(2, 200003, 100), (520, 20000, 100), (2, 300003, 2000)])
+def test_dense_topk_of_sorted_rows(B, N, k):
+    """The best items side by side: more items reach the threshold than the
+    list holds, in buckets that it does."""
+    prob, t = _problem(B, N, 2, 2, 16, 16, torch.float32, seed=N + k)
+    order = torch.argsort(mol.score(prob)[0], descending=True)
+    t[1].copy_(t[1][:, order].clone())
+    t[3].copy_(t[3][order].clone())
+    phi = mol.score(prob)
+    s, i = mol.topk_exact(prob, k)
+    torch.cuda.synchronize()
+    ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
+    assert torch.equal(s, ws[:, :k]) and torch.equal(i.long(), wi[:, :k])
+
+
 def test_long_rows_without_scores():
     """Every column excluded, or all but a few, of more buckets than the
     selection collects."""
@@ -212,7 +227,8 @@ def test_rerank_of_tied_candidates():
 
 @pytest.mark.parametrize("B", [1, 8, 16])     # four, two and one slices of bucket maxima
 def test_query_of_zeros(B):
-    """Every item tied, of more buckets than the selection collects: the first k."""
+    """Every item tied, of more buckets than the selection collects: the first k.
+    Then the corpus in the order of a query's scores."""
     g = torch.Generator(device="cuda").manual_seed(1)
     r = lambda *s: 0.1 * torch.randn(s, generator=g, device="cuda")   # noqa: E731
     Q, X = r(B, 8, 32).bfloat16(), r(8, 400003, 32).bfloat16()
@@ -221,3 +237,12 @@ def test_query_of_zeros(B):
     s, i = mol.topk_exact(prob, 100)
     torch.cuda.synchronize()
     assert bool((s[B - 1] == 0).all()) and torch.equal(i[B - 1].long().cpu(), torch.arange(100))
+    if B > 1:
+        order = torch.argsort(mol.score(prob)[0], descending=True)
+        prob = mol.Problem(Q, X[:, order].contiguous(), r(B, 64), r(400003, 64), *[x.zero_() for x in (
+            r(64, 64).bfloat16(), r(64), r(64, 64).bfloat16(), r(64))])
+    phi = mol.score(prob)
+    s, i = mol.topk_exact(prob, 100)
+    torch.cuda.synchronize()
+    ws, wi = torch.sort(phi, dim=1, descending=True, stable=True)
+    assert torch.equal(s, ws[:, :100]) and torch.equal(i.long(), wi[:, :100])
