@@ -115,10 +115,11 @@ typedef enum {
  *    of RMS up to 1.  bf16 shapes without a fused kernel take the same
  *    two-term chain in the pair-wise kernel (P <= 64, H <= 128), others
  *    the float32 path below.
- *  - MOL_FLAG_F32_GATING: the gating MLP, softmax and phi run in float32 in
- *    the pair-wise kernel (component dots still on matrix cores, exact
- *    products, float32 sums), more than ten times slower than the fused
- *    path, with no limit on the weights.  It takes precedence when both
+ *  - MOL_FLAG_F32_GATING: the gating MLP, softmax and phi run in float32 on
+ *    f32 matrix instructions (component dots from exact products, float32
+ *    sums), with no limit on the weights: mol_score of 16 x 524,288 pairs of
+ *    8 x 8 components, d = 64, H = 64 takes 1.78 ms against 0.34 ms by
+ *    default and 0.45 ms on two bf16 terms.  It takes precedence when both
  *    flags are set.
  * float32 problems always take the float32 path. */
 typedef struct mol_problem {
@@ -307,13 +308,15 @@ int mol_gap_bound_combined(int32_t B, int32_t P, int32_t m, const float *dots,
 
 /* Kernel timing, a diagnostic for throughput measurements.
  * mol_timing_enable(1) makes every later call record a pair of HIP events on
- * its stream around its main kernel: the fused scoring kernel of mol_score,
- * the scoring + per-range top-k scan of mol_topk_exact (and of
- * mol_topk_exact_bounded, mol_topk_maxdot), the whole sequence of
- * mol_topk_two_pass, the two
- * per-component scans (with the threshold selection between them) of
- * mol_topk_per_embd and the candidate scoring of mol_rerank
- * (validation, merges of partial lists and decoding are outside the pair).
+ * its stream around its main kernel: the scoring kernel of mol_score, of
+ * mol_topk_exact, mol_topk_exact_bounded and mol_topk_maxdot (with the
+ * per-range lists where the call keeps those; alone where it stores dense
+ * scores; one pair for each slab of queries or tile of items where it runs in
+ * several, all counted by mol_timing_read), the whole sequence of
+ * mol_topk_two_pass, the per-component scans (with the threshold selection
+ * between them) or the dot products of mol_topk_per_embd and the candidate
+ * scoring of mol_rerank (validation, the selection from dense scores, merges of
+ * partial lists and decoding are outside the pair).
  * mol_timing_enable(0) stops recording; records already taken stay.
  * mol_timing_read(op, &ms, &n) waits for the recorded events of operation
  * `op` (a mol_op code), writes their summed duration in milliseconds and

@@ -109,7 +109,8 @@ __global__ __launch_bounds__(128 * WV, 2) void k_dots_phi(DevProb pr, const floa
   if (nk > 1) stage(1);
   for (int i = tid; i < nq * P; i += 64 * S::W) sAq[i] = pr.a_q[static_cast<long>(b0) * P + i];
 
-  // the gating operands, whose reads the K loop covers
+  // the gating operands (their conversion to float16 waits here for their reads,
+  // and for the first two stages with them)
   const int ci = lane & 15, g = lane >> 4;
   Mlp mlp;
   mlp.load_padded(pr, ci, g);

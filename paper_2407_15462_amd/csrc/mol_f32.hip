@@ -28,8 +28,8 @@
 // registers than H = 16 and four waves a SIMD stay resident.  Measured: 32 x
 // 65,537 pairs of 4 x 4 float32 components, d = 64, H = 32: 0.158 ms (one
 // thread a pair, scalar dot products: 29.8 ms); 16 x 32,768 pairs of 8 x 8 bf16
-// components, d = 64, H = 64: 0.131 ms (7.1 ms).  About a third of the matrix
-// rate: the rest is the latency of each tile's item rows and the two barriers
+// components, d = 64, H = 64: 0.121 ms (7.1 ms).  A third and not quite half of
+// the f32 matrix rate: the rest is the latency of each tile's item rows and the two barriers
 // of a tile, which the other workgroups of the CU cover only in part.
 #include "mol_tile.h"
 

@@ -53,7 +53,8 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 // query-vector blocks of 32 per wave, chosen so that the B operands and two
 // tiles' accumulators stay in registers: 4 in the bucket scan at d = 64,
-// 2 otherwise (the threshold scan also keeps staging state)
+// 2 otherwise (the threshold scan also keeps staging state); the pruned pass
+// with 4 at d = 64 spills 11 registers
 constexpr int nb_for(int d, bool scan2) { return (d >= 128 || scan2) ? 2 : 4; }
 // small batches (at most 256 query vectors) use one block per wave, so that
 // no wave multiplies empty vector slots

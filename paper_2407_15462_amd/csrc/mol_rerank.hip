@@ -5,8 +5,8 @@
 // walks it 16 items at a time: the items' component embeddings are gathered
 // from the component-major corpus one step ahead, by direct global -> LDS
 // copies (one 16-byte copy per lane per component and K block) into a
-// buffer of the wave (Px d / 32 KB), and read back as MFMA operands at the start of their
-// step (their gating logits a_x are prefetched into registers);
+// buffer of the wave (Px d / 32 KB), and read back as MFMA operands at the start
+// of their step (their gating logits a_x are prefetched into registers);
 // GEMM1 forms the 8 x 16 dot products of the query's components with the
 // items' components in rows 2 pq of the 16x16x32 tile (the odd rows are
 // zero), which leaves them in the run layout of mol_tile.h, and the shared
@@ -157,9 +157,13 @@ bool rerank_supported(const DevProb& pr) { return fused_supported(pr, 1); }
 
 // Candidates per wave: the largest power of two from 4096 down to 32 that
 // still gives three quarters of a round of resident waves (two 4-wave workgroups
-// per CU on 256 CUs; 32 x 14,800: 97 us with 256 a wave, 104 with 128), so that long lists amortise each wave's operand set-up and
+// per CU on 256 CUs), so that long lists amortise each wave's operand set-up and
 // small batches still fill the chip (8 queries x 1260 candidates: 49 us with
-// 256 a wave, 12 us with 32; 64 x 640: 32 and 13 us).  With the candidates in
+// 256 a wave, 12 us with 32; 64 x 640: 32 and 13 us).  The line is a compromise;
+// kernel us with 3/8, 1/2, 3/4 and a whole round: 32 x 14,800 of 8 x 8, d = 32
+// 87, 89, 89, 92; 300 x 1000 of 8 x 4, d = 64 45, 46, 38, 38; 64 x 8192 of 8 x 8,
+// d = 64 113, 114, 117, 118; 1024 x 1024 199, 199, 217, 218; 256 x 8192 of 8 x 4,
+// d = 128 315, 316, 346, 345.  With the candidates in
 // ascending id bins (the dedup's output order) and every wave resident at
 // once, the waves sweep the corpus together and the several queries that share
 // an item gather it close in time (exact_1m: 1.67 ms with 2048, 1.52 ms with

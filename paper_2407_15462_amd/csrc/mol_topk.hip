@@ -52,10 +52,13 @@ __device__ __forceinline__ uint32_t score_image(float f) { return f == f ? float
 // each row); bmax: NULL, or [rows][bmax_stride] bucket maxima; ids: NULL (item
 // = column), or the item of each column [rows][ids_stride]; rank_nan: see
 // DenseRows.  Rows with fewer than k items are padded with (-inf, -1).
-// NT threads a row (1024: two workgroups a CU, at most 64 registers).  NEG: the rows are ranked by -phi, and that is what is
-// written (a runtime sign is 500 instructions more, 0.3 us a call).
+// NT threads a row (1024: two workgroups a CU, at most 64 registers; 8 to 16
+// are spilled, in the binned sort and the radix finish).  NEG: the rows are ranked by
+// -phi, and that is what is written (a runtime sign is 500 instructions more,
+// 0.3 us a call).
 template <int NT, bool NEG>
-__global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P, long p_rows, int L_all,
+__global__ __launch_bounds__(NT, 8) void k_topk_dense(const float* __restrict__ phi, long phi_stride, int P,
+                                                           long p_rows, int L_all,
                                                            const int32_t* __restrict__ row_len,
                                                            const float* __restrict__ bmax, long bmax_stride, int SL,
                                                            const int32_t* __restrict__ ids, long ids_stride, int k,
